@@ -1122,7 +1122,9 @@ bool ys_shape(const cisigma_ctx *c, size_t *rows, size_t *cols) {
         if (c->sp[s].nel >= 2) {
             *rows = std::max(*rows, size_t(c->sp[s].nK) * c->sp[s].npv);
             *cols = std::max(*cols, size_t(c->pl[s].ld[0]));
-            ok = ok && cis::same_spin_materialisable(c->sp[s].npv);
+            // (the inverse pair table the gather reads is built for at most 64 occupied
+            // pairs per string: with 12 electrons and more the atomic kernels run)
+            ok = ok && cis::same_spin_materialisable(c->sp[s].npv) && c->sp[s].d_pair_inv;
         }
     return ok && *rows > 0;
 }
