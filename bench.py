@@ -4,7 +4,8 @@
 One step = one full sigma build (sigma_1 + sigma_2 + sigma_3 of Eq. 8, with the
 layout conversions) through cisigma_apply on a device-resident CI vector.
 Prints one JSON line with
-  * value: sigma builds/s of the FP32 path (FP32 MFMA, FP32 accumulation);
+  * value: sigma builds/s of the FP32 path (FP32 accumulation; the alpha-beta
+    products as exact bf16 splits of the FP32 operands);
   * roofline: the alpha-beta contraction kernel (the dominant one) against the
     FP32 matrix-core peak, its duration measured with HIP events on its own
     stream over the timed region; its numerator is the method's own work, the
@@ -279,8 +280,8 @@ def stored_traffic(kernel_tag):
     taken (the summary records the source's SHA-256)."""
     import hashlib
     csrc = os.path.join(ROOT, "paper_1707_04346_amd", "csrc")
-    one_block = kernel_tag in ("k_sigma_ab_ws", "k_sigma_ab_x")
-    srcs = [os.path.join(csrc, f) for f in (("sigma_abx.hip", "abx.h") if one_block else ("sigma_ab.hip",))]
+    one_block = kernel_tag == "k_sigma_ab_s"
+    srcs = [os.path.join(csrc, f) for f in (("sigma_abs.hip", "scatter_prog.h", "split.h") if one_block else ("sigma_ab.hip",))]
     prof = os.path.join(ROOT, "profiles", f"{kernel_tag}_cas16_fp32_traffic.txt")
     if not (all(os.path.exists(f) for f in srcs) and os.path.exists(prof)):
         return None
@@ -559,13 +560,10 @@ def main():
     ab_s = pp32["sigma_ab"] / 1e3
     achieved = flops / ab_s / 1e12
     owner = bool(path32 & cis.PATH_AB_OWNER)
-    shared = bool(path32 & cis.PATH_AB_SHARED_CU)
-    tag = ("k_sigma_ab_x" if shared else "k_sigma_ab_ws") if owner else "k_sigma_ab"
-    kdesc = {"k_sigma_ab_x": "k_sigma_ab_x (owner-computes sigma_3, one-W-tile form, two workgroups per CU: "
-                             "gathered C rows -> FP32 MFMA on six waves over three SIMDs, LDS scatter on two "
-                             "waves on the fourth)",
-             "k_sigma_ab_ws": "k_sigma_ab_ws (owner-computes sigma_3: gathered C rows -> FP32 MFMA on six waves "
-                              "over three SIMDs, LDS scatter on two waves on the fourth)",
+    tag = "k_sigma_ab_s" if owner else "k_sigma_ab"
+    kdesc = {"k_sigma_ab_s": "k_sigma_ab_s (owner-computes sigma_3: gathered C rows, split into bf16 parts -> six bf16 "
+                             "MFMA products per FP32 product, LDS scatter; two workgroups per CU; the fraction is of "
+                             "the FP32 matrix peak)",
              "k_sigma_ab": "k_sigma_ab (sigma_3 gather -> FP32 MFMA -> atomic scatter)"}
     roofline = {"bound": "mfma", "achieved": achieved, "peak": PEAK["fp32"], "unit": "TFLOP/s",
                 "frac": achieved / PEAK["fp32"],

@@ -78,9 +78,8 @@ extern "C" {
 #define CISIGMA_OPT_SIGMA_PATH 8   /* 0: automatic kernel choice; 1: only the general (scatter-atomic) kernels;
                                       2: for one-block spaces, the owner-computes units of the GAS form
                                       in place of the one-block owner kernel (rebuilds the unit tables);
-                                      3: as 0, but the one-block owner kernel in FP32 in its two-W-tile
-                                      form (one workgroup per compute unit) even where two workgroups of
-                                      the one-W-tile form would fit */
+                                      3: as 0, but the one-block owner kernel in FP32 with one workgroup
+                                      per compute unit even where two would fit */
 #define CISIGMA_OPT_UNIT_LAUNCH 19 /* owner-computes units: 0 (default) one launch over every unit, longest
                                       rows of work first; 1: one launch per unit, in the same order (the
                                       per-block launch baseline) */
@@ -427,17 +426,19 @@ int cisigma_pass_times(cisigma_ctx *ctx, double *ms, int *ncalls);
  */
 #define CISIGMA_PATH_AB_OWNER 1          /* sigma_3 by the owner-computes kernel (no global atomics) */
 #define CISIGMA_PATH_SS_MATERIALISED 2   /* same-spin parts by materialised pair products + gather */
-#define CISIGMA_PATH_AB_SHARED_CU 4      /* sigma_3 by the one-block owner kernel in its one-W-tile form, two
-                                            workgroups per compute unit (FP32, where two fit) */
+#define CISIGMA_PATH_AB_SHARED_CU 4      /* sigma_3 by the one-block owner kernel with two workgroups per
+                                            compute unit (FP32, where two fit) */
 int cisigma_last_path(const cisigma_ctx *ctx, int dtype, int *flags);
 
 /*
  * cisigma_last_shape -- the compiled shape of the owner-computes sigma_3
  * kernel (the alpha-beta part of Eq. 8) that the most recent cisigma_apply of
  * dtype launched, for tests that must know which variant ran:
- *   shape[0]  k steps of gathered alpha rows (4 rows each)
+ *   shape[0]  k steps of gathered alpha rows (4 rows each; the FP32 one-block
+ *             kernel multiplies 32 rows at a time and reports the same count)
  *   shape[1]  16-row blocks of orbital pairs
- *   shape[2]  scatter-plan entries per lane and tile
+ *   shape[2]  scatter-plan entries per lane and tile (FP32 one-block kernel: those
+ *             a plan of equal runs per lane would take)
  *   shape[3]  0: no owner-computes kernel ran (general kernel); 1: one-block
  *             kernel with the own row in a k step; 2: one-block kernel with the
  *             own row as the rank-1 start of the accumulators; 3: units of

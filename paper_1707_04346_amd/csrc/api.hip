@@ -13,11 +13,16 @@
 #include <functional>
 #include <cmath>
 #include <cstdio>
+#include <atomic>
 #include <cstring>
+#include <exception>
 #include <mutex>
 #include <new>
+#include <system_error>
+#include <thread>
 
 #include "internal.h"
+#include "scatter_prog.h"
 
 #define CIS_API extern "C" __attribute__((visibility("default")))
 
@@ -139,6 +144,7 @@ void free_ctx(cisigma_ctx *c) {
     (void)hipFree(c->bt.blk); (void)hipFree(c->bt.tb); (void)hipFree(c->bt.tr); (void)hipFree(c->bt.tc);
     (void)hipFree(c->d_pblk); (void)hipFree(c->d_blkoff);
     (void)hipFree(c->plan.d_entries[0]); (void)hipFree(c->plan.d_entries[1]);
+    (void)hipFree(c->prog.d_words);
     (void)hipFree(c->d_act_start); (void)hipFree(c->d_act_tiles);
     (void)hipFree(c->go.d_slot); (void)hipFree(c->go.d_coff); (void)hipFree(c->go.d_g32); (void)hipFree(c->go.d_g64);
     for (int d = 0; d < 2; ++d) {
@@ -410,13 +416,47 @@ struct PlanTiles {
     int need = 1;
 };
 
+// f(t) for every t in [0, n), on up to eight threads (the tiles of a plan are
+// independent, and planning them is most of the host time of cisigma_init); an
+// exception of a worker is thrown again here
+template <typename F>
+void for_tiles(int n, const F &f) {
+    const int nt = std::min({8, int(std::thread::hardware_concurrency()), n / 32});
+    if (nt < 2) {
+        for (int t = 0; t < n; ++t) f(t);
+        return;
+    }
+    std::atomic<int> next{0};
+    std::exception_ptr err;
+    std::mutex m;
+    auto work = [&]() {
+        try {
+            for (int t; (t = next.fetch_add(8)) < n;)
+                for (int i = t; i < std::min(n, t + 8); ++i) f(i);
+        } catch (...) {
+            std::lock_guard<std::mutex> lock(m);
+            if (!err) err = std::current_exception();
+            next = n;
+        }
+    };
+    std::vector<std::thread> pool;
+    try {
+        pool.reserve(size_t(nt - 1));
+        for (int i = 1; i < nt; ++i) pool.emplace_back(work);
+    } catch (const std::exception &) {
+    }                                       // fewer threads (none: this one does it all)
+    work();
+    for (std::thread &t : pool) t.join();
+    if (err) std::rethrow_exception(err);
+}
+
 int plan_items(cisigma_ctx *c, const PlanSpec &ps, const std::vector<uint32_t> &exc, const std::vector<uint32_t> &str,
                PlanTiles &out) {
     constexpr int WS = 33;
     const auto &B = c->sp[1];
     out.tiles.assign(ps.ntile, {});
-    out.need = 1;
-    for (int t = 0; t < ps.ntile; ++t) {
+    std::vector<int> needs(size_t(ps.ntile), 1);
+    for_tiles(ps.ntile, [&](int t) {
         auto &tile = out.tiles[t];
         for (int col = 0; col < 32; ++col) {
             const int Jb = ps.source(t, col);
@@ -456,8 +496,10 @@ int plan_items(cisigma_ctx *c, const PlanSpec &ps, const std::vector<uint32_t> &
             }
             return ranges <= 4;
         };
-        while (!fits(size_t(64) * out.need)) ++out.need;
-    }
+        while (!fits(size_t(64) * needs[t])) ++needs[t];
+    });
+    out.need = 1;
+    for (int v : needs) out.need = std::max(out.need, v);
     return CISIGMA_OK;
 }
 
@@ -553,14 +595,8 @@ int plan_tables(cisigma_ctx *c, std::vector<uint32_t> &exc, std::vector<uint32_t
     return CISIGMA_OK;
 }
 
-// Builds the two encodings of a scatter plan into P (P.ew = 0: no plan).
-int make_scatter_plan(cisigma_ctx *c, const PlanSpec &ps, cis::ScatterPlan &P) {
-    std::vector<uint32_t> exc, str;
-    int rc = plan_tables(c, exc, str);
-    if (rc) return rc;
-    PlanTiles pt;
-    rc = plan_items(c, ps, exc, str, pt);
-    if (rc) return rc;
+// Builds the FP64 encoding of a scatter plan into P (P.ew = 0: no plan).
+int make_scatter_plan(cisigma_ctx *c, const PlanSpec &ps, const PlanTiles &pt, cis::ScatterPlan &P) {
     int ew = 0;
     for (int cand : {ps.width(pt.need), 16})
         if (cand >= pt.need && ps.width(cand) == cand && plan_fits(pt, cand)) { ew = cand; break; }
@@ -568,9 +604,42 @@ int make_scatter_plan(cisigma_ctx *c, const PlanSpec &ps, cis::ScatterPlan &P) {
     std::vector<uint32_t> plan[2];
     plan_emit(ps, pt, ew, plan);
     HIP_OR_FAIL(c, upload(&P.d_entries[0], plan[0]), "init: scatter plan");
-    HIP_OR_FAIL(c, upload(&P.d_entries[1], plan[1]), "init: scatter plan");
     P.ntile = ps.ntile;
     P.ew = ew;
+    return CISIGMA_OK;
+}
+
+// The first compiled program that every tile of the space fits.
+int build_scatter_prog(cisigma_ctx *c, const PlanTiles &pt) {
+    constexpr int WS = 33, WS32 = 36;   // W row strides of the items and of the FP32 kernel
+    const int rb = (c->npair + 15) / 16;
+    cis::ProgLayout L{};
+    L.zero = 32;
+    L.scratch = uint32_t(16 * rb * WS32);
+    L.spare = uint32_t(c->pl[0].ld[0]);
+    L.bytes = 4;
+    L.unit = L.sunit = 1;
+    std::vector<std::vector<cis::ProgItem>> tiles(pt.tiles.size());
+    for (size_t t = 0; t < tiles.size(); ++t)
+        for (const PlanItem &it : pt.tiles[t])
+            tiles[t].push_back({it.tgt, it.widx / WS * WS32 + it.widx % WS, it.neg});
+    for (int g = 0; g < cis::kNumProgs; ++g) {
+        if (!cis::sigma_ab_split_prog(rb, g)) continue;
+        const size_t per = size_t(cis::kProgWaves) * cis::kProgs[g].words() * cis::kProgLanes;
+        std::vector<uint32_t> words(per * tiles.size());
+        std::atomic<bool> ok{true};
+        for_tiles(int(tiles.size()), [&](int t) {
+            std::vector<uint32_t> w;
+            if (ok && cis::prog_pack(cis::kProgs[g], L, tiles[t], w)) std::copy(w.begin(), w.end(), words.begin() + per * t);
+            else ok = false;
+        });
+        if (!ok) continue;
+        HIP_OR_FAIL(c, upload(&c->prog.d_words, words), "init: scatter program");
+        c->prog.ntile = int(tiles.size());
+        c->prog.prog = g;
+        cis::sigma_ab_owner_shape(c->sp[0].nexc, c->npair, c->plan.ew ? c->plan.ew : 16, c->prog.shape);
+        break;
+    }
     return CISIGMA_OK;
 }
 
@@ -592,7 +661,15 @@ int build_scatter_plan(cisigma_ctx *c) {
     ps.unit[1] = 1;
     const int anexc = c->sp[0].nexc, npair = c->npair;
     ps.width = [=](int need) { return cis::sigma_ab_owner_width(anexc, npair, need); };
-    return make_scatter_plan(c, ps, c->plan);
+    std::vector<uint32_t> exc, str;
+    int rc = plan_tables(c, exc, str);
+    if (rc) return rc;
+    PlanTiles pt;
+    rc = plan_items(c, ps, exc, str, pt);
+    if (rc) return rc;
+    rc = make_scatter_plan(c, ps, pt, c->plan);
+    if (rc) return rc;
+    return build_scatter_prog(c, pt);
 }
 
 

@@ -147,6 +147,15 @@ struct ScatterPlan {
     int ew = 0;                                    // entries per lane and tile (0: no plan)
 };
 
+// The scatter of the one-block sigma_3 kernel in FP32 as a program of rounds
+// (scatter_prog.h): every tile's words, [ntile][4 waves][words][64 lanes].
+struct ProgPlan {
+    uint32_t *d_words = nullptr;   // nullptr: none
+    int ntile = 0;
+    int prog = 0;                  // index into kProgs
+    int shape[4] = {0, 0, 0, 0};   // what cisigma_last_shape reports
+};
+
 // Owner-computes sigma_3 for GAS spaces: W rows are the orbital pairs grouped
 // by the GAS spaces of their two orbitals, the gathered rows of an alpha string
 // are its single excitations grouped by source type, and every alpha type has
@@ -225,6 +234,7 @@ struct cisigma_ctx {
     cis::Workspace ws[2];          // per dtype (0 FP64, 1 FP32)
     cis::BlockTilesDev bt{};       // tiles of the caller-layout blocks
     cis::ScatterPlan plan;         // beta-side scatter plan of the owner-computes sigma_3 kernel
+    cis::ProgPlan prog;            // the same for the FP32 kernel
     // general sigma_3 kernel: per alpha type, the 64-column beta tiles that can
     // change sigma (CSR over alpha types; all tiles for one-block spaces)
     int *d_act_start = nullptr;    // [ntype_a + 1]
@@ -255,7 +265,7 @@ struct cisigma_ctx {
     int log_calls = 0;             // Davidson calls logged so far
     int last_path[2] = {0, 0};     // CISIGMA_PATH_* flags of the last apply, [FP64, FP32]
     int last_shape[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};   // owner-computes sigma_3 shape of the last apply
-    int abx_shared[2] = {0, 0};    // the one-block owner kernel last ran two workgroups per CU, [FP64, FP32]
+    int ab_shared = 0;             // the one-block FP32 owner kernel last ran two workgroups per CU
     // kernel choice: 0 automatic, 1 the general scatter-atomic kernels only (CISIGMA_OPT_SIGMA_PATH)
     int ab_mode = 0;               // CISIGMA_OPT_SIGMA_PATH
     int deterministic = 0;         // CISIGMA_OPT_DETERMINISTIC
@@ -296,10 +306,15 @@ hipError_t build_diag_tables(cisigma_ctx *ctx);
 int sigma_ab_kp(int npair);
 hipError_t launch_fill(void *x, int64_t n, int dtype, hipStream_t s);
 hipError_t launch_sigma_ab(const cisigma_ctx *ctx, const void *C, void *sigma, int dtype, hipStream_t s);
-// owner-computes sigma_3 (one-block spaces with a scatter plan): false when the
-// shape has no compiled kernel (nothing launched), else *err is the launch status
-bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *C, void *sigma, int dtype, hipStream_t s,
-                           hipError_t *err);
+// owner-computes sigma_3 in FP64 (one-block spaces with a scatter plan): false when
+// the shape has no compiled kernel (nothing launched), else *err is the launch status
+bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *C, void *sigma, hipStream_t s, hipError_t *err);
+// the FP32 form (split products): false when the space has no program (nothing launched)
+bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *C, void *sigma, hipStream_t s, hipError_t *err);
+// whether it is compiled for rb 16-row blocks of pairs and a scatter program
+bool sigma_ab_split_prog(int rb, int prog);
+// shape[4] of the owner-computes kernel for anexc excitations, npair pairs and a plan of ew entries per lane
+void sigma_ab_owner_shape(int anexc, int npair, int ew, int *shape);
 // plan width (entries per lane and tile) the owner-computes kernel uses for a
 // shape that needs `need`; 0 when no compiled kernel covers it
 int sigma_ab_owner_width(int anexc, int npair, int need);

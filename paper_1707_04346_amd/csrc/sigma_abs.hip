@@ -1,0 +1,367 @@
+// sigma_abs.hip -- the alpha-beta part sigma_3 (Eq. 8) of one-block (CAS) spaces
+// of up to 16 orbitals in FP32: owner-computes rows as in sigma_abx.hip, with the
+// contraction on the bf16 matrix cores (split.h) and the beta-side scatter as a
+// program of rounds (scatter_prog.h).
+//
+//   W(kl, Jb) = sum_a A(kl, a) C(Ja_a, Jb)                 one 32-column tile at a time
+//   sigma(Ia, Ib) += sum_{(kl, Jb): Ib = E_kl Jb} <Ib|E_kl|Jb> W(kl, Jb)
+//
+// A workgroup of four waves owns one alpha string Ia: its sigma row and one W tile
+// in LDS.  Wave (g, cb) holds the split A of half of the 16-row kl blocks in
+// registers and multiplies the tile's column half cb; all four then scatter a
+// quarter of the tile's groups each.  Between two barriers a wave computes the
+// next tile's W in registers and scatters this tile's; two workgroups share a
+// compute unit (72 KB of LDS, at most 256 registers), so one's matrix
+// instructions run while the other scatters.
+//
+// What bounds it (CAS(16,16), 18.5 ms; the FP32 instructions took 31.9): 54 matrix
+// instructions of 16 cycles and ~170 vector instructions per wave and tile.  Beside
+// a matrix instruction about three vector ones issue free of charge, so the products
+// with the splitting of their operands alone take 14 ms; the scatter, alone 11 ms
+// (a third of it bank conflicts), hides behind the other workgroup's products only
+// in part.  Four waves that multiply and four that scatter in one workgroup, with
+// two W tiles, measured 22 ms: one wave per SIMD does not hide its own latencies.
+#include "internal.h"
+#include "bufio.h"
+#include "scatter_prog.h"
+#include "split.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace cis {
+namespace {
+
+constexpr int kNT = 32;      // tile columns
+constexpr int kWS = 36;      // W row stride: 16-byte rows, a lane's four columns in one store
+
+struct AbsArgs {
+    const float *cp;         // C, alpha-major padded (row stride ld); row Na is zero
+    float *sp;               // sigma accumulator, same layout (read, then overwritten)
+    const uint32_t *aexc;    // [Na][anexc]
+    const uint32_t *astr;    // [Na]
+    const float *gp;         // [n*n][kp]
+    const uint32_t *plan;    // [ntile][4 waves][words][64 lanes]
+    uint32_t cp_bytes, plan_bytes;   // < 2^31
+    int anexc, n, kp, npair, Na, ld;
+};
+
+// A workgroup barrier with the wave's LDS accesses complete.  The explicit wait is
+// needed: at a barrier that a loop's back edge reaches, the compiler (ROCm 7.2)
+// dropped the one that __syncthreads implies.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
+// LDS by byte offset: the kernel has dynamic LDS only, which starts at 0, so that
+// the constant part of an address is the instruction's immediate offset
+typedef __attribute__((address_space(3))) float lds_float;
+__device__ __forceinline__ float lds_ld(uint32_t off) { return *reinterpret_cast<const lds_float *>(off); }
+__device__ __forceinline__ void lds_st(uint32_t off, float v) { *reinterpret_cast<lds_float *>(off) = v; }
+
+// Reference field I of a lane's plan words: the W (or scratch) element of the
+// buffer at byte offset WB, signed
+template <int I, uint32_t WB, int NW>
+__device__ __forceinline__ float prog_ref(const uint32_t (&w)[NW]) {
+    const uint32_t x = w[I / 2];
+    const float v = lds_ld((I & 1 ? (x >> 16) & 0x7fffu : x & 0x7fffu) + WB);
+    const uint32_t s = I & 1 ? x : x << 16;
+    return __uint_as_float(__float_as_uint(v) ^ (s & 0x80000000u));
+}
+template <int I, int NW>
+__device__ __forceinline__ uint32_t prog_slot(const uint32_t (&w)[NW]) {
+    return I & 1 ? w[I / 2] >> 16 : w[I / 2] & 0xffffu;
+}
+template <int I, int N, uint32_t WB, int NW>
+__device__ __forceinline__ float prog_sum(const uint32_t (&w)[NW]) {
+    if constexpr (N == 1) return prog_ref<I, WB>(w);
+    else return prog_sum<I, N / 2, WB>(w) + prog_sum<I + N / 2, N - N / 2, WB>(w);
+}
+template <int PG>
+constexpr int prog_round_field(int r) {
+    int x = kProgs[PG].np * kProgs[PG].ps;
+    for (int i = 0; i < r; ++i) x += 1 + kProgs[PG].r[i];
+    return x;
+}
+// the sums of rounds R, R + 1, ... of a tile and the slots they go to
+template <int PG, int R, uint32_t WB, int NW>
+__device__ __forceinline__ void prog_rounds(const uint32_t (&w)[NW], float (&sum)[6], uint32_t (&slot)[6]) {
+    if constexpr (R < kProgs[PG].nr) {
+        constexpr int F = prog_round_field<PG>(R);
+        slot[R] = prog_slot<F>(w);
+        sum[R] = prog_sum<F + 1, kProgs[PG].r[R], WB>(w);
+        prog_rounds<PG, R + 1, WB>(w, sum, slot);
+    }
+}
+
+// sum_{j in Ia} (jj|kl) for the kl pair of row m
+__device__ __forceinline__ float self_coef(const AbsArgs &p, uint32_t xa, int m) {
+    float val = 0;
+    for (uint32_t b = xa; b; b &= b - 1) {
+        const int j = __ffs(b) - 1;
+        val += p.gp[int64_t(j * p.n + j) * p.kp + m];
+    }
+    return val;
+}
+
+// KS: 32-row steps over the gathered rows; NR: row blocks of this wave, from rb0;
+// SELF: Ia's own row takes a slot of the steps, else it is added in FP32 (rank 1)
+template <int KS, int NR, int RB, int PG, bool SELF>
+__device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int cb, int rb0, int wave, int lane) {
+    constexpr int NRA = NR > 0 ? NR : 1;
+    constexpr int MP = 16 * RB;
+    constexpr int NW = kProgs[PG].words();
+    const int lr = lane & 15, lk = lane >> 4;
+    const uint32_t xa = p.astr[Ia];
+    // gathered rows of this lane: k = 32 s + 8 (lane / 16) + j
+    Split8 A[NRA][KS];
+    uint32_t boff[KS][8];
+    const uint32_t col = uint32_t(cb * 16 + lr);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        float a[NRA][8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int k = 32 * s + 8 * lk + j;
+            int J = p.Na;
+            const float *g = nullptr;
+            float sg = 0;
+            if (k < p.anexc) {
+                const uint32_t e = p.aexc[int64_t(Ia) * p.anexc + k];
+                if (e != kExcNone) {
+                    J = int(e >> 11);
+                    const int i = (e >> 6) & 31, jj = (e >> 1) & 31;   // <Ia|E_ij|Ja>, Ja = Ia - i + j
+                    g = p.gp + int64_t(i * p.n + jj) * p.kp;
+                    sg = (e & 1) ? -1.0f : 1.0f;
+                }
+            } else if (SELF && k == p.anexc) {
+                J = Ia;
+            }
+            boff[s][j] = (uint32_t(J) * uint32_t(p.ld) + col) * 4u;   // < cp_bytes
+#pragma unroll
+            for (int r = 0; r < NRA; ++r) {
+                const int m = (rb0 + r) * 16 + lr;
+                float val = 0;
+                if (r < NR && m < p.npair) {
+                    if (g) val = sg * g[m];
+                    else if (SELF && k == p.anexc) val = self_coef(p, xa, m);
+                }
+                a[r][j] = val;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < NRA; ++r) A[r][s] = split_round(a[r]);
+    }
+    float dI[NRA];
+    uint32_t boffI = 0;
+    if constexpr (!SELF) {
+#pragma unroll
+        for (int r = 0; r < NRA; ++r) {
+            const int m = (rb0 + r) * 16 + lr;
+            dI[r] = r < NR && m < p.npair ? self_coef(p, xa, m) : 0.0f;
+        }
+        boffI = (uint32_t(Ia) * uint32_t(p.ld) + uint32_t(cb * 16 + 4 * lk)) * 4u;
+    }
+    const __amdgpu_buffer_rsrc_t cr = buffer_of(p.cp, p.cp_bytes);
+    const __amdgpu_buffer_rsrc_t pr = buffer_of(p.plan, p.plan_bytes);
+    const int ntile = p.ld / kNT;
+    float b[KS][8];
+    bf_floatx4 cI{}, cN{};
+    floatx4 acc[NRA];
+    auto load_step = [&](int s, uint32_t so) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) buffer_ld(b[s][j], cr, boff[s][j], so);
+    };
+    auto load_self = [&](uint32_t so) {
+        if constexpr (!SELF) {
+            cI = cN;
+            buffer_ld(cN, cr, boffI, so);
+        }
+    };
+    // W of the rows held in b, then the rows of tile `next` into b.  D[Jb][kl]:
+    // a lane ends with four columns Jb of one kl row.
+    auto products = [&](int next) {
+        bf16x8 h[KS];
+        Split8 c[KS];
+        const uint32_t so = uint32_t(next) * (kNT * 4u);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            c[s] = split_trunc(b[s]);
+            load_step(s, so);
+        }
+        load_self(so);
+#pragma unroll
+        for (int r = 0; r < NRA; ++r) acc[r] = floatx4{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            h[s] = c[s].h;
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[r] = mfma_bf16(c[s].l, A[r][s].h, acc[r]);
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[r] = mfma_bf16(c[s].h, A[r][s].l, acc[r]);
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[r] = mfma_bf16(c[s].m, A[r][s].m, acc[r]);
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[r] = mfma_bf16(c[s].h, A[r][s].m, acc[r]);
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[r] = mfma_bf16(c[s].m, A[r][s].h, acc[r]);
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[r] = mfma_bf16(h[s], A[r][s].h, acc[r]);
+    };
+    auto store_w = [&]() {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            floatx4 v = acc[r];
+            if constexpr (!SELF)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = __builtin_fmaf(dI[r], cI[i], v[i]);
+            *reinterpret_cast<floatx4 *>(W + ((rb0 + r) * 16 + lr) * kWS + cb * 16 + 4 * lk) = v;
+        }
+    };
+    uint32_t pw[NW];
+    const uint32_t pl = uint32_t(wave * NW * 64 + lane) * 4u;
+    auto plan_load = [&](int tile) {
+        const uint32_t so = uint32_t(tile) * uint32_t(kProgWaves * NW * 64 * 4);
+#pragma unroll
+        for (int q = 0; q < NW; ++q) pw[q] = buffer_ld_u32(pr, pl + q * 256u, so);
+    };
+    // byte offsets in LDS: the waves' scratch elements, the sigma row
+    constexpr uint32_t SC = MP * kWS * 4u, SIG = SC + kProgWaves * 64 * 4u;
+    constexpr int NRD = kProgs[PG].nr;
+    static_assert(kProgs[PG].np == 1, "one partial round");
+    const uint32_t mine = uint32_t(wave * 64 + lane) * 4u;
+    // this wave's quarter of a tile's groups
+    auto scatter = [&]() {
+        lds_st(mine + SC, prog_sum<0, kProgs[PG].ps, 0u>(pw));
+        float sum[6], old[6];
+        uint32_t slot[6];
+        prog_rounds<PG, 0, 0u>(pw, sum, slot);
+#pragma unroll
+        for (int i = 0; i < NRD; ++i) old[i] = lds_ld(slot[i] + SIG);
+#pragma unroll
+        for (int i = 0; i < NRD; ++i) lds_st(slot[i] + SIG, old[i] + sum[i]);
+    };
+#pragma unroll
+    for (int s = 0; s < KS; ++s) load_step(s, 0u);
+    if constexpr (!SELF) buffer_ld(cN, cr, boffI, 0u);
+    plan_load(0);
+    products(ntile > 1 ? 1 : 0);
+    lds_barrier();                       // the sigma row and the zeros of W's pad columns are in LDS
+    store_w();
+    lds_barrier();                       // W of tile 0 ready
+    for (int tile = 0; tile + 1 < ntile; ++tile) {
+        products(tile + 2 < ntile ? tile + 2 : ntile - 1);
+        __builtin_amdgcn_sched_barrier(0);   // (mixed into the products the scatter is slower: 19.1 against 18.4 ms)
+        scatter();
+        plan_load(tile + 1);
+        lds_barrier();                   // W of this tile consumed
+        store_w();
+        lds_barrier();                   // W of the next tile ready
+    }
+    scatter();
+}
+
+template <int KS, int RB, int PG, bool SELF>
+__global__ __launch_bounds__(256, 2) void k_sigma_ab_s(AbsArgs p) {
+    constexpr int MP = 16 * RB;
+    constexpr int R0 = (RB + 1) / 2, R1 = RB - R0;         // row blocks of the two wave pairs
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    float *W = reinterpret_cast<float *>(smem_raw);        // [MP][kWS], then the waves' scratch
+    float *sig = W + MP * kWS + kProgWaves * 64;           // [ld + 64]: slots ld.. take discarded writes
+    const int Ia = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float *row = p.sp + int64_t(Ia) * p.ld;
+    for (int c = tid * 4; c < p.ld; c += 1024)
+        *reinterpret_cast<floatx4 *>(sig + c) = *reinterpret_cast<const floatx4 *>(row + c);
+    for (int r = tid; r < MP; r += 256) W[r * kWS + kNT] = 0.0f;   // pad column: unused references read it
+    if (wave < 2) abs_body<KS, R0, RB, PG, SELF>(p, W, Ia, wave & 1, 0, wave, lane);
+    else abs_body<KS, R1, RB, PG, SELF>(p, W, Ia, wave & 1, R0, wave, lane);
+    __syncthreads();
+    for (int c = tid * 4; c < p.ld; c += 1024)
+        *reinterpret_cast<floatx4 *>(row + c) = *reinterpret_cast<const floatx4 *>(sig + c);
+}
+
+size_t abs_lds(int ld, int rb) { return (size_t(16) * rb * kWS + kProgWaves * 64 + ld + 64) * sizeof(float); }
+
+// alone: pad the LDS so that a compute unit holds one workgroup
+template <int KS, int RB, int PG, bool SELF>
+hipError_t run_abs(const AbsArgs &a, hipStream_t s, bool alone) {
+    size_t lds = abs_lds(a.ld, RB);
+    if (alone) lds = std::max<size_t>(lds, 81 * 1024);
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sigma_ab_s<KS, RB, PG, SELF>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_sigma_ab_s<KS, RB, PG, SELF>), dim3(a.Na), dim3(256), lds, s, a);
+    return hipGetLastError();
+}
+
+// Compiled (KS, RB, program): a space of n orbitals has RB = ceil(n(n+1)/32) and
+// KS = 1 while its alpha excitations and own row fit 32 rows (always up to 10
+// orbitals), else 2.  Two programs per size: the one CAS(n, n/2) needs and the one
+// every filling fits.
+#define CIS_ABS_SHAPES(X) \
+    X(1, 1, 0) X(1, 2, 0) X(1, 3, 0) X(1, 3, 1) X(1, 4, 0) X(1, 4, 1) \
+    X(1, 5, 1) X(1, 5, 4) X(2, 5, 1) X(2, 5, 4) X(1, 6, 2) X(1, 6, 4) X(2, 6, 2) X(2, 6, 4) \
+    X(1, 7, 2) X(1, 7, 4) X(2, 7, 2) X(2, 7, 4) X(1, 8, 3) X(1, 8, 4) X(2, 8, 3) X(2, 8, 4) \
+    X(1, 9, 3) X(1, 9, 4) X(2, 9, 3) X(2, 9, 4)
+
+}  // namespace
+
+bool sigma_ab_split_prog(int rb, int prog) {
+#define CIS_HAS(K, R, P) if (rb == R && prog == P) return true;
+    CIS_ABS_SHAPES(CIS_HAS)
+#undef CIS_HAS
+    return false;
+}
+
+bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipError_t *err) {
+    const ProgPlan &P = ctx->prog;
+    if (!P.d_words) return false;
+    const auto &A = ctx->sp[0];
+    AbsArgs x{};
+    x.cp = static_cast<const float *>(cp);
+    x.sp = static_cast<float *>(sp);
+    x.aexc = A.d_exc;
+    x.astr = A.d_str;
+    x.gp = ctx->d_gp32;
+    x.plan = P.d_words;
+    x.anexc = A.nexc;
+    x.n = ctx->n;
+    x.kp = ctx->kp;
+    x.npair = ctx->npair;
+    x.Na = A.nstr;
+    x.ld = ctx->pl[0].ld[0];
+    const int rb = (x.npair + 15) / 16;
+    if (abs_lds(x.ld, rb) > 160 * 1024) return false;
+    // 32-bit byte offsets of the gathered rows (the zero row Na included) and of the plan
+    const uint64_t cpb = (uint64_t(x.Na) + 1) * uint64_t(x.ld) * sizeof(float);
+    const uint64_t plb = uint64_t(P.ntile) * kProgWaves * kProgs[P.prog].words() * 64 * sizeof(uint32_t);
+    if (cpb >= (uint64_t(1) << 31) || plb >= (uint64_t(1) << 31)) return false;
+    x.cp_bytes = uint32_t(cpb);
+    x.plan_bytes = uint32_t(plb);
+    const bool alone = ctx->ab_mode == 3;
+    const int ks = (x.anexc + 1 + 31) / 32;
+    auto *c = const_cast<cisigma_ctx *>(ctx);
+    bool ran = false;
+    // 64 excitations (8 of 16 orbitals) fill two steps: the own row as a rank-1 term
+    if (x.anexc == 64 && rb == 9) {
+        if (P.prog == 3) { *err = run_abs<2, 9, 3, false>(x, s, alone); ran = true; }
+        if (P.prog == 4) { *err = run_abs<2, 9, 4, false>(x, s, alone); ran = true; }
+    }
+#define CIS_RUN(K, R, G) \
+    if (!ran && ks == K && rb == R && P.prog == G) { *err = run_abs<K, R, G, true>(x, s, alone); ran = true; }
+    CIS_ABS_SHAPES(CIS_RUN)
+#undef CIS_RUN
+    if (!ran) return false;
+    c->ab_shared = !alone && abs_lds(x.ld, rb) <= 80 * 1024;
+    for (int i = 0; i < 4; ++i) c->last_shape[1][i] = P.shape[i];
+    return true;
+}
+
+}  // namespace cis

@@ -1,5 +1,5 @@
 // sigma_abx.hip -- owner-computes form of the alpha-beta part sigma_3 (Eq. 8)
-// for one-block (CAS) spaces of up to 16 orbitals.
+// for one-block (CAS) spaces of up to 16 orbitals, in FP64 (FP32: sigma_abs.hip).
 //
 // One workgroup per output alpha string Ia keeps the whole sigma row of Ia in
 // LDS and visits the beta strings in 32-column tiles:
@@ -24,7 +24,6 @@
 #include "abx.h"
 
 #include <algorithm>
-#include <type_traits>
 
 namespace cis {
 namespace {
@@ -171,15 +170,18 @@ __device__ __forceinline__ void abx_store_w(T *W, const typename Mfma<T>::acc_t 
                 W[((rb0 + r) * 16 + M::out_row(lane, i)) * kAbxWS + cb * 16 + (lane & 15)] = acc[r][i];
 }
 
-// ---- eight-wave form with one W buffer (FP64; FP32 where two fit per CU) ---------
+// ---- eight-wave form -------------------------------------------------------------
 //
-// The roles are split by SIMD as in the two-buffer form below (waves 3 and 7
-// scatter, the other six multiply), but with one W tile: the producing waves
-// compute the next tile's W in registers while the scatter waves consume this
-// tile's, and store it between two barriers.  The FP64 sigma row leaves room for
-// no second tile; in FP32 the smaller LDS lets two workgroups share a compute
-// unit (CAS(16,16): 71 KB each, 118 registers), so one workgroup's matrix waves
-// issue while the other's wait at a barrier.
+// On gfx950 an FP64 MFMA keeps its SIMD from issuing vector instructions of
+// other waves, so a scatter wave that shares a SIMD with a producing wave waits
+// out every matrix instruction.  The roles are therefore split by SIMD: the
+// eight waves of a workgroup are placed on the four SIMDs in turn (wave w on
+// SIMD w mod 4), waves 3 and 7 scatter (the four plan ranges of a tile, two
+// each) and share one SIMD, and the other six multiply -- three 16-row-block
+// groups x two 16-column halves -- on the other three SIMDs.  The sigma row
+// leaves room for one W tile: the producing waves compute the next tile's W in
+// registers while the scatter waves consume this tile's, and store it between
+// two barriers.
 template <typename T, int KS, int RB, int EW, bool SELF>
 __global__ __launch_bounds__(512, 1) void k_sigma_ab_x(AbxArgs<T> p) {
     using acc_t = typename Mfma<T>::acc_t;
@@ -262,135 +264,20 @@ __global__ __launch_bounds__(512, 1) void k_sigma_ab_x(AbxArgs<T> p) {
         *reinterpret_cast<vec_t *>(p.sp + rowoff + cc) = *reinterpret_cast<const vec_t *>(sig + cc);
 }
 
-// ---- eight-wave form (FP32): six producing and two scattering waves ----------
-//
-// On gfx950 an FP32 MFMA keeps its SIMD from issuing vector instructions of
-// other waves, so a scatter wave that shares a SIMD with a producing wave waits
-// out every matrix instruction.  The roles are therefore split by SIMD: the
-// eight waves of a workgroup are placed on the four SIMDs in turn (wave w on
-// SIMD w mod 4), waves 3 and 7 scatter (the four plan ranges of a tile, two
-// each) and share one SIMD, and the other six multiply -- three 16-row-block
-// groups x two 16-column halves -- on the other three SIMDs.  Waves 0-2 and
-// 4-6 compute W of tile t+1 into one of two W buffers while waves 3 and 7
-// scatter tile t from the other; one barrier per tile.  LDS: two W tiles and
-// the sigma row (~88 KB for CAS(16,16)).
-template <typename T, int KS, int RB, int EW, bool SELF>
-__global__ __launch_bounds__(512, 1) void k_sigma_ab_ws(AbxArgs<T> p) {
-    using acc_t = typename Mfma<T>::acc_t;
-    using vec_t = typename Mfma<T>::vec_t;
-    constexpr int VEC = 16 / sizeof(T);
-    constexpr int RBW = (RB + 2) / 3;
-    constexpr int MP = 16 * RB;
-    constexpr int PW = (EW + 1) * 64;                      // plan words per range and tile
-    constexpr int PT = 4 * PW;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    T *W0 = reinterpret_cast<T *>(smem_raw);               // [2][MP][WS]
-    T *W1 = W0 + MP * kAbxWS;
-    T *sig = W1 + MP * kAbxWS;                             // [ld + 64]: slots ld.. take discarded writes
-
-    const int Ia = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: the roles branch per wave
-    const int64_t rowoff = int64_t(Ia) * p.ld;
-    for (int c = tid * VEC; c < p.ld; c += 512 * VEC)
-        *reinterpret_cast<vec_t *>(sig + c) = *reinterpret_cast<const vec_t *>(p.sp + rowoff + c);
-    for (int r = tid; r < 2 * MP; r += 512) W0[r * kAbxWS + kAbxNT] = T(0);   // pad column: plan padding reads it
-    const int ntile = p.ld / kAbxNT;
-    __syncthreads();                           // the sigma row is in LDS
-    if ((wave & 3) != 3) {
-        const int m = (wave >> 2) * 3 + (wave & 3);        // 0..5
-        const int cb = m & 1, rb0 = (m >> 1) * RBW;
-        const int nrb = RB - rb0 < RBW ? RB - rb0 : RBW;   // may be <= 0 for small RB
-        T A[RBW][KS];
-        uint32_t boff[KS];
-        abx_fragments<T, KS, RBW, SELF>(p, Ia, lane, cb, rb0, nrb, A, boff);
-        T dI[RBW][4] = {};
-        uint32_t boffI = 0;
-        if constexpr (!SELF) abx_self_fragments<T, RBW>(p, Ia, lane, cb, rb0, nrb, dI, boffI);
-        const __amdgpu_buffer_rsrc_t cr = buffer_of(p.cp, p.cp_bytes);
-        T b[KS];
-        T cI = 0;
-        acc_t acc[RBW];
-        abx_load<T, KS>(cr, boff, 0, b);
-        if constexpr (!SELF) buffer_ld(cI, cr, boffI, 0u);
-        abx_products<T, KS, RBW, SELF>(cr, A, boff, ntile > 1 ? 1 : 0, b, acc, dI, boffI, cI);
-        abx_store_w<T, RBW>(W0, acc, lane, cb, rb0, nrb);
-        __syncthreads();                       // W of tile 0 ready
-        for (int tile = 0; tile < ntile; ++tile) {
-            if (tile + 1 < ntile) {
-                const int t2 = tile + 2 < ntile ? tile + 2 : ntile - 1;
-                abx_products<T, KS, RBW, SELF>(cr, A, boff, t2, b, acc, dI, boffI, cI);
-                abx_store_w<T, RBW>((tile + 1) & 1 ? W1 : W0, acc, lane, cb, rb0, nrb);
-            }
-            __syncthreads();
-        }
-    } else {
-        const __amdgpu_buffer_rsrc_t pr = buffer_of(p.plan, p.plan_bytes);
-        const int sw = wave >> 2;                          // plan ranges sw and sw + 2
-        const uint32_t pl0 = uint32_t(sw * PW + lane) * 4u, pl1 = uint32_t((sw + 2) * PW + lane) * 4u;
-        const uint32_t spare = uint32_t(p.ld + lane) * uint32_t(sizeof(T));
-        // two tiles per trip, plan words in alternating registers: the words of
-        // the next tile stay in flight for a whole tile, across the barrier
-        uint32_t pa0[EW], ha0, pa1[EW], ha1, pb0[EW], hb0, pb1[EW], hb1;
-        abx_plan_load<EW>(pr, pl0, 0u, pa0, ha0);
-        abx_plan_load<EW>(pr, pl1, 0u, pa1, ha1);
-        __syncthreads();                       // W of tile 0 ready
-        for (int tile = 0; tile < ntile; tile += 2) {
-            const int t1 = tile + 1 < ntile ? tile + 1 : tile, t2 = tile + 2 < ntile ? tile + 2 : t1;
-            abx_plan_load<EW>(pr, pl0, uint32_t(t1) * (PT * 4u), pb0, hb0);
-            abx_plan_load<EW>(pr, pl1, uint32_t(t1) * (PT * 4u), pb1, hb1);
-            abx_scatter<T, EW>(W0, sig, pa0, ha0, spare);
-            abx_scatter<T, EW>(W0, sig, pa1, ha1, spare);
-            __syncthreads();                   // tile consumed; the next W is ready
-            if (tile + 1 < ntile) {
-                abx_plan_load<EW>(pr, pl0, uint32_t(t2) * (PT * 4u), pa0, ha0);
-                abx_plan_load<EW>(pr, pl1, uint32_t(t2) * (PT * 4u), pa1, ha1);
-                abx_scatter<T, EW>(W1, sig, pb0, hb0, spare);
-                abx_scatter<T, EW>(W1, sig, pb1, hb1, spare);
-                __syncthreads();
-            }
-        }
-    }
-    for (int cc = tid * VEC; cc < p.ld; cc += 512 * VEC)
-        *reinterpret_cast<vec_t *>(p.sp + rowoff + cc) = *reinterpret_cast<const vec_t *>(sig + cc);
-}
-
-// LDS bytes: nw W tiles and the sigma row with its 64 discard slots
+// LDS bytes: the W tile and the sigma row with its 64 discard slots
 template <typename T>
-size_t abx_lds(int ld, int rb, int nw) {
-    return (size_t(nw) * 16 * rb * kAbxWS + ld + 64) * sizeof(T);
+size_t abx_lds(int ld, int rb) {
+    return (size_t(16) * rb * kAbxWS + ld + 64) * sizeof(T);
 }
 
-// FP32: the one-W-tile form when two of its workgroups fit on a compute unit
-// (registers and LDS, as the runtime's occupancy query reports them): while
-// one workgroup waits at a barrier the other's matrix waves issue (CAS(16,16)
-// sigma_3 34.6 -> 32.1 ms against the two-W-tile form, which fits one per CU);
-// otherwise the two-W-tile form.  FP64: one W tile (its row leaves room for no
-// more).  *shared: the one-W-tile form ran two workgroups per CU.  two_w: the
-// two-W-tile form in FP32 wherever it fits (CISIGMA_OPT_SIGMA_PATH = 3).
 template <typename T, int KS, int RB, int EW, bool SELF>
-hipError_t run_abx(const AbxArgs<T> &a, hipStream_t s, int *shared, bool two_w) {
-    *shared = 0;
-    const size_t lds1 = abx_lds<T>(a.ld, RB, 1);
-    if (lds1 > 160 * 1024 || 16 * RB < a.npair || 4 * KS < a.anexc + (SELF ? 1 : 0)) return hipErrorInvalidValue;
-    const void *kx = reinterpret_cast<const void *>(&k_sigma_ab_x<T, KS, RB, EW, SELF>);
-    hipError_t e = hipFuncSetAttribute(kx, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds1));
+hipError_t run_abx(const AbxArgs<T> &a, hipStream_t s) {
+    const size_t lds = abx_lds<T>(a.ld, RB);
+    if (lds > 160 * 1024 || 16 * RB < a.npair || 4 * KS < a.anexc + (SELF ? 1 : 0)) return hipErrorInvalidValue;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sigma_ab_x<T, KS, RB, EW, SELF>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
-    if constexpr (sizeof(T) == 4) {
-        int per_cu = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kx, 512, lds1);
-        if (e != hipSuccess) return e;
-        const size_t lds2 = abx_lds<T>(a.ld, RB, 2);
-        if ((per_cu < 2 || two_w) && lds2 <= 160 * 1024) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sigma_ab_ws<T, KS, RB, EW, SELF>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, int(lds2));
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((k_sigma_ab_ws<T, KS, RB, EW, SELF>), dim3(a.Na), dim3(512), lds2, s, a);
-            return hipGetLastError();
-        }
-        *shared = per_cu >= 2 ? 1 : 0;
-    }
-    hipLaunchKernelGGL((k_sigma_ab_x<T, KS, RB, EW, SELF>), dim3(a.Na), dim3(512), lds1, s, a);
+    hipLaunchKernelGGL((k_sigma_ab_x<T, KS, RB, EW, SELF>), dim3(a.Na), dim3(512), lds, s, a);
     return hipGetLastError();
 }
 
@@ -423,16 +310,15 @@ int width_for(int ks, int rb, int need) {
     return best;
 }
 
-// shape[4] receives {KS, RB, EW, 1: row in a k step, 2: rank-1 start}; *shared, two_w as run_abx
+// shape[4] receives {KS, RB, EW, 1: row in a k step, 2: rank-1 start}
 template <typename T>
-bool dispatch_abx(const AbxArgs<T> &a, int ew, hipStream_t s, hipError_t *err, int *shape, int *shared,
-                  bool two_w) {
+bool dispatch_abx(const AbxArgs<T> &a, int ew, hipStream_t s, hipError_t *err, int *shape) {
     const int rb = rb_of(a.npair);
     if (a.anexc > 0 && a.anexc % 4 == 0) {
         const int ks1 = a.anexc / 4;
 #define CIS_RUN1(K, R, E)                                           \
     if (ks1 == K && rb == R && ew == E) {                           \
-        *err = run_abx<T, K, R, E, false>(a, s, shared, two_w);     \
+        *err = run_abx<T, K, R, E, false>(a, s);                    \
         shape[0] = K; shape[1] = R; shape[2] = E; shape[3] = 2;     \
         return true;                                                \
     }
@@ -442,7 +328,7 @@ bool dispatch_abx(const AbxArgs<T> &a, int ew, hipStream_t s, hipError_t *err, i
     const int ks = ks_of(a.anexc);
 #define CIS_RUN(K, R, E)                                            \
     if (ks == K && rb == R && ew == E) {                            \
-        *err = run_abx<T, K, R, E, true>(a, s, shared, two_w);      \
+        *err = run_abx<T, K, R, E, true>(a, s);                     \
         shape[0] = K; shape[1] = R; shape[2] = E; shape[3] = 1;     \
         return true;                                                \
     }
@@ -451,10 +337,10 @@ bool dispatch_abx(const AbxArgs<T> &a, int ew, hipStream_t s, hipError_t *err, i
     return false;
 }
 
-template <typename T>
 bool owner_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipError_t *err) {
+    using T = double;
     const ScatterPlan &P = ctx->plan;
-    const uint32_t *plan = P.d_entries[sizeof(T) == 4 ? 1 : 0];
+    const uint32_t *plan = P.d_entries[0];
     if (!plan || P.ew == 0) return false;
     const auto &A = ctx->sp[0];
     AbxArgs<T> x{};
@@ -462,8 +348,7 @@ bool owner_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hi
     x.sp = static_cast<T *>(sp);
     x.aexc = A.d_exc;
     x.astr = A.d_str;
-    x.gp = std::is_same<T, float>::value ? reinterpret_cast<const T *>(ctx->d_gp32)
-                                         : reinterpret_cast<const T *>(ctx->d_gp64);
+    x.gp = ctx->d_gp64;
     x.plan = plan;
     x.anexc = A.nexc;
     x.n = ctx->n;
@@ -471,7 +356,7 @@ bool owner_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hi
     x.npair = ctx->npair;
     x.Na = A.nstr;
     x.ld = ctx->pl[0].ld[0];
-    if (abx_lds<T>(x.ld, rb_of(x.npair), 1) > 160 * 1024) return false;
+    if (abx_lds<T>(x.ld, rb_of(x.npair)) > 160 * 1024) return false;
     // 32-bit byte offsets of the gathered rows (the zero row Na included) and of the plan
     const uint64_t cpb = (uint64_t(x.Na) + 1) * uint64_t(x.ld) * sizeof(T);
     const uint64_t plb = uint64_t(P.ntile) * 4 * (P.ew + 1) * 64 * sizeof(uint32_t);
@@ -479,8 +364,7 @@ bool owner_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hi
     x.cp_bytes = uint32_t(cpb);
     x.plan_bytes = uint32_t(plb);
     auto *c = const_cast<cisigma_ctx *>(ctx);
-    return dispatch_abx<T>(x, P.ew, s, err, c->last_shape[sizeof(T) == 4], &c->abx_shared[sizeof(T) == 4],
-                           ctx->ab_mode == 3);
+    return dispatch_abx<T>(x, P.ew, s, err, c->last_shape[0]);
 }
 
 }  // namespace
@@ -489,9 +373,19 @@ int sigma_ab_owner_width(int anexc, int npair, int need) {
     return width_for(ks_of(anexc), rb_of(npair), need);
 }
 
-bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *cp, void *sp, int dtype, hipStream_t s,
-                           hipError_t *err) {
-    return dtype == CISIGMA_FP32 ? owner_t<float>(ctx, cp, sp, s, err) : owner_t<double>(ctx, cp, sp, s, err);
+void sigma_ab_owner_shape(int anexc, int npair, int ew, int *shape) {
+    const int rb = rb_of(npair);
+    shape[0] = ks_of(anexc);
+    shape[1] = rb;
+    shape[2] = ew;
+    shape[3] = 1;
+#define CIS_R1(K, R, E) if (anexc == 4 * K && rb == R && ew == E) { shape[0] = K; shape[3] = 2; }
+    CIS_ABX_SHAPES_R1(CIS_R1)
+#undef CIS_R1
+}
+
+bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipError_t *err) {
+    return owner_t(ctx, cp, sp, s, err);
 }
 
 }  // namespace cis
