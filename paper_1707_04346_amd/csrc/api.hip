@@ -20,6 +20,7 @@
 #include <new>
 #include <system_error>
 #include <thread>
+#include <tuple>
 
 #include "internal.h"
 #include "scatter_prog.h"
@@ -755,16 +756,36 @@ int build_gas_owner(cisigma_ctx *c, bool one_block) {
             }
         }
     } else {
+        // with spatial symmetry by the pair's irrep first: a source tile of one irrep
+        // leads into the unit's irrep through the pairs of one irrep only
+        auto irrep = [&](const std::pair<int, int> &x) { return c->sym ? c->orbsym[x.first] ^ c->orbsym[x.second] : 0; };
         std::stable_sort(pairs.begin(), pairs.end(), [&](const std::pair<int, int> &x, const std::pair<int, int> &y) {
-            return std::make_pair(space[x.first], space[x.second]) < std::make_pair(space[y.first], space[y.second]);
+            return std::make_tuple(irrep(x), space[x.first], space[x.second]) <
+                   std::make_tuple(irrep(y), space[y.first], space[y.second]);
         });
-        for (int r = 0; r < c->npair; ++r) row_of[cis::pair_ge(pairs[r].first, pairs[r].second)] = r;
         nrows = c->npair;
+        for (int r = 0; r < c->npair; ++r) row_of[cis::pair_ge(pairs[r].first, pairs[r].second)] = r;
+        // each irrep on whole 16-row blocks where the same kernel shape holds them
+        int K = 0, R = 0, K2 = 0, R2 = 0, aligned = 0;
+        std::vector<int> row2(c->npair);
+        for (int r = 0; r < c->npair; ++r) {
+            if (r > 0 && irrep(pairs[r]) != irrep(pairs[r - 1])) aligned = (aligned + 15) / 16 * 16;
+            row2[cis::pair_ge(pairs[r].first, pairs[r].second)] = aligned++;
+        }
+        const int ksn = (A.nexc + 1 + 3) / 4;
+        if (c->sym && cis::sigma_ab_gas_shape(ksn, (nrows + 15) / 16, &K, &R) &&
+            cis::sigma_ab_gas_shape(ksn, (aligned + 15) / 16, &K2, &R2) && K == K2 && R == R2) {
+            row_of = row2;
+            nrows = aligned;
+        }
     }
-    const int rb = (nrows + 15) / 16, mp = 16 * rb;
-    const int ks = (A.nexc + 1 + 3) / 4, kp = 4 * ks;
-    if (ks > 32 || rb > 32 || B.ntype > 255 || size_t(mp) * WS * 8 >= 65536) return CISIGMA_OK;
-    if (cis::sigma_ab_gas_width(ks, rb, 1) == 0) return CISIGMA_OK;
+    // the smallest compiled shape (missing rows and steps are zeros)
+    int ks = 0, rb = 0;
+    if ((A.nexc + 1 + 3) / 4 > 32 || (nrows + 15) / 16 > 32 || B.ntype > 255 ||
+        !cis::sigma_ab_gas_shape((A.nexc + 1 + 3) / 4, (nrows + 15) / 16, &ks, &rb))
+        return CISIGMA_OK;
+    const int mp = 16 * rb, kp = 4 * ks;
+    if (size_t(mp) * WS * 8 >= 65536) return CISIGMA_OK;
     // type moved by one electron from space `from` to space `to` (-1: no such type)
     auto moved = [&](const cis::SpinTables &S, int t, int from, int to) {
         if (from == to) return t;
@@ -791,7 +812,7 @@ int build_gas_owner(cisigma_ctx *c, bool one_block) {
             slot_src[size_t(ta) * kp + q] = -3;
         }
         slot[size_t(ta) * kp + A.nexc] = -2;
-        slot_src[size_t(ta) * kp + A.nexc] = ta;
+        slot_src[size_t(ta) * kp + A.nexc] = -3;   // the kernel orders the slots: any step may hold it
     }
     for (int ta = 0; ta < A.ntype && !c->sym; ++ta) {
         std::vector<int> occ_space, vir_space;   // GAS space of the i-th occupied / virtual orbital
@@ -905,8 +926,10 @@ int build_gas_owner(cisigma_ctx *c, bool one_block) {
         const size_t es = d == 0 ? 8 : 4;
         // the kernel addresses C with 32-bit element offsets (its zero row included)
         if (uint64_t(c->pl[0].size) + uint64_t(ldmax) >= (uint64_t(1) << 32)) continue;
-        // (point-group spaces: one more word per beta type, the kernel's per-type k-step masks)
-        const size_t fixed = (size_t(16) * rb * WS + 64) * es + size_t(4) * (kp + (c->sym ? 1 : 0)) * ntb;
+        // (point-group spaces: one more word per beta type, the kernel's per-type k-step masks,
+        // and two per k row, the ordered slots)
+        const size_t fixed = (size_t(16) * rb * WS + 64) * es + size_t(4) * (kp + (c->sym ? 1 : 0)) * ntb +
+                             (c->sym ? size_t(8) * kp : 0);
         if (fixed >= 160 * 1024) continue;
         int cmax = int(std::min<size_t>((160 * 1024 - fixed) / es, 65536 - 64 - 1));
         if (c->unit_cols > 0) cmax = std::min(cmax, c->unit_cols);

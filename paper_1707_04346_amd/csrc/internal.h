@@ -320,6 +320,8 @@ void sigma_ab_owner_shape(int anexc, int npair, int ew, int *shape);
 int sigma_ab_owner_width(int anexc, int npair, int need);
 // the same for the GAS owner-computes kernel with ks k steps and rb row blocks
 int sigma_ab_gas_width(int ks, int rb, int need);
+// the smallest compiled shape with at least ks k steps and rb row blocks (false: none)
+bool sigma_ab_gas_shape(int ks, int rb, int *K, int *R);
 // owner-computes sigma_3 on a GAS space: false when no compiled kernel covers it
 bool launch_sigma_ab_gas(const cisigma_ctx *ctx, const void *C, void *sigma, int dtype, hipStream_t s,
                          hipError_t *err);

@@ -108,8 +108,13 @@ __device__ __forceinline__ void abg_scatter_ch(const T *W, T *sig, const uint32_
     *d = *d + carry;
 }
 
+// Point-group items multiply few k steps and row blocks and wait for their loads
+// instead: two workgroups share a compute unit there
+template <int KS, int RB, int NW, bool RTK>
+constexpr int kAbgWaves = RTK && KS * RB <= 17 * 9 ? NW / 2 : 1;   // waves per SIMD at least
+
 template <typename T, int KS, int RB, int EW, int NW, bool RTK>
-__global__ __launch_bounds__(64 * NW, 1) void k_sigma_ab_g(AbgArgs<T> p) {
+__global__ __launch_bounds__(64 * NW, (kAbgWaves<KS, RB, NW, RTK>)) void k_sigma_ab_g(AbgArgs<T> p) {
     using M = Mfma<T>;
     using acc_t = typename M::acc_t;
     constexpr int NT = 64 * NW;                             // threads
@@ -120,7 +125,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_sigma_ab_g(AbgArgs<T> p) {
     // before; sigma_3 93.7 -> 82.9 ms).  Smaller shapes keep two row groups x two
     // column halves: the strided split leaves their row blocks uneven (CAS(16,16)
     // D2h, 9 row blocks: 84.1 -> 92.6 ms with it).
-    constexpr bool FC = sizeof(T) == 8 && (RB + 1) / 2 * KS * 2 > 320;
+    constexpr bool FC = sizeof(T) == 8 && (RB + 1) / 2 * KS * 2 > (RTK ? 120 : 320);
     constexpr int NH = FC ? 2 : 1;                          // column halves per wave
     constexpr int NG = FC ? NW : NW / 2;                    // row-block groups (x 2 / NH column halves)
     // eight waves: gathers as 32-bit byte offsets through a buffer resource (C
@@ -163,10 +168,40 @@ __global__ __launch_bounds__(64 * NW, 1) void k_sigma_ab_g(AbgArgs<T> p) {
         const T *src = p.sp + segrow[u] + int64_t(ra) * p.ld[u] - o;
         for (int x = x0 + tid; x < x1; x += NT) sig[x - ulo] = src[x];
     }
+    uint32_t *ukm = rowoff + p.ntb * KP;                  // RTK: [ntb] k-step masks,
+    int *sls = reinterpret_cast<int *>(ukm + p.ntb);      // [KP] slots, [KP] their source types
     const int *sl = p.slot + int64_t(ta) * KP;
+    // RTK (point-group spaces): the source type of an excitation depends on its
+    // orbitals' irreps, so the host lists the slots in excitation order; here they
+    // are ordered by source type (none last), so that the rows a tile of one beta
+    // type meets are neighbours and fill few k steps (CAS(16,16) D2h: 3 of 17
+    // instead of about 7)
+    if constexpr (RTK) {
+        int *key = sls + KP;
+        for (int q = tid; q < KP; q += NT) {
+            const int e = sl[q];
+            int k = 1 << 30;
+            if (e == -2) {
+                k = ta;
+            } else if (e >= 0) {
+                const uint32_t w = p.aexc[int64_t(Ia) * p.anexc + e];
+                if (w != kExcNone) k = p.atype[w >> 11];
+            }
+            key[q] = k;
+        }
+        __syncthreads();
+        for (int q = tid; q < KP; q += NT) {
+            const int k = key[q];
+            int pos = 0;
+            for (int j = 0; j < KP; ++j) pos += key[j] < k || (key[j] == k && j < q) ? 1 : 0;
+            sls[pos] = sl[q];
+        }
+        __syncthreads();
+    }
+    auto slot = [&](int q) { return RTK ? sls[q] : sl[q]; };
     for (int idx = tid; idx < KP * p.ntb; idx += NT) {
         const int u = idx / KP, q = idx % KP;
-        const int e = sl[q];
+        const int e = slot(q);
         int Ja = -1;
         if (e == -2) {
             Ja = Ia;
@@ -182,12 +217,10 @@ __global__ __launch_bounds__(64 * NW, 1) void k_sigma_ab_g(AbgArgs<T> p) {
         }
         rowoff[idx] = off;
     }
-    // RTK (point-group spaces): the host's k-step masks are per alpha type and
-    // take every step, but a tile of beta type u only meets the slots whose
-    // source row lies in a block allowed with u (the others gather the zero
-    // row); the steps holding one, per u, narrow each item's mask (CAS(16,16)
-    // D2h sigma_3: FP64 83.9 -> 64.5 ms, FP32 40.0 -> 37.7 ms, the same sigma)
-    uint32_t *ukm = rowoff + p.ntb * KP;                  // [ntb]
+    // RTK: the host's k-step masks are per alpha type and take every step, but a
+    // tile of beta type u only meets the slots whose source row lies in a block
+    // allowed with u (the others gather the zero row); the steps holding one, per
+    // u, narrow each item's mask
     if constexpr (RTK) {
         __syncthreads();                                  // rowoff complete
         for (int u = tid; u < p.ntb; u += NT) {
@@ -202,7 +235,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_sigma_ab_g(AbgArgs<T> p) {
     const uint32_t xa = p.astr[Ia];
 #pragma unroll
     for (int t = 0; t < KS; ++t) {
-        const int e = sl[4 * t + (lane >> 4)];
+        const int e = slot(4 * t + (lane >> 4));
         const T *g = nullptr;
         T sg = 0;
         if (e >= 0) {
@@ -553,7 +586,8 @@ __global__ __launch_bounds__(512, 1) void k_sigma_ab_gw(AbgArgs<T> p) {
 
 template <typename T>
 size_t abg_lds(int nvirt, int rb, int ks, int ntb, int rtk) {
-    return (size_t(16) * rb * kAbxWS + nvirt + 64) * sizeof(T) + (size_t(4) * ks + rtk) * ntb * sizeof(uint32_t);
+    return (size_t(16) * rb * kAbxWS + nvirt + 64) * sizeof(T) + (size_t(4) * ks + rtk) * ntb * sizeof(uint32_t) +
+           size_t(rtk) * 8 * ks * sizeof(uint32_t);
 }
 
 // Waves per workgroup of the GAS kernel: FP32 with C below 4 GB eight (two per
@@ -578,11 +612,11 @@ hipError_t run_abg_rtk(const AbgArgs<T> &a, int na, hipStream_t s) {
     return run_abg_nw<T, KS, RB, EW, 4, RTK>(a, na, s);
 }
 
-// the per-beta-type k-step masks are compiled for the shapes of point-group
-// spaces up to CAS(16,16) (17 k steps x 9 row blocks); larger shapes run without
+// the ordered slots and per-beta-type k-step masks are compiled for the shapes of
+// point-group spaces up to CAS(18,18) (21 k steps x 11 row blocks)
 template <typename T, int KS, int RB, int EW>
 hipError_t run_abg(const AbgArgs<T> &a, int na, hipStream_t s) {
-    if constexpr (KS * RB <= 17 * 9)
+    if constexpr (KS * RB <= 21 * 11)
         if (a.rtk) return run_abg_rtk<T, KS, RB, EW, true>(a, na, s);
     return run_abg_rtk<T, KS, RB, EW, false>(a, na, s);
 }
@@ -605,11 +639,12 @@ hipError_t run_abgw(const AbgArgs<T> &a, int na, hipStream_t s) {
 // compiled (KS, RB, EW) shapes of the GAS kernel: small test spaces (GAS, one-block
 // CAS(8,8) and CAS(10,10) split into units, CAS(8,8) with point-group symmetry),
 // GAS(20,20) 6/8/6, CAS(18,18) (whose sigma row is too long for the one-block
-// kernel) and CAS(16,16) with point-group symmetry
+// kernel), and 12, 14 and 16 orbitals.  A space takes the smallest shape that
+// holds it (gas_shape_for): missing k steps and W rows are zeros and never active
 #define CIS_ABG_SHAPES(X) \
     X(3, 2, 4) X(3, 2, 16) X(4, 2, 4) X(4, 2, 16) X(4, 3, 4) X(4, 3, 16) X(5, 3, 4) X(5, 3, 16) X(5, 4, 4) \
-    X(5, 4, 16) X(7, 5, 4) X(7, 5, 16) X(26, 14, 16) X(21, 11, 8) X(21, 11, 12) X(21, 11, 16) X(17, 9, 4) \
-    X(17, 9, 8) X(17, 9, 16)
+    X(5, 4, 16) X(7, 5, 4) X(7, 5, 16) X(10, 5, 4) X(10, 5, 16) X(13, 7, 4) X(13, 7, 16) X(26, 14, 16) \
+    X(21, 11, 8) X(21, 11, 12) X(21, 11, 16) X(17, 9, 4) X(17, 9, 8) X(17, 9, 16)
 
 int gas_width_for(int ks, int rb, int need) {
     int best = 0;
@@ -706,6 +741,15 @@ bool gas_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipE
 }  // namespace
 
 int sigma_ab_gas_width(int ks, int rb, int need) { return gas_width_for(ks, rb, need); }
+
+bool sigma_ab_gas_shape(int ks, int rb, int *K, int *R) {
+    *K = *R = 0;
+#define CIS_S(KK, RR, E) \
+    if (KK >= ks && RR >= rb && (*K == 0 || KK * RR < *K * *R)) { *K = KK; *R = RR; }
+    CIS_ABG_SHAPES(CIS_S)
+#undef CIS_S
+    return *K != 0;
+}
 
 bool launch_sigma_ab_gas(const cisigma_ctx *ctx, const void *cp, void *sp, int dtype, hipStream_t s,
                          hipError_t *err) {
