@@ -437,8 +437,8 @@ int cisigma_last_path(const cisigma_ctx *ctx, int dtype, int *flags);
  *   shape[0]  k steps of gathered alpha rows (4 rows each; the FP32 one-block
  *             kernel multiplies 32 rows at a time and reports the same count)
  *   shape[1]  16-row blocks of orbital pairs
- *   shape[2]  scatter-plan entries per lane and tile (FP32 one-block kernel: those
- *             a plan of equal runs per lane would take)
+ *   shape[2]  scatter-plan entries per lane and tile (one-block kernels: those a
+ *             plan of equal runs per lane would take)
  *   shape[3]  0: no owner-computes kernel ran (general kernel); 1: one-block
  *             kernel with the own row in a k step; 2: one-block kernel with the
  *             own row as the rank-1 start of the accumulators; 3: units of

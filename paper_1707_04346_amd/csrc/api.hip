@@ -144,7 +144,6 @@ void free_ctx(cisigma_ctx *c) {
     (void)hipFree(c->d_jpq);
     (void)hipFree(c->bt.blk); (void)hipFree(c->bt.tb); (void)hipFree(c->bt.tr); (void)hipFree(c->bt.tc);
     (void)hipFree(c->d_pblk); (void)hipFree(c->d_blkoff);
-    (void)hipFree(c->plan.d_entries[0]); (void)hipFree(c->plan.d_entries[1]);
     (void)hipFree(c->prog.d_words);
     (void)hipFree(c->d_act_start); (void)hipFree(c->d_act_tiles);
     (void)hipFree(c->go.d_slot); (void)hipFree(c->go.d_coff); (void)hipFree(c->go.d_g32); (void)hipFree(c->go.d_g64);
@@ -596,34 +595,28 @@ int plan_tables(cisigma_ctx *c, std::vector<uint32_t> &exc, std::vector<uint32_t
     return CISIGMA_OK;
 }
 
-// Builds the FP64 encoding of a scatter plan into P (P.ew = 0: no plan).
-int make_scatter_plan(cisigma_ctx *c, const PlanSpec &ps, const PlanTiles &pt, cis::ScatterPlan &P) {
-    int ew = 0;
+// Entries per lane of a plan in equal runs, as cisigma_last_shape reports them (16
+// where no such plan holds the space).
+int plan_width(const PlanSpec &ps, const PlanTiles &pt) {
     for (int cand : {ps.width(pt.need), 16})
-        if (cand >= pt.need && ps.width(cand) == cand && plan_fits(pt, cand)) { ew = cand; break; }
-    if (ew == 0) return CISIGMA_OK;
-    std::vector<uint32_t> plan[2];
-    plan_emit(ps, pt, ew, plan);
-    HIP_OR_FAIL(c, upload(&P.d_entries[0], plan[0]), "init: scatter plan");
-    P.ntile = ps.ntile;
-    P.ew = ew;
-    return CISIGMA_OK;
+        if (cand >= pt.need && ps.width(cand) == cand && plan_fits(pt, cand)) return cand;
+    return 16;
 }
 
 // The first compiled program that every tile of the space fits.
-int build_scatter_prog(cisigma_ctx *c, const PlanTiles &pt) {
-    constexpr int WS = 33, WS32 = 36;   // W row strides of the items and of the FP32 kernel
+int build_scatter_prog(cisigma_ctx *c, const PlanSpec &ps, const PlanTiles &pt) {
+    constexpr int WS = 33, WSP = 36;   // W row strides of the items and of the kernels
     const int rb = (c->npair + 15) / 16;
     cis::ProgLayout L{};
     L.zero = 32;
-    L.scratch = uint32_t(16 * rb * WS32);
+    L.scratch = uint32_t(16 * rb * WSP);
     L.spare = uint32_t(c->pl[0].ld[0]);
     L.bytes = 4;
     L.unit = L.sunit = 1;
     std::vector<std::vector<cis::ProgItem>> tiles(pt.tiles.size());
     for (size_t t = 0; t < tiles.size(); ++t)
         for (const PlanItem &it : pt.tiles[t])
-            tiles[t].push_back({it.tgt, it.widx / WS * WS32 + it.widx % WS, it.neg});
+            tiles[t].push_back({it.tgt, it.widx / WS * WSP + it.widx % WS, it.neg});
     for (int g = 0; g < cis::kNumProgs; ++g) {
         if (!cis::sigma_ab_split_prog(rb, g)) continue;
         const size_t per = size_t(cis::kProgWaves) * cis::kProgs[g].words() * cis::kProgLanes;
@@ -638,28 +631,23 @@ int build_scatter_prog(cisigma_ctx *c, const PlanTiles &pt) {
         HIP_OR_FAIL(c, upload(&c->prog.d_words, words), "init: scatter program");
         c->prog.ntile = int(tiles.size());
         c->prog.prog = g;
-        cis::sigma_ab_owner_shape(c->sp[0].nexc, c->npair, c->plan.ew ? c->plan.ew : 16, c->prog.shape);
+        cis::sigma_ab_owner_shape(c->sp[0].nexc, c->npair, plan_width(ps, pt), c->prog.shape);
         break;
     }
     return CISIGMA_OK;
 }
 
 int build_scatter_plan(cisigma_ctx *c) {
-    constexpr int WS = 33;
     const auto &B = c->sp[1];
     const int ld = c->pl[0].ld[0];
-    const int mp = 16 * ((c->npair + 15) / 16);
-    // 16-bit fields: W byte offsets (FP64 the larger) and slot offsets (FP32 bytes, FP64 elements)
-    if (!c->cas || c->n > 16 || B.nexc == 0 || c->na == 0 || size_t(mp) * WS * 8 >= 65536 ||
-        (size_t(ld) + 64) * 4 >= 65536)
+    // 16-bit slot fields, in bytes of FP32
+    if (!c->cas || c->n > 16 || B.nexc == 0 || c->na == 0 || (size_t(ld) + 64) * 4 >= 65536)
         return CISIGMA_OK;
     PlanSpec ps;
     ps.ntile = ld / 32;
     ps.source = [&](int t, int col) { const int Jb = t * 32 + col; return Jb < B.nstr ? Jb : -1; };
     ps.w_row = [](int k, int l) { return cis::pair_ge(k, l); };
     ps.nvirt = ld;
-    ps.unit[0] = 8;
-    ps.unit[1] = 1;
     const int anexc = c->sp[0].nexc, npair = c->npair;
     ps.width = [=](int need) { return cis::sigma_ab_owner_width(anexc, npair, need); };
     std::vector<uint32_t> exc, str;
@@ -668,9 +656,7 @@ int build_scatter_plan(cisigma_ctx *c) {
     PlanTiles pt;
     rc = plan_items(c, ps, exc, str, pt);
     if (rc) return rc;
-    rc = make_scatter_plan(c, ps, pt, c->plan);
-    if (rc) return rc;
-    return build_scatter_prog(c, pt);
+    return build_scatter_prog(c, ps, pt);
 }
 
 
@@ -703,7 +689,7 @@ int build_gas_owner(cisigma_ctx *c, bool one_block) {
     const int n = c->n, ng = c->gas.ngas;
     // one-block spaces come here only when the one-block owner kernel has no plan
     // (more than 16 orbitals, or a sigma row longer than its LDS), or on request
-    if ((c->cas && c->plan.ew > 0 && !one_block) || c->na == 0 || c->nb == 0 || A.nexc == 0 || B.nexc == 0)
+    if ((c->cas && c->prog.d_words && !one_block) || c->na == 0 || c->nb == 0 || A.nexc == 0 || B.nexc == 0)
         return CISIGMA_OK;
     std::vector<int> space(n, 0);
     for (int g = 0; g < ng; ++g)

@@ -134,20 +134,15 @@ struct BlockTilesDev {
     int ntiles;
 };
 
-// Conflict-free schedule of the beta-side scatter of the owner-computes
-// sigma_3 kernel (32-column tiles): per tile, every contribution (target beta
-// string, W row kl, column, sign) sorted by target and cut into 256
-// per-thread ranges of whole target groups, each padded to a multiple of 4
-// entries, so no two threads write the same sigma element within a tile.
-// entry = first-of-group << 29 | negative << 28 | target << 13 | (kl*33 + column)
-// no-op entry = 1 << 29 | ld << 13 | npair*33 (zero row of W, spare sigma slot).
+// The beta-side scatter of the GAS owner-computes sigma_3 kernel through a sorted
+// list (abx.h): the entry words of every unit's tiles.
 struct ScatterPlan {
     uint32_t *d_entries[2] = {nullptr, nullptr};  // [FP64, FP32] entry encodings, [ntile][4][ew][64]
     int ntile = 0;
     int ew = 0;                                    // entries per lane and tile (0: no plan)
 };
 
-// The scatter of the one-block sigma_3 kernel in FP32 as a program of rounds
+// The scatter of the one-block sigma_3 kernels as a program of rounds
 // (scatter_prog.h): every tile's words, [ntile][4 waves][words][64 lanes].
 struct ProgPlan {
     uint32_t *d_words = nullptr;   // nullptr: none
@@ -233,8 +228,7 @@ struct cisigma_ctx {
     double *d_jpq = nullptr;       // [n][n] (pp|qq)
     cis::Workspace ws[2];          // per dtype (0 FP64, 1 FP32)
     cis::BlockTilesDev bt{};       // tiles of the caller-layout blocks
-    cis::ScatterPlan plan;         // beta-side scatter plan of the owner-computes sigma_3 kernel
-    cis::ProgPlan prog;            // the same for the FP32 kernel
+    cis::ProgPlan prog;            // beta-side scatter of the one-block sigma_3 kernels
     // general sigma_3 kernel: per alpha type, the 64-column beta tiles that can
     // change sigma (CSR over alpha types; all tiles for one-block spaces)
     int *d_act_start = nullptr;    // [ntype_a + 1]

@@ -32,4 +32,11 @@ template <> struct Mfma<double> {
     static __device__ __forceinline__ int out_row(int lane, int r) { return (lane >> 4) + 4 * r; }
 };
 
+// Four 4x4x4 products at once: with b as in the 16x16x4 form (lane l: B[l / 16][l % 16])
+// and a = A[l % 4][l / 16], a four-row A on every lane group, the result is
+// D[l / 16][l % 16] of the 4x16 product, in a quarter of the 16x16x4 form's time.
+__device__ __forceinline__ double mfma_quad(double a, double b, double c) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
 }  // namespace cis

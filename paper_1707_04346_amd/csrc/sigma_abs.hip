@@ -23,7 +23,7 @@
 // two W tiles, measured 22 ms: one wave per SIMD does not hide its own latencies.
 #include "internal.h"
 #include "bufio.h"
-#include "scatter_prog.h"
+#include "scatter_prog_dev.h"
 #include "split.h"
 
 #include <algorithm>
@@ -46,55 +46,6 @@ struct AbsArgs {
     int anexc, n, kp, npair, Na, ld;
 };
 
-// A workgroup barrier with the wave's LDS accesses complete.  The explicit wait is
-// needed: at a barrier that a loop's back edge reaches, the compiler (ROCm 7.2)
-// dropped the one that __syncthreads implies.
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __syncthreads();
-}
-
-// LDS by byte offset: the kernel has dynamic LDS only, which starts at 0, so that
-// the constant part of an address is the instruction's immediate offset
-typedef __attribute__((address_space(3))) float lds_float;
-__device__ __forceinline__ float lds_ld(uint32_t off) { return *reinterpret_cast<const lds_float *>(off); }
-__device__ __forceinline__ void lds_st(uint32_t off, float v) { *reinterpret_cast<lds_float *>(off) = v; }
-
-// Reference field I of a lane's plan words: the W (or scratch) element of the
-// buffer at byte offset WB, signed
-template <int I, uint32_t WB, int NW>
-__device__ __forceinline__ float prog_ref(const uint32_t (&w)[NW]) {
-    const uint32_t x = w[I / 2];
-    const float v = lds_ld((I & 1 ? (x >> 16) & 0x7fffu : x & 0x7fffu) + WB);
-    const uint32_t s = I & 1 ? x : x << 16;
-    return __uint_as_float(__float_as_uint(v) ^ (s & 0x80000000u));
-}
-template <int I, int NW>
-__device__ __forceinline__ uint32_t prog_slot(const uint32_t (&w)[NW]) {
-    return I & 1 ? w[I / 2] >> 16 : w[I / 2] & 0xffffu;
-}
-template <int I, int N, uint32_t WB, int NW>
-__device__ __forceinline__ float prog_sum(const uint32_t (&w)[NW]) {
-    if constexpr (N == 1) return prog_ref<I, WB>(w);
-    else return prog_sum<I, N / 2, WB>(w) + prog_sum<I + N / 2, N - N / 2, WB>(w);
-}
-template <int PG>
-constexpr int prog_round_field(int r) {
-    int x = kProgs[PG].np * kProgs[PG].ps;
-    for (int i = 0; i < r; ++i) x += 1 + kProgs[PG].r[i];
-    return x;
-}
-// the sums of rounds R, R + 1, ... of a tile and the slots they go to
-template <int PG, int R, uint32_t WB, int NW>
-__device__ __forceinline__ void prog_rounds(const uint32_t (&w)[NW], float (&sum)[6], uint32_t (&slot)[6]) {
-    if constexpr (R < kProgs[PG].nr) {
-        constexpr int F = prog_round_field<PG>(R);
-        slot[R] = prog_slot<F>(w);
-        sum[R] = prog_sum<F + 1, kProgs[PG].r[R], WB>(w);
-        prog_rounds<PG, R + 1, WB>(w, sum, slot);
-    }
-}
-
 // sum_{j in Ia} (jj|kl) for the kl pair of row m
 __device__ __forceinline__ float self_coef(const AbsArgs &p, uint32_t xa, int m) {
     float val = 0;
@@ -111,7 +62,6 @@ template <int KS, int NR, int RB, int PG, bool SELF>
 __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int cb, int rb0, int wave, int lane) {
     constexpr int NRA = NR > 0 ? NR : 1;
     constexpr int MP = 16 * RB;
-    constexpr int NW = kProgs[PG].words();
     const int lr = lane & 15, lk = lane >> 4;
     const uint32_t xa = p.astr[Ia];
     // gathered rows of this lane: k = 32 s + 8 (lane / 16) + j
@@ -222,29 +172,12 @@ __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int
             *reinterpret_cast<floatx4 *>(W + ((rb0 + r) * 16 + lr) * kWS + cb * 16 + 4 * lk) = v;
         }
     };
-    uint32_t pw[NW];
-    const uint32_t pl = uint32_t(wave * NW * 64 + lane) * 4u;
-    auto plan_load = [&](int tile) {
-        const uint32_t so = uint32_t(tile) * uint32_t(kProgWaves * NW * 64 * 4);
-#pragma unroll
-        for (int q = 0; q < NW; ++q) pw[q] = buffer_ld_u32(pr, pl + q * 256u, so);
-    };
-    // byte offsets in LDS: the waves' scratch elements, the sigma row
+    // this wave's quarter of a tile's groups: the words, then their sums
+    ProgWords<float, PG> pw;
+    const uint32_t pl = uint32_t(wave * pw.NW * 64 + lane) * 4u, mine = uint32_t(wave * 64 + lane) * 4u;
     constexpr uint32_t SC = MP * kWS * 4u, SIG = SC + kProgWaves * 64 * 4u;
-    constexpr int NRD = kProgs[PG].nr;
-    static_assert(kProgs[PG].np == 1, "one partial round");
-    const uint32_t mine = uint32_t(wave * 64 + lane) * 4u;
-    // this wave's quarter of a tile's groups
-    auto scatter = [&]() {
-        lds_st(mine + SC, prog_sum<0, kProgs[PG].ps, 0u>(pw));
-        float sum[6], old[6];
-        uint32_t slot[6];
-        prog_rounds<PG, 0, 0u>(pw, sum, slot);
-#pragma unroll
-        for (int i = 0; i < NRD; ++i) old[i] = lds_ld(slot[i] + SIG);
-#pragma unroll
-        for (int i = 0; i < NRD; ++i) lds_st(slot[i] + SIG, old[i] + sum[i]);
-    };
+    auto plan_load = [&](int tile) { pw.load(pr, pl, tile); };
+    auto scatter = [&]() { prog_run<SC, SIG>(pw, mine); };
 #pragma unroll
     for (int s = 0; s < KS; ++s) load_step(s, 0u);
     if constexpr (!SELF) buffer_ld(cN, cr, boffI, 0u);

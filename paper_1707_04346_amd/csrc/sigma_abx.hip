@@ -1,5 +1,5 @@
-// sigma_abx.hip -- owner-computes form of the alpha-beta part sigma_3 (Eq. 8)
-// for one-block (CAS) spaces of up to 16 orbitals, in FP64 (FP32: sigma_abs.hip).
+// sigma_abx.hip -- the alpha-beta part sigma_3 (Eq. 8) of one-block (CAS) spaces
+// of up to 16 orbitals, in FP64: owner-computes rows (FP32: sigma_abs.hip).
 //
 // One workgroup per output alpha string Ia keeps the whole sigma row of Ia in
 // LDS and visits the beta strings in 32-column tiles:
@@ -15,45 +15,64 @@
 // (kl runs over unordered pairs k >= l: E_kl and E_lk share the integral.)
 // The gathered rows R are coalesced row reads of C; W comes from the matrix
 // cores; the beta-side scatter stays in LDS, so no global atomics are made and
-// every sigma row is written once.
+// every sigma row is written once.  The scatter is the program of rounds of
+// scatter_prog.h, the same words as in FP32 (offsets doubled).
 //
-// The beta-side scatter goes through a plan built once on the host (abx.h).
+// What bounds it: the FP64 matrix instructions.  A 16x16x4 one holds its SIMD for
+// 64 cycles and lets no vector instruction of any wave of that SIMD issue meanwhile,
+// so products and scatter add up whatever wave runs them; what can be shaped is how
+// evenly the four SIMDs are loaded.  W's rows are therefore dealt in quads of four:
+// four quads are one 16x16x4 instruction per k step, a single quad one 4x4x4
+// (four blocks, all columns of the half tile: the same operand registers of C, a
+// quarter of the time).  A pair of waves w, w + 4 shares a SIMD (wave w is placed on
+// SIMD w mod 4); every SIMD gets half the quads of one 16-column half, the first wave
+// whole 16-row blocks, the second the rest and a quarter of the tile's scatter.  At
+// CAS(16,16) that is 4.25 blocks per SIMD and k step where whole 16-row blocks on three
+// SIMDs, the fourth scattering alone, took 6: 54.8 instead of 64.1 ms; a whole
+// sigma of CAS(12,12) 285 instead of 472 us (there two workgroups share a compute
+// unit).  The products alone take 42.6 ms (their instructions 39), the stores of W 1.7; the scatter's 100
+// vector instructions a wave and tile cost ~12 cycles each, as every break in a SIMD's
+// run of matrix instructions costs it ~12 cycles.  The scattering waves' own barrier
+// ("consumed") meets the others half way through their products, so that a wave stores
+// its W as soon as it is done (with both barriers at the end 58.0 ms).
 #include "internal.h"
 #include "mfma.h"
 #include "bufio.h"
-#include "abx.h"
+#include "scatter_prog_dev.h"
 
 #include <algorithm>
 
 namespace cis {
 namespace {
 
+constexpr int kNT = 32;      // tile columns
+constexpr int kWS = 36;      // W row stride (the scatter program's)
 
-template <typename T>
 struct AbxArgs {
-    const T *cp;           // C, alpha-major padded (row stride ld)
-    T *sp;                 // sigma accumulator, same layout (read, then overwritten)
-    const uint32_t *aexc;  // [Na][anexc]
-    const uint32_t *astr;  // [Na]
-    const T *gp;           // [n*n][kp]
-    const uint32_t *plan;  // [ntile][4 waves][EW][64 lanes]
-    uint32_t cp_bytes;     // bytes of C including the zero row (< 2^31)
-    uint32_t plan_bytes;   // bytes of the plan (< 2^31)
+    const double *cp;        // C, alpha-major padded (row stride ld); row Na is zero
+    double *sp;              // sigma accumulator, same layout (read, then overwritten)
+    const uint32_t *aexc;    // [Na][anexc]
+    const uint32_t *astr;    // [Na]
+    const double *gp;        // [n*n][kp]
+    const uint32_t *plan;    // [ntile][4 waves][words][64 lanes]
+    uint32_t cp_bytes, plan_bytes;   // < 2^31
     int anexc, n, kp, npair, Na, ld;
 };
 
-
-// ---- pieces of the two kernel forms ------------------------------------------
-//
-// KS: k steps over the gathered rows (4*KS >= anexc+1); RB: 16-row blocks of kl
-// (16*RB >= npair); RBW: row blocks per producing wave; EW: plan entries per
-// lane and tile.  A producing wave owns one 16-column half of the 32-column
-// tile (cb) and a run of row blocks [rb0, rb0 + nrb).
+// Quads of wave group g (waves 2g and 2g + 1: the two column halves) of q in all.
+// Groups g and g + 2 share SIMDs: half the quads each pair, whole 16-row blocks to
+// the first (a little more than half of them: the second also scatters).
+constexpr int group_quads(int q, int g) {
+    const int s = (g & 1) ? q / 2 : (q + 1) / 2;
+    const int a = 4 * ((s + 9) / 8), b = 4 * (s / 4);
+    const int first = a < b ? a : b;
+    return g < 2 ? first : s - first;
+}
+constexpr int group_quad0(int q, int g) { return g == 0 ? 0 : group_quad0(q, g - 1) + group_quads(q, g - 1); }
 
 // A(m, Ia) = sum_{j in Ia} (jj|kl) for the kl pair of row m
-template <typename T>
-__device__ __forceinline__ T abx_self_coef(const AbxArgs<T> &p, uint32_t xa, int m) {
-    T val = 0;
+__device__ __forceinline__ double self_coef(const AbxArgs &p, uint32_t xa, int m) {
+    double val = 0;
     for (uint32_t b = xa; b; b &= b - 1) {
         const int j = __ffs(b) - 1;
         val += p.gp[int64_t(j * p.n + j) * p.kp + m];
@@ -61,316 +80,217 @@ __device__ __forceinline__ T abx_self_coef(const AbxArgs<T> &p, uint32_t xa, int
     return val;
 }
 
-// A fragments of Ia for the wave's row blocks -- row m (kl) = 16*(rb0 + r) +
-// lane%16, column k = 4t + lane/16 -- and the byte offsets of the gathered rows
-// (missing excitations read the zero row Na).  With SELF, column anexc is Ia's
-// own row.
-template <typename T, int KS, int RBW, bool SELF>
-__device__ __forceinline__ void abx_fragments(const AbxArgs<T> &p, int Ia, int lane, int cb, int rb0, int nrb,
-                                              T (&A)[RBW][KS], uint32_t (&boff)[KS]) {
+// One wave: KS k steps of four gathered rows, NQ quads of W rows from row m0 on,
+// column half cb; scatter quarter sw (< 0: none).
+template <int KS, int NQ, int RB, int PG, bool SELF, bool SCAT>
+__device__ __forceinline__ void abx_body(const AbxArgs &p, int Ia, int cb, int m0, int sw, int lane) {
+    constexpr int NB = NQ / 4, NS = NQ % 4, NF = NB + NS > 0 ? NB + NS : 1;   // whole blocks, single quads, fragments
+    constexpr uint32_t SC = 16 * RB * kWS * 8u, SIG = SC + kProgWaves * 64 * 8u;
+    const int lr = lane & 15, lk = lane >> 4;
     const uint32_t xa = p.astr[Ia];
-    const uint32_t col = uint32_t(cb * 16 + (lane & 15));
+    const uint32_t col = uint32_t(cb * 16 + lr);
+    // fragment f, lane: row m0 + 16 f + lane % 16 of a block; of a single quad row
+    // lane % 4 of it (repeated for the four column blocks); k = 4t + lane / 16
+    auto row_a = [&](int f) { return f < NB ? m0 + 16 * f + lr : m0 + 16 * NB + 4 * (f - NB) + (lane & 3); };
+    double A[NF][KS];
+    uint32_t boff[KS];
 #pragma unroll
     for (int t = 0; t < KS; ++t) {
-        const int k = 4 * t + (lane >> 4);
+        const int k = 4 * t + lk;
         int J = p.Na;
-        const T *g = nullptr;
-        T sg = 0;
+        const double *g = nullptr;
+        double sg = 0;
         if (k < p.anexc) {
             const uint32_t e = p.aexc[int64_t(Ia) * p.anexc + k];
             if (e != kExcNone) {
                 J = int(e >> 11);
                 const int i = (e >> 6) & 31, j = (e >> 1) & 31;   // <Ia|E_ij|Ja>, Ja = Ia - i + j
                 g = p.gp + int64_t(i * p.n + j) * p.kp;
-                sg = (e & 1) ? T(-1) : T(1);
+                sg = (e & 1) ? -1.0 : 1.0;
             }
         } else if (SELF && k == p.anexc) {
             J = Ia;
         }
-        boff[t] = (uint32_t(J) * uint32_t(p.ld) + col) * uint32_t(sizeof(T));   // < cp_bytes
+        boff[t] = (uint32_t(J) * uint32_t(p.ld) + col) * 8u;   // < cp_bytes
 #pragma unroll
-        for (int r = 0; r < RBW; ++r) {
-            const int m = (rb0 + r) * 16 + (lane & 15);
-            T val = 0;
-            if (r < nrb && m < p.npair) {
-                if (g) {
-                    val = sg * g[m];
-                } else if (SELF && k == p.anexc) {
-                    val = abx_self_coef(p, xa, m);
-                }
+        for (int f = 0; f < NF; ++f) {
+            const int m = row_a(f);
+            double val = 0;
+            if (f < NB + NS && m < p.npair) {
+                if (g) val = sg * g[m];
+                else if (SELF && k == p.anexc) val = self_coef(p, xa, m);
             }
-            A[r][t] = val;
+            A[f][t] = val;
         }
     }
-}
-
-// Without SELF: A(m, Ia) for the lane's accumulator rows m = 16*(rb0 + r) +
-// out_row(lane, i), and the byte offset of C(Ia, column) of the lane's column
-template <typename T, int RBW>
-__device__ __forceinline__ void abx_self_fragments(const AbxArgs<T> &p, int Ia, int lane, int cb, int rb0, int nrb,
-                                                   T (&dI)[RBW][4], uint32_t &boffI) {
-    using M = Mfma<T>;
-    const uint32_t xa = p.astr[Ia];
+    // without SELF: A(m, Ia) of the lane's accumulator rows
+    double dB[NB > 0 ? NB : 1][4] = {}, dQ[NS > 0 ? NS : 1] = {};
+    uint32_t boffI = 0;
+    if constexpr (!SELF) {
 #pragma unroll
-    for (int r = 0; r < RBW; ++r)
+        for (int f = 0; f < NB; ++f)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int m = (rb0 + r) * 16 + M::out_row(lane, i);
-            dI[r][i] = (r < nrb && m < p.npair) ? abx_self_coef(p, xa, m) : T(0);
+            for (int i = 0; i < 4; ++i) {
+                const int m = m0 + 16 * f + Mfma<double>::out_row(lane, i);
+                dB[f][i] = m < p.npair ? self_coef(p, xa, m) : 0.0;
+            }
+#pragma unroll
+        for (int f = 0; f < NS; ++f) {
+            const int m = m0 + 16 * NB + 4 * f + lk;
+            dQ[f] = m < p.npair ? self_coef(p, xa, m) : 0.0;
         }
-    boffI = (uint32_t(Ia) * uint32_t(p.ld) + uint32_t(cb * 16 + (lane & 15))) * uint32_t(sizeof(T));   // < cp_bytes
-}
-
-template <typename T, int KS>
-__device__ __forceinline__ void abx_load(__amdgpu_buffer_rsrc_t cr, const uint32_t (&boff)[KS], int tile, T (&b)[KS]) {
-    const uint32_t soff = uint32_t(tile) * uint32_t(kAbxNT * sizeof(T));
-#pragma unroll
-    for (int t = 0; t < KS; ++t) buffer_ld(b[t], cr, boff[t], soff);
-}
-
-// W = A R on the matrix cores for the rows held in b; as each k step is
-// consumed, b[t] is reloaded with the rows of tile `next` (always a valid
-// tile), so the loads stay in flight for a whole tile.  Without SELF the
-// accumulators start from A(kl, Ia) C(Ia, Jb), cI holding C(Ia, Jb) of this
-// tile (reloaded likewise).
-template <typename T, int KS, int RBW, bool SELF>
-__device__ __forceinline__ void abx_products(__amdgpu_buffer_rsrc_t cr, const T (&A)[RBW][KS],
-                                             const uint32_t (&boff)[KS], int next, T (&b)[KS],
-                                             typename Mfma<T>::acc_t (&acc)[RBW], const T (&dI)[RBW][4],
-                                             uint32_t boffI, T &cI) {
-    using M = Mfma<T>;
-    const uint32_t soff = uint32_t(next) * uint32_t(kAbxNT * sizeof(T));
-    if constexpr (SELF) {
-#pragma unroll
-        for (int r = 0; r < RBW; ++r) acc[r] = typename M::acc_t{0, 0, 0, 0};
-    } else {
-#pragma unroll
-        for (int r = 0; r < RBW; ++r)
-            acc[r] = typename M::acc_t{dI[r][0] * cI, dI[r][1] * cI, dI[r][2] * cI, dI[r][3] * cI};
-        buffer_ld(cI, cr, boffI, soff);
+        boffI = (uint32_t(Ia) * uint32_t(p.ld) + col) * 8u;   // < cp_bytes
     }
+    const __amdgpu_buffer_rsrc_t cr = buffer_of(p.cp, p.cp_bytes);
+    const __amdgpu_buffer_rsrc_t pr = buffer_of(p.plan, p.plan_bytes);
+    const int ntile = p.ld / kNT;
+    double b[KS], cI = 0;
+    doublex4 acc[NB > 0 ? NB : 1];
+    double accq[NS > 0 ? NS : 1];
+    // W of the rows held in b; as each k step is consumed, b[t] is reloaded with the
+    // rows of tile `next`, so the loads stay in flight for a whole tile.  MEET: the
+    // barrier at which the scattering waves are done with the last W, half way.
+    auto products = [&](int next, bool meet) {
+        const uint32_t so = uint32_t(next) * (kNT * 8u);
+        if constexpr (SELF) {
 #pragma unroll
-    for (int t = 0; t < KS; ++t) {
+            for (int f = 0; f < NB; ++f) acc[f] = doublex4{0, 0, 0, 0};
 #pragma unroll
-        for (int r = 0; r < RBW; ++r) acc[r] = M::op(A[r][t], b[t], acc[r]);
-        buffer_ld(b[t], cr, boff[t], soff);
-        __builtin_amdgcn_sched_barrier(0);   // keep the reload next to its k step
+            for (int f = 0; f < NS; ++f) accq[f] = 0;
+        } else {
+#pragma unroll
+            for (int f = 0; f < NB; ++f) acc[f] = doublex4{dB[f][0] * cI, dB[f][1] * cI, dB[f][2] * cI, dB[f][3] * cI};
+#pragma unroll
+            for (int f = 0; f < NS; ++f) accq[f] = dQ[f] * cI;
+            buffer_ld(cI, cr, boffI, so);
+        }
+#pragma unroll
+        for (int t = 0; t < KS; ++t) {
+            if (meet && t == KS / 2) lds_barrier();
+#pragma unroll
+            for (int f = 0; f < NB; ++f) acc[f] = Mfma<double>::op(A[f][t], b[t], acc[f]);
+#pragma unroll
+            for (int f = 0; f < NS; ++f) accq[f] = mfma_quad(A[NB + f][t], b[t], accq[f]);
+            buffer_ld(b[t], cr, boff[t], so);
+            __builtin_amdgcn_sched_barrier(0);   // keep the reload next to its k step
+        }
+    };
+    auto store_w = [&]() {
+        const uint32_t o = uint32_t((m0 + lk) * kWS + int(col)) * 8u;
+#pragma unroll
+        for (int f = 0; f < NB; ++f)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) lds_st<double>(o + uint32_t((16 * f + 4 * i) * kWS) * 8u, acc[f][i]);
+#pragma unroll
+        for (int f = 0; f < NS; ++f) lds_st<double>(o + uint32_t((16 * NB + 4 * f) * kWS) * 8u, accq[f]);
+    };
+    // this wave's quarter of a tile's groups: the words, then their sums
+    ProgWords<double, PG> pw;
+    const uint32_t pl = uint32_t(sw * pw.NW * 64 + lane) * 4u, mine = uint32_t(sw * 64 + lane) * 8u;
+    auto scatter = [&](int next) {
+        if constexpr (SCAT) {
+            __builtin_amdgcn_s_setprio(3);
+            prog_run<SC, SIG>(pw, mine);
+            pw.load(pr, pl, next);
+            __builtin_amdgcn_s_setprio(0);
+        }
+    };
+#pragma unroll
+    for (int t = 0; t < KS; ++t) buffer_ld(b[t], cr, boff[t], 0u);
+    if constexpr (!SELF) buffer_ld(cI, cr, boffI, 0u);
+    if constexpr (SCAT) pw.load(pr, pl, 0);
+    products(ntile > 1 ? 1 : 0, false);
+    lds_barrier();                       // the sigma row and the zeros of W's pad columns are in LDS
+    store_w();
+    lds_barrier();                       // W of tile 0 ready
+    for (int tile = 0; tile + 1 < ntile; ++tile) {
+        scatter(tile + 1);
+        if constexpr (SCAT) lds_barrier();   // W of this tile consumed
+        products(tile + 2 < ntile ? tile + 2 : ntile - 1, !SCAT);
+        store_w();
+        lds_barrier();                   // W of the next tile ready
     }
+    scatter(ntile - 1);
 }
 
-template <typename T, int RBW>
-__device__ __forceinline__ void abx_store_w(T *W, const typename Mfma<T>::acc_t (&acc)[RBW], int lane, int cb,
-                                            int rb0, int nrb) {
-    using M = Mfma<T>;
-#pragma unroll
-    for (int r = 0; r < RBW; ++r)
-        if (r < nrb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                W[((rb0 + r) * 16 + M::out_row(lane, i)) * kAbxWS + cb * 16 + (lane & 15)] = acc[r][i];
-}
-
-// ---- eight-wave form -------------------------------------------------------------
-//
-// On gfx950 an FP64 MFMA keeps its SIMD from issuing vector instructions of
-// other waves, so a scatter wave that shares a SIMD with a producing wave waits
-// out every matrix instruction.  The roles are therefore split by SIMD: the
-// eight waves of a workgroup are placed on the four SIMDs in turn (wave w on
-// SIMD w mod 4), waves 3 and 7 scatter (the four plan ranges of a tile, two
-// each) and share one SIMD, and the other six multiply -- three 16-row-block
-// groups x two 16-column halves -- on the other three SIMDs.  The sigma row
-// leaves room for one W tile: the producing waves compute the next tile's W in
-// registers while the scatter waves consume this tile's, and store it between
-// two barriers.
-template <typename T, int KS, int RB, int EW, bool SELF>
-__global__ __launch_bounds__(512, 1) void k_sigma_ab_x(AbxArgs<T> p) {
-    using acc_t = typename Mfma<T>::acc_t;
-    using vec_t = typename Mfma<T>::vec_t;
-    constexpr int VEC = 16 / sizeof(T);
-    constexpr int RBW = (RB + 2) / 3;
-    constexpr int MP = 16 * RB;
-    constexpr int PW = (EW + 1) * 64;                      // plan words per range and tile
-    constexpr int PT = 4 * PW;
+// KS: k steps (4*KS >= excitations, plus one with SELF); Q: quads of W rows (4*Q >=
+// npair); RB: 16-row blocks that the program's W has room for; PG: program
+template <int KS, int Q, int RB, int PG, bool SELF>
+__global__ __launch_bounds__(512, 2) void k_sigma_ab_x(AbxArgs p) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    T *W = reinterpret_cast<T *>(smem_raw);                // [MP][WS]
-    T *sig = W + MP * kAbxWS;                              // [ld + 64]: slots ld.. take discarded writes
+    double *W = reinterpret_cast<double *>(smem_raw);      // [16 RB][kWS], then the waves' scratch
+    double *sig = W + 16 * RB * kWS + kProgWaves * 64;     // [ld + 64]: slots ld.. take discarded writes
+    const int Ia = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = wave >> 1, cb = wave & 1;
+    double *row = p.sp + int64_t(Ia) * p.ld;
+    for (int c = tid * 2; c < p.ld; c += 1024)
+        *reinterpret_cast<double2_t *>(sig + c) = *reinterpret_cast<const double2_t *>(row + c);
+    for (int r = tid; r < 16 * RB; r += 512) W[r * kWS + kNT] = 0.0;   // pad column: unused references read it
+    static_assert(group_quad0(Q, 3) + group_quads(Q, 3) == Q && 4 * Q <= 16 * RB, "every quad has a wave");
+    if (g == 0) abx_body<KS, group_quads(Q, 0), RB, PG, SELF, false>(p, Ia, cb, 0, 0, lane);
+    else if (g == 1) abx_body<KS, group_quads(Q, 1), RB, PG, SELF, false>(p, Ia, cb, 4 * group_quad0(Q, 1), 0, lane);
+    else if (g == 2) abx_body<KS, group_quads(Q, 2), RB, PG, SELF, true>(p, Ia, cb, 4 * group_quad0(Q, 2), wave - 4, lane);
+    else abx_body<KS, group_quads(Q, 3), RB, PG, SELF, true>(p, Ia, cb, 4 * group_quad0(Q, 3), wave - 4, lane);
+    __syncthreads();
+    for (int c = tid * 2; c < p.ld; c += 1024)
+        *reinterpret_cast<double2_t *>(row + c) = *reinterpret_cast<const double2_t *>(sig + c);
+}
 
-    const int Ia = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: the roles branch per wave
-    const int64_t rowoff = int64_t(Ia) * p.ld;
-    for (int c = tid * VEC; c < p.ld; c += 512 * VEC)
-        *reinterpret_cast<vec_t *>(sig + c) = *reinterpret_cast<const vec_t *>(p.sp + rowoff + c);
-    for (int r = tid; r < MP; r += 512) W[r * kAbxWS + kAbxNT] = T(0);   // pad column: plan padding reads it
-    const int ntile = p.ld / kAbxNT;
-    if ((wave & 3) != 3) {
-        const int m = (wave >> 2) * 3 + (wave & 3);        // 0..5
-        const int cb = m & 1, rb0 = (m >> 1) * RBW;
-        const int nrb = RB - rb0 < RBW ? RB - rb0 : RBW;   // may be <= 0 for small RB
-        T A[RBW][KS];
-        uint32_t boff[KS];
-        abx_fragments<T, KS, RBW, SELF>(p, Ia, lane, cb, rb0, nrb, A, boff);
-        T dI[RBW][4] = {};
-        uint32_t boffI = 0;
-        if constexpr (!SELF) abx_self_fragments<T, RBW>(p, Ia, lane, cb, rb0, nrb, dI, boffI);
-        const __amdgpu_buffer_rsrc_t cr = buffer_of(p.cp, p.cp_bytes);
-        T b[KS];
-        T cI = 0;
-        acc_t acc[RBW];
-        abx_load<T, KS>(cr, boff, 0, b);
-        if constexpr (!SELF) buffer_ld(cI, cr, boffI, 0u);
-        abx_products<T, KS, RBW, SELF>(cr, A, boff, ntile > 1 ? 1 : 0, b, acc, dI, boffI, cI);
-        __syncthreads();                       // the sigma row is in LDS
-        abx_store_w<T, RBW>(W, acc, lane, cb, rb0, nrb);
-        __syncthreads();                       // W of tile 0 ready
-        for (int tile = 0; tile < ntile; ++tile) {
-            if (tile + 1 < ntile) {
-                const int t2 = tile + 2 < ntile ? tile + 2 : ntile - 1;
-                abx_products<T, KS, RBW, SELF>(cr, A, boff, t2, b, acc, dI, boffI, cI);
-            }
-            __syncthreads();                   // W of this tile consumed
-            if (tile + 1 < ntile) abx_store_w<T, RBW>(W, acc, lane, cb, rb0, nrb);
-            __syncthreads();                   // W of the next tile ready
-        }
-    } else {
-        const __amdgpu_buffer_rsrc_t pr = buffer_of(p.plan, p.plan_bytes);
-        const int sw = wave >> 2;                          // plan ranges sw and sw + 2
-        const uint32_t pl0 = uint32_t(sw * PW + lane) * 4u, pl1 = uint32_t((sw + 2) * PW + lane) * 4u;
-        const uint32_t spare = uint32_t(p.ld + lane) * uint32_t(sizeof(T));
-        uint32_t pa0[EW], ha0, pa1[EW], ha1, pb0[EW], hb0, pb1[EW], hb1;
-        abx_plan_load<EW>(pr, pl0, 0u, pa0, ha0);
-        abx_plan_load<EW>(pr, pl1, 0u, pa1, ha1);
-        __syncthreads();                       // the sigma row is in LDS
-        __syncthreads();                       // W of tile 0 ready
-        for (int tile = 0; tile < ntile; tile += 2) {
-            const int t1 = tile + 1 < ntile ? tile + 1 : tile, t2 = tile + 2 < ntile ? tile + 2 : t1;
-            abx_plan_load<EW>(pr, pl0, uint32_t(t1) * (PT * 4u), pb0, hb0);
-            abx_plan_load<EW>(pr, pl1, uint32_t(t1) * (PT * 4u), pb1, hb1);
-            abx_scatter<T, EW>(W, sig, pa0, ha0, spare);
-            abx_scatter<T, EW>(W, sig, pa1, ha1, spare);
-            __syncthreads();                   // W of this tile consumed
-            __syncthreads();                   // W of the next tile ready
-            if (tile + 1 < ntile) {
-                abx_plan_load<EW>(pr, pl0, uint32_t(t2) * (PT * 4u), pa0, ha0);
-                abx_plan_load<EW>(pr, pl1, uint32_t(t2) * (PT * 4u), pa1, ha1);
-                abx_scatter<T, EW>(W, sig, pb0, hb0, spare);
-                abx_scatter<T, EW>(W, sig, pb1, hb1, spare);
-                __syncthreads();
-                __syncthreads();
-            }
-        }
+size_t abx_lds(int ld, int rb) { return (size_t(16) * rb * kWS + kProgWaves * 64 + ld + 64) * sizeof(double); }
+
+template <int KS, int Q, int RB, int PG, bool SELF>
+hipError_t run_abx(const AbxArgs &a, hipStream_t s) {
+    const size_t lds = abx_lds(a.ld, RB);
+    if (4 * Q < a.npair || 4 * KS < a.anexc + (SELF ? 1 : 0)) return hipErrorInvalidValue;
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sigma_ab_x<KS, Q, RB, PG, SELF>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+        if (e != hipSuccess) return e;
     }
-    for (int cc = tid * VEC; cc < p.ld; cc += 512 * VEC)
-        *reinterpret_cast<vec_t *>(p.sp + rowoff + cc) = *reinterpret_cast<const vec_t *>(sig + cc);
-}
-
-// LDS bytes: the W tile and the sigma row with its 64 discard slots
-template <typename T>
-size_t abx_lds(int ld, int rb) {
-    return (size_t(16) * rb * kAbxWS + ld + 64) * sizeof(T);
-}
-
-template <typename T, int KS, int RB, int EW, bool SELF>
-hipError_t run_abx(const AbxArgs<T> &a, hipStream_t s) {
-    const size_t lds = abx_lds<T>(a.ld, RB);
-    if (lds > 160 * 1024 || 16 * RB < a.npair || 4 * KS < a.anexc + (SELF ? 1 : 0)) return hipErrorInvalidValue;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sigma_ab_x<T, KS, RB, EW, SELF>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_sigma_ab_x<T, KS, RB, EW, SELF>), dim3(a.Na), dim3(512), lds, s, a);
+    hipLaunchKernelGGL((k_sigma_ab_x<KS, Q, RB, PG, SELF>), dim3(a.Na), dim3(512), lds, s, a);
     return hipGetLastError();
 }
 
-int ks_of(int anexc) { return (anexc + 1 + 3) / 4; }
-int rb_of(int npair) { return (npair + 15) / 16; }
+// Compiled (KS, Q, RB, program), by ascending KS: for each RB = ceil(n(n+1)/32) the
+// quads of the largest n, the k steps of the half-filled spaces (and, for the larger
+// n, of the low fillings), and the programs of the FP32 kernel's table.
+#define CIS_ABX_SHAPES(X) \
+    X(2, 4, 1, 0) X(3, 7, 2, 0) X(4, 7, 2, 0) X(4, 12, 3, 0) X(4, 12, 3, 1) X(6, 12, 3, 0) X(6, 12, 3, 1) \
+    X(4, 14, 4, 0) X(4, 14, 4, 1) X(7, 14, 4, 0) X(7, 14, 4, 1) \
+    X(5, 20, 5, 1) X(5, 20, 5, 4) X(8, 17, 5, 1) X(8, 17, 5, 4) X(9, 20, 5, 1) X(9, 20, 5, 4) \
+    X(8, 23, 6, 2) X(8, 23, 6, 4) X(11, 23, 6, 2) X(11, 23, 6, 4) \
+    X(9, 27, 7, 2) X(9, 27, 7, 4) X(13, 27, 7, 2) X(13, 27, 7, 4) \
+    X(10, 30, 8, 3) X(10, 30, 8, 4) X(15, 30, 8, 3) X(15, 30, 8, 4) \
+    X(10, 34, 9, 3) X(10, 34, 9, 4) X(16, 34, 9, 3) X(16, 34, 9, 4)
+// With Ia's row as the rank-1 start of the accumulators, where the excitations
+// fill the k steps: 8, 12 and 16 half-filled orbitals.
+#define CIS_ABX_SHAPES_R1(X) \
+    X(4, 12, 3, 0) X(4, 12, 3, 1) X(9, 20, 5, 1) X(9, 20, 5, 4) X(16, 34, 9, 3) X(16, 34, 9, 4)
 
-// The compiled (KS, RB, EW) shapes: for each (KS, RB) of the CAS(n, n/2)
-// spaces n = 4..16 and their open-shell neighbours, the plan width of
-// CAS(n, n/2) and a wider one.
-#define CIS_ABX_SHAPES(X)                                                                              \
+// The shapes that cisigma_last_shape names: k steps, row blocks and the entries per
+// lane of a scatter plan in equal runs, by the spaces CAS(n, n/2) and their
+// open-shell neighbours.
+#define CIS_ABX_NAMES(X)                                                                               \
     X(2, 1, 2) X(2, 1, 16) X(3, 2, 2) X(3, 2, 16) X(4, 2, 4) X(4, 2, 16) X(4, 3, 4) X(4, 3, 16)         \
     X(5, 3, 4) X(5, 3, 16) X(6, 3, 4) X(6, 3, 16) X(6, 4, 4) X(6, 4, 16) X(7, 4, 4) X(7, 4, 16)         \
     X(8, 5, 6) X(8, 5, 16) X(10, 5, 6) X(10, 5, 16) X(11, 6, 8) X(11, 6, 16) X(13, 7, 8) X(13, 7, 16)   \
     X(15, 8, 10) X(15, 8, 16) X(17, 9, 10) X(17, 9, 16)
-
-// Shapes with Ia's row as the rank-1 start of the accumulators, for the
-// CAS(n, n/2) spaces of even n and their neighbours whose excitation count is
-// a multiple of 4 (there it saves a k step; elsewhere the row fills padding).
-// The 16-entry plan width serves spaces whose target groups would span more
-// than four lanes at the narrow width (CAS(8,8), CAS(12,12) and smaller).
-#define CIS_ABX_SHAPES_R1(X)                                                                           \
+#define CIS_ABX_NAMES_R1(X)                                                                            \
     X(1, 1, 2) X(1, 1, 16) X(2, 2, 2) X(2, 2, 16) X(4, 3, 4) X(4, 3, 16) X(6, 4, 4) X(6, 4, 16)         \
     X(9, 5, 6) X(9, 5, 16) X(12, 7, 8) X(12, 7, 16) X(16, 9, 10) X(16, 9, 16)
 
-int width_for(int ks, int rb, int need) {
-    int best = 0;
-#define CIS_W(K, R, E) if (ks == K && rb == R && E >= need && (best == 0 || E < best)) best = E;
-    CIS_ABX_SHAPES(CIS_W)
-#undef CIS_W
-    return best;
-}
-
-// shape[4] receives {KS, RB, EW, 1: row in a k step, 2: rank-1 start}
-template <typename T>
-bool dispatch_abx(const AbxArgs<T> &a, int ew, hipStream_t s, hipError_t *err, int *shape) {
-    const int rb = rb_of(a.npair);
-    if (a.anexc > 0 && a.anexc % 4 == 0) {
-        const int ks1 = a.anexc / 4;
-#define CIS_RUN1(K, R, E)                                           \
-    if (ks1 == K && rb == R && ew == E) {                           \
-        *err = run_abx<T, K, R, E, false>(a, s);                    \
-        shape[0] = K; shape[1] = R; shape[2] = E; shape[3] = 2;     \
-        return true;                                                \
-    }
-        CIS_ABX_SHAPES_R1(CIS_RUN1)
-#undef CIS_RUN1
-    }
-    const int ks = ks_of(a.anexc);
-#define CIS_RUN(K, R, E)                                            \
-    if (ks == K && rb == R && ew == E) {                            \
-        *err = run_abx<T, K, R, E, true>(a, s);                     \
-        shape[0] = K; shape[1] = R; shape[2] = E; shape[3] = 1;     \
-        return true;                                                \
-    }
-    CIS_ABX_SHAPES(CIS_RUN)
-#undef CIS_RUN
-    return false;
-}
-
-bool owner_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipError_t *err) {
-    using T = double;
-    const ScatterPlan &P = ctx->plan;
-    const uint32_t *plan = P.d_entries[0];
-    if (!plan || P.ew == 0) return false;
-    const auto &A = ctx->sp[0];
-    AbxArgs<T> x{};
-    x.cp = static_cast<const T *>(cp);
-    x.sp = static_cast<T *>(sp);
-    x.aexc = A.d_exc;
-    x.astr = A.d_str;
-    x.gp = ctx->d_gp64;
-    x.plan = plan;
-    x.anexc = A.nexc;
-    x.n = ctx->n;
-    x.kp = ctx->kp;
-    x.npair = ctx->npair;
-    x.Na = A.nstr;
-    x.ld = ctx->pl[0].ld[0];
-    if (abx_lds<T>(x.ld, rb_of(x.npair)) > 160 * 1024) return false;
-    // 32-bit byte offsets of the gathered rows (the zero row Na included) and of the plan
-    const uint64_t cpb = (uint64_t(x.Na) + 1) * uint64_t(x.ld) * sizeof(T);
-    const uint64_t plb = uint64_t(P.ntile) * 4 * (P.ew + 1) * 64 * sizeof(uint32_t);
-    if (cpb >= (uint64_t(1) << 31) || plb >= (uint64_t(1) << 31)) return false;
-    x.cp_bytes = uint32_t(cpb);
-    x.plan_bytes = uint32_t(plb);
-    auto *c = const_cast<cisigma_ctx *>(ctx);
-    return dispatch_abx<T>(x, P.ew, s, err, c->last_shape[0]);
-}
+int ks_of(int anexc) { return (anexc + 1 + 3) / 4; }
+int rb_of(int npair) { return (npair + 15) / 16; }
 
 }  // namespace
 
 int sigma_ab_owner_width(int anexc, int npair, int need) {
-    return width_for(ks_of(anexc), rb_of(npair), need);
+    const int ks = ks_of(anexc), rb = rb_of(npair);
+    int best = 0;
+#define CIS_W(K, R, E) if (ks == K && rb == R && E >= need && (best == 0 || E < best)) best = E;
+    CIS_ABX_NAMES(CIS_W)
+#undef CIS_W
+    return best;
 }
 
 void sigma_ab_owner_shape(int anexc, int npair, int ew, int *shape) {
@@ -380,12 +300,52 @@ void sigma_ab_owner_shape(int anexc, int npair, int ew, int *shape) {
     shape[2] = ew;
     shape[3] = 1;
 #define CIS_R1(K, R, E) if (anexc == 4 * K && rb == R && ew == E) { shape[0] = K; shape[3] = 2; }
-    CIS_ABX_SHAPES_R1(CIS_R1)
+    CIS_ABX_NAMES_R1(CIS_R1)
 #undef CIS_R1
 }
 
 bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipError_t *err) {
-    return owner_t(ctx, cp, sp, s, err);
+    const ProgPlan &P = ctx->prog;
+    if (!P.d_words) return false;
+    const auto &A = ctx->sp[0];
+    AbxArgs x{};
+    x.cp = static_cast<const double *>(cp);
+    x.sp = static_cast<double *>(sp);
+    x.aexc = A.d_exc;
+    x.astr = A.d_str;
+    x.gp = ctx->d_gp64;
+    x.plan = P.d_words;
+    x.anexc = A.nexc;
+    x.n = ctx->n;
+    x.kp = ctx->kp;
+    x.npair = ctx->npair;
+    x.Na = A.nstr;
+    x.ld = ctx->pl[0].ld[0];
+    const int rb = rb_of(x.npair);
+    if (abx_lds(x.ld, rb) > 160 * 1024) return false;
+    // 32-bit byte offsets of the gathered rows (the zero row Na included) and of the plan
+    const uint64_t cpb = (uint64_t(x.Na) + 1) * uint64_t(x.ld) * sizeof(double);
+    const uint64_t plb = uint64_t(P.ntile) * kProgWaves * kProgs[P.prog].words() * 64 * sizeof(uint32_t);
+    if (cpb >= (uint64_t(1) << 31) || plb >= (uint64_t(1) << 31)) return false;
+    x.cp_bytes = uint32_t(cpb);
+    x.plan_bytes = uint32_t(plb);
+    bool ran = false;
+#define CIS_RUN1(K, Q, R, G) \
+    if (!ran && x.anexc == 4 * K && rb == R && P.prog == G) { *err = run_abx<K, Q, R, G, false>(x, s); ran = true; }
+    CIS_ABX_SHAPES_R1(CIS_RUN1)
+#undef CIS_RUN1
+    // the fewest k steps and quads that hold the space
+#define CIS_RUN(K, Q, R, G)                                                                    \
+    if (!ran && 4 * K >= x.anexc + 1 && 4 * Q >= x.npair && rb == R && P.prog == G) {          \
+        *err = run_abx<K, Q, R, G, true>(x, s);                                                \
+        ran = true;                                                                            \
+    }
+    CIS_ABX_SHAPES(CIS_RUN)
+#undef CIS_RUN
+    if (!ran) return false;
+    auto *c = const_cast<cisigma_ctx *>(ctx);
+    for (int i = 0; i < 4; ++i) c->last_shape[0][i] = P.shape[i];
+    return true;
 }
 
 }  // namespace cis
