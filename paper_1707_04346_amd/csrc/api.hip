@@ -1200,6 +1200,10 @@ size_t workspace_copy_bytes(const cisigma_ctx *c, size_t es) {
 
 // rows of the materialised same-spin products (one-type spins whose pair count
 // has MFMA kernels), their widest row, and whether every spin qualifies
+size_t ys_spin_bytes(const cisigma_ctx *c, int s, size_t es) {
+    return size_t(c->sp[s].nK) * c->sp[s].npv * size_t(c->pl[s].ld[0]) * es;
+}
+
 bool ys_shape(const cisigma_ctx *c, size_t *rows, size_t *cols) {
     *rows = 0;
     *cols = 0;
@@ -1213,6 +1217,21 @@ bool ys_shape(const cisigma_ctx *c, size_t *rows, size_t *cols) {
             ok = ok && cis::same_spin_materialisable(c->sp[s].npv) && c->sp[s].d_pair_inv;
         }
     return ok && *rows > 0;
+}
+
+// Bytes of the stored rows of both spins side by side, 0 where the spins go one after
+// the other: only for rows that stay in the Infinity Cache (256 MB) until they are
+// gathered.  There a sigma is a few launches of a few microseconds each: with both
+// spins in one launch a sigma of CAS(6,6) takes 18.9 instead of 24.6 us, of CAS(12,12) in
+// FP32 156 instead of 162; larger ones gain nothing.
+size_t ys_both_bytes(const cisigma_ctx *c, size_t es) {
+    size_t rows = 0, cols = 0, total = 0;
+    if (!ys_shape(c, &rows, &cols)) return 0;
+    for (int s = 0; s < 2; ++s) {
+        if (c->sp[s].nel < 2) return 0;
+        total += ys_spin_bytes(c, s, es);
+    }
+    return total <= (size_t(224) << 20) ? total : 0;
 }
 
 int ensure_workspace(cisigma_ctx *c, int dtype) {
@@ -1247,10 +1266,14 @@ int ensure_workspace(cisigma_ctx *c, int dtype) {
                                                                    cis::kTileCols);
             chunk = std::min(chunk, slab);
         }
-        if (chunk >= size_t(cis::kTileCols) && hipMalloc(&W.ys, rows * chunk * es) == hipSuccess)
+        size_t both = chunk == cols ? ys_both_bytes(c, es) : 0;
+        if (both > budget) both = 0;
+        if (chunk >= size_t(cis::kTileCols) && hipMalloc(&W.ys, std::max(rows * chunk * es, both)) == hipSuccess) {
             W.ys_chunk = int(chunk);
-        else
+            if (both) W.ys2 = static_cast<unsigned char *>(W.ys) + ys_spin_bytes(c, 0, es);
+        } else {
             W.ys = nullptr;
+        }
     }
     // several types: all rows at once when they fit in half of what is free
     const int64_t ny = ys_rows_elems(c);
@@ -1313,8 +1336,18 @@ int apply_sigma_ws(cisigma_ctx *c, const void *C, void *sigma, int dtype, hipStr
     }
     HIP_OR_FAIL(c, mark(CISIGMA_PASS_CLEAR), "apply: profiling events");
     const int chunk = c->ss_chunk > 0 ? std::min(c->ss_chunk, W.ys_chunk) : W.ys_chunk;
-    HIP_OR_FAIL(c, launch_sigma_same_spin(c, 0, W.cp, par ? W.st : W.sp, dtype, s, mat ? W.ys : nullptr, chunk),
-                "apply: sigma_2 (alpha-alpha)");
+    // small spaces: both spins in one launch of each kernel (with profiling on one after
+    // the other, so that each can be timed)
+    const bool fork = own && !par && c->overlap && c->side;
+    const bool both = mat && W.ys2 && !par && !fork && !prof && chunk >= c->pl[0].ld[0] && chunk >= c->pl[1].ld[0];
+    if (both) {
+        const void *X[2] = {W.cp, W.ct};
+        void *Y[2] = {W.sp, W.st}, *Ys[2] = {W.ys, W.ys2};
+        HIP_OR_FAIL(c, launch_same_spin_both(c, X, Y, dtype, s, Ys), "apply: sigma_1 and sigma_2 (same spin)");
+    } else {
+        HIP_OR_FAIL(c, launch_sigma_same_spin(c, 0, W.cp, par ? W.st : W.sp, dtype, s, mat ? W.ys : nullptr, chunk),
+                    "apply: sigma_2 (alpha-alpha)");
+    }
     HIP_OR_FAIL(c, mark(CISIGMA_PASS_SIGMA_AA), "apply: profiling events");
     // the beta-beta pass (memory-bound) overlaps the alpha-beta pass (matrix-core
     // bound) on the side stream: they read different copies of C and write
@@ -1322,7 +1355,6 @@ int apply_sigma_ws(cisigma_ctx *c, const void *C, void *sigma, int dtype, hipStr
     // alpha-alpha pass, which precedes the fork.  The events of the alpha-beta
     // pass then time it while the other runs; the beta-beta "pass" time is the
     // wait for it after that.
-    const bool fork = own && !par && c->overlap && c->side;
     if (fork) {
         HIP_OR_FAIL(c, hipEventRecord(c->ev_fork, s), "apply: fork");
         HIP_OR_FAIL(c, hipStreamWaitEvent(c->side, c->ev_fork, 0), "apply: fork");
@@ -1341,7 +1373,7 @@ int apply_sigma_ws(cisigma_ctx *c, const void *C, void *sigma, int dtype, hipStr
     HIP_OR_FAIL(c, mark(CISIGMA_PASS_SIGMA_AB), "apply: profiling events");
     if (fork)
         HIP_OR_FAIL(c, hipStreamWaitEvent(s, c->ev_join, 0), "apply: join");
-    else if (!par)
+    else if (!par && !both)
         HIP_OR_FAIL(c, launch_sigma_same_spin(c, 1, W.ct, W.st, dtype, s, mat ? W.ys : nullptr, chunk),
                     "apply: sigma_1 (beta-beta)");
     HIP_OR_FAIL(c, mark(CISIGMA_PASS_SIGMA_BB), "apply: profiling events");
@@ -1396,6 +1428,9 @@ int apply_sigma_noalloc(cisigma_ctx *c, const void *C, void *sigma, int dtype, h
         if (chunk >= size_t(cis::kTileCols)) {
             W.ys = base + copies;
             W.ys_chunk = int(chunk);
+            const size_t both = ys_both_bytes(c, es);
+            if (both && both <= kNoallocScratchBytes - copies)
+                W.ys2 = static_cast<unsigned char *>(W.ys) + ys_spin_bytes(c, 0, es);
         }
     }
     const int64_t ny = ys_rows_elems(c);

@@ -191,6 +191,7 @@ struct Workspace {
     void *st = nullptr;    // beta same-spin sigma, beta-major padded layout
     void *ys = nullptr;    // materialised same-spin rows (one-type spins), ys_chunk columns each
     int ys_chunk = 0;
+    void *ys2 = nullptr;   // in ys: the beta rows beside the alpha ones (small spaces, all columns), else null
     bool ready = false;
 };
 
@@ -326,6 +327,10 @@ hipError_t launch_sigma_same_spin(const cisigma_ctx *ctx, int spin, const void *
                                   hipStream_t s, void *Ys = nullptr, int chunk = 0);
 // whether the same-spin pair count npv has compiled MFMA kernels (else a plain
 // atomic kernel serves it and the materialised form is not used)
+// Both spins of a one-block space (two or more electrons each) by one launch of each
+// kernel; X, Y, Ys by spin, Ys all columns.
+hipError_t launch_same_spin_both(const cisigma_ctx *ctx, const void *const *X, void *const *Y, int dtype, hipStream_t s,
+                                 void *const *Ys);
 bool same_spin_materialisable(int npv);
 // smallest compiled same-spin pair-kernel shape (k steps, 16-row blocks) for
 // lists of `count` pairs; false when none is compiled

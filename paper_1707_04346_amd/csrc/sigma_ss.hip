@@ -269,7 +269,7 @@ struct SsyArgs {
 };
 
 template <typename T, int KS, int MBL>
-__global__ __launch_bounds__(256, 2) void k_sigma_ss_y(SsyArgs<T> p) {
+__device__ __forceinline__ void ssy_body(const SsyArgs<T> &p, int block) {
     using M = Mfma<T>;
     using acc_t = typename M::acc_t;
     using vec_t = typename M::vec_t;
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(256, 2) void k_sigma_ss_y(SsyArgs<T> p) {
     int *pid = rowJ + NE;
     int *neg = pid + NE;
 
-    const int K = xcd_contig(int(blockIdx.x), int(gridDim.x));
+    const int K = xcd_contig(block, p.nK);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (int q = tid; q < NE; q += 256) {
         const uint32_t w = (q < p.npv) ? p.pairs[int64_t(K) * p.npv + q] : kPairNone;
@@ -370,17 +370,43 @@ __global__ __launch_bounds__(256, 2) void k_sigma_ss_y(SsyArgs<T> p) {
     }
 }
 
+template <typename T, int KS, int MBL>
+__global__ __launch_bounds__(256, 2) void k_sigma_ss_y(SsyArgs<T> p) {
+    ssy_body<T, KS, MBL>(p, int(blockIdx.x));
+}
+
+// Both spins in a launch, the first a.nK workgroups the first.  For small spaces, which
+// are bound by launches and by grids that leave the chip idle.  (A kernel of its own:
+// with the choice of the set in the one-spin kernel the passes of 13 orbitals took 5 to
+// 20% longer.)
+template <typename T, int KS, int MBL>
+__global__ __launch_bounds__(256, 2) void k_sigma_ss_y2(SsyArgs<T> a, SsyArgs<T> b) {
+    if (int(blockIdx.x) < a.nK) ssy_body<T, KS, MBL>(a, int(blockIdx.x));
+    else ssy_body<T, KS, MBL>(b, int(blockIdx.x) - a.nK);
+}
+
+template <typename T>
+struct GatherArgs {
+    const T *Ys;             // rows of ldy columns, from column col_begin on
+    int64_t ldy, ld;
+    int col_begin, col_end;
+    const int *inv;          // [nstr][per]
+    int per, nstr;
+    T *out;                  // row stride ld
+};
+
 // out(I, c) = sum over the occupied pairs of I of the materialised rows
 // Ys(K*npv + e, c): the owner-computes half of the same-spin part.
 template <typename T>
-__global__ __launch_bounds__(256) void k_pair_gather(const T *__restrict__ Ys, int64_t ldy, int col_begin,
-                                                     int col_end, const int *__restrict__ inv, int per,
-                                                     T *__restrict__ out, int64_t ld) {
+__device__ __forceinline__ void gather_body(const GatherArgs<T> &p, int I) {
+    const T *__restrict__ Ys = p.Ys;
+    T *__restrict__ out = p.out;
+    const int64_t ldy = p.ldy, ld = p.ld;
+    const int col_begin = p.col_begin, col_end = p.col_end, per = p.per;
     using vec_t = typename Mfma<T>::vec_t;
     constexpr int VEC = 16 / sizeof(T);
     __shared__ int rows[64];
-    const int I = blockIdx.x;
-    for (int q = threadIdx.x; q < per; q += blockDim.x) rows[q] = inv[int64_t(I) * per + q];
+    for (int q = threadIdx.x; q < per; q += blockDim.x) rows[q] = p.inv[int64_t(I) * per + q];
     __syncthreads();
     for (int c = col_begin + int(threadIdx.x) * VEC; c < col_end; c += int(blockDim.x) * VEC) {
         // every row of Y is read once (streaming loads); four rows in flight per step
@@ -398,6 +424,16 @@ __global__ __launch_bounds__(256) void k_pair_gather(const T *__restrict__ Ys, i
             acc += __builtin_nontemporal_load(reinterpret_cast<const vec_t *>(Ys + int64_t(rows[q]) * ldy + (c - col_begin)));
         *reinterpret_cast<vec_t *>(out + int64_t(I) * ld + c) = acc + acc2;
     }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_pair_gather(GatherArgs<T> p) {
+    gather_body<T>(p, int(blockIdx.x));
+}
+template <typename T>
+__global__ __launch_bounds__(256) void k_pair_gather2(GatherArgs<T> a, GatherArgs<T> b) {
+    if (int(blockIdx.x) < a.nstr) gather_body<T>(a, int(blockIdx.x));
+    else gather_body<T>(b, int(blockIdx.x) - a.nstr);
 }
 
 // Spaces with several types: out row I (type t) = sum over the occupied pairs
@@ -527,23 +563,32 @@ hipError_t run_ss(const SsArgs<T> &a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// one spin (b.nK = 0) or both
 template <typename T, int KS, int MBL>
-hipError_t run_ssy(const SsyArgs<T> &a, hipStream_t s) {
+hipError_t run_ssy(const SsyArgs<T> &a, const SsyArgs<T> &b, hipStream_t s) {
     constexpr int KP = 4 * KS, MP = 16 * MBL;
     constexpr int NE = KP > MP ? KP : MP;
     const size_t lds = size_t(MP) * (KP + 1) * sizeof(T) + 3 * NE * sizeof(int);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sigma_ss_y<T, KS, MBL>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_sigma_ss_y<T, KS, MBL>), dim3(a.nK), dim3(256), lds, s, a);
+    void (*const one)(SsyArgs<T>) = k_sigma_ss_y<T, KS, MBL>;
+    void (*const two)(SsyArgs<T>, SsyArgs<T>) = k_sigma_ss_y2<T, KS, MBL>;
+    if (lds > 64 * 1024) {
+        const hipError_t e =
+            hipFuncSetAttribute(b.nK ? reinterpret_cast<const void *>(two) : reinterpret_cast<const void *>(one),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+        if (e != hipSuccess) return e;
+    }
+    if (b.nK) hipLaunchKernelGGL(two, dim3(a.nK + b.nK), dim3(256), lds, s, a, b);
+    else hipLaunchKernelGGL(one, dim3(a.nK), dim3(256), lds, s, a);
     return hipGetLastError();
 }
 
+// the shape of the spin with more pairs (the other's missing ones are zero rows)
 template <typename T>
-hipError_t dispatch_ssy(const SsyArgs<T> &a, hipStream_t s) {
-    const int ks = (a.npv + 3) / 4;
-    const int mbl = (a.npv + 15) / 16;
-#define CIS_SSY(K, MB) if (ks == K && mbl == MB) return run_ssy<T, K, MB>(a, s);
+hipError_t dispatch_ssy(const SsyArgs<T> &a, const SsyArgs<T> &b, hipStream_t s) {
+    const int npv = std::max(a.npv, b.npv);
+    const int ks = (npv + 3) / 4;
+    const int mbl = (npv + 15) / 16;
+#define CIS_SSY(K, MB) if (ks == K && mbl == MB) return run_ssy<T, K, MB>(a, b, s);
     CIS_SSY(1, 1) CIS_SSY(2, 1) CIS_SSY(3, 1) CIS_SSY(4, 1) CIS_SSY(4, 2) CIS_SSY(6, 2) CIS_SSY(7, 2) CIS_SSY(9, 3)
     CIS_SSY(12, 3) CIS_SSY(14, 4) CIS_SSY(17, 5) CIS_SSY(20, 5) CIS_SSY(23, 6) CIS_SSY(27, 7) CIS_SSY(30, 8)
     CIS_SSY(34, 9) CIS_SSY(39, 10) CIS_SSY(43, 11)
@@ -583,6 +628,55 @@ hipError_t dispatch_ss(const SsArgs<T> &a, hipStream_t s) {
     CIS_SS(34, 9) CIS_SS(39, 10) CIS_SS(43, 11)
 #undef CIS_SS
     return hipErrorInvalidValue;
+}
+
+// bytes of a spin's C copy, the zero row included
+template <typename T>
+uint64_t copy_bytes(const cisigma_ctx *ctx, int spin) {
+    return (uint64_t(ctx->sp[spin].nstr) + 1) * uint64_t(ctx->pl[spin].ld[0]) * sizeof(T);
+}
+
+template <typename T>
+SsyArgs<T> ssy_args(const cisigma_ctx *ctx, int spin, const void *X, void *Ys, int c0, int c1) {
+    const auto &S = ctx->sp[spin];
+    SsyArgs<T> y{};
+    y.X = static_cast<const T *>(X);
+    y.Ys = static_cast<T *>(Ys);
+    y.pairs = S.d_pairs;
+    y.V = std::is_same<T, float>::value ? reinterpret_cast<const T *>(ctx->d_v32[spin])
+                                        : reinterpret_cast<const T *>(ctx->d_v64[spin]);
+    y.x_bytes = uint32_t(copy_bytes<T>(ctx, spin));
+    y.npv = S.npv;
+    y.nK = S.nK;
+    y.nps = ctx->nps;
+    y.nstr = S.nstr;
+    y.ld = int(ctx->pl[spin].ld[0]);
+    y.ldy = c1 - c0;
+    y.col_begin = c0;
+    y.col_end = c1;
+    return y;
+}
+
+template <typename T>
+GatherArgs<T> gather_args(const cisigma_ctx *ctx, int spin, const void *Ys, void *Y, int c0, int c1) {
+    const auto &S = ctx->sp[spin];
+    return {static_cast<const T *>(Ys), int64_t(c1 - c0), ctx->pl[spin].ld[0], c0, c1, S.d_pair_inv,
+            S.nel * (S.nel - 1) / 2, S.nstr, static_cast<T *>(Y)};
+}
+
+template <typename T>
+hipError_t same_spin_both_t(const cisigma_ctx *ctx, const void *const *X, void *const *Y, void *const *Ys, hipStream_t s) {
+    SsyArgs<T> y[2];
+    GatherArgs<T> g[2];
+    for (int spin = 0; spin < 2; ++spin) {
+        const int ld = int(ctx->pl[spin].ld[0]);
+        y[spin] = ssy_args<T>(ctx, spin, X[spin], Ys[spin], 0, ld);
+        g[spin] = gather_args<T>(ctx, spin, Ys[spin], Y[spin], 0, ld);
+    }
+    const hipError_t e = dispatch_ssy<T>(y[0], y[1], s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_pair_gather2<T>), dim3(g[0].nstr + g[1].nstr), dim3(256), 0, s, g[0], g[1]);
+    return hipGetLastError();
 }
 
 template <typename T>
@@ -659,26 +753,12 @@ hipError_t same_spin_t(const cisigma_ctx *ctx, int spin, const void *X, void *Y,
     }
     // materialised form, one column chunk at a time: store rows K*npv+P, then gather per string
     const int64_t ld = L.ld[0];
-    const uint64_t x_bytes = (uint64_t(S.nstr) + 1) * uint64_t(ld) * sizeof(T);   // the zero row included
+    const uint64_t x_bytes = copy_bytes<T>(ctx, spin);
     for (int c0 = 0; c0 < ld; c0 += chunk) {
         const int c1 = int(std::min<int64_t>(ld, c0 + chunk));
         hipError_t e;
         if (x_bytes < (uint64_t(1) << 31) && uint64_t(S.npv) * uint64_t(c1 - c0) * sizeof(T) < (uint64_t(1) << 31)) {
-            SsyArgs<T> y{};
-            y.X = static_cast<const T *>(X);
-            y.Ys = static_cast<T *>(Ys);
-            y.pairs = S.d_pairs;
-            y.V = a.V;
-            y.x_bytes = uint32_t(x_bytes);
-            y.npv = S.npv;
-            y.nK = S.nK;
-            y.nps = ctx->nps;
-            y.nstr = S.nstr;
-            y.ld = int(ld);
-            y.ldy = c1 - c0;
-            y.col_begin = c0;
-            y.col_end = c1;
-            e = dispatch_ssy<T>(y, s);
+            e = dispatch_ssy<T>(ssy_args<T>(ctx, spin, X, Ys, c0, c1), SsyArgs<T>{}, s);
         } else {
             a.Ys = static_cast<T *>(Ys);
             a.ldy = c1 - c0;
@@ -688,8 +768,7 @@ hipError_t same_spin_t(const cisigma_ctx *ctx, int spin, const void *X, void *Y,
             e = dispatch_ss<T, 1>(a, s);
         }
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_pair_gather<T>), dim3(S.nstr), dim3(256), 0, s, static_cast<const T *>(Ys),
-                           int64_t(c1 - c0), c0, c1, S.d_pair_inv, per, static_cast<T *>(Y), ld);
+        hipLaunchKernelGGL((k_pair_gather<T>), dim3(S.nstr), dim3(256), 0, s, gather_args<T>(ctx, spin, Ys, Y, c0, c1));
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -702,6 +781,11 @@ hipError_t launch_sigma_same_spin(const cisigma_ctx *ctx, int spin, const void *
                                   hipStream_t s, void *Ys, int chunk) {
     return dtype == CISIGMA_FP32 ? same_spin_t<float>(ctx, spin, X, Y, Ys, chunk, s)
                                  : same_spin_t<double>(ctx, spin, X, Y, Ys, chunk, s);
+}
+
+hipError_t launch_same_spin_both(const cisigma_ctx *ctx, const void *const *X, void *const *Y, int dtype, hipStream_t s,
+                                 void *const *Ys) {
+    return dtype == CISIGMA_FP32 ? same_spin_both_t<float>(ctx, X, Y, Ys, s) : same_spin_both_t<double>(ctx, X, Y, Ys, s);
 }
 
 bool same_spin_materialisable(int npv) { return ss_shape_compiled(npv); }

@@ -68,3 +68,49 @@ def test_gas_shapes(case, dtype):
     n, na, nb, gas = case
     _, err, _ = both(n, na, nb, dtype, 55, gas=gas)
     assert err <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("space", [(5, 2, 2), (6, 3, 3), (7, 1, 4), (8, 2, 6), (8, 5, 2), (9, 2, 2), (10, 5, 5), (11, 7, 3),
+                                   (12, 6, 6)], ids=lambda s: f"n{s[0]}a{s[1]}b{s[2]}")
+def test_both_spins_in_one_launch(space, dtype):
+    """Small spaces run the same-spin parts of both spins together, except while the
+    passes are timed: the same sums, so the same bits."""
+    import paper_1707_04346_amd as cis
+    n, na, nb = space
+    h, g = si.integrals(n, 2 * n, 59)
+    ctx = cis.Context(n, na, nb, h, g)
+    C = torch.tensor(si.ci_vector(ctx.ndet, 60), dtype=dtype, device="cuda")
+    S = [torch.full_like(C, float("nan")) for _ in range(3)]
+    ctx.apply(C, S[0])
+    ctx.set_option(cis.OPT_PROFILE, 1)
+    ctx.apply(C, S[1])
+    ctx.set_option(cis.OPT_PROFILE, 0)
+    ctx.apply(C, S[2])
+    torch.cuda.synchronize()
+    atomic = na == 1 or nb == 1            # (a single electron's part is added by atomics)
+    assert torch.equal(S[0], S[2]) or atomic
+    assert rel(S[0].double().cpu().numpy(), S[1].double().cpu().numpy()) <= (TOL[dtype] if atomic else 0.0)
+
+
+RDM = [(1, 1, 1), (3, 1, 2), (7, 3, 6), (8, 1, 7), (11, 2, 3), (12, 3, 2), (13, 2, 3), (13, 3, 1), (14, 2, 2), (15, 1, 3),
+       (15, 2, 2), (16, 2, 2), (16, 0, 3), (16, 1, 8)]
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("space", RDM, ids=lambda s: f"n{s[0]}a{s[1]}b{s[2]}")
+def test_density_shapes(space, dtype):
+    import paper_1707_04346_amd as cis
+    n, na, nb = space
+    h, g = si.integrals(n, 2 * n, 57)
+    ctx, ref = cis.Context(n, na, nb, h, g), oracle.Space(n, na, nb, h, g)
+    C = torch.tensor(si.ci_vector(ctx.ndet, 58), dtype=dtype, device="cuda")
+    g1 = torch.full((n, n), float("nan"), dtype=torch.float64, device="cuda")
+    g2 = torch.full((n, n, n, n), float("nan"), dtype=torch.float64, device="cuda")
+    ctx.rdm(C, g1, g2)
+    torch.cuda.synchronize()
+    for got, want in zip((g1, g2), ref.rdm(C.double().cpu().numpy())):
+        if abs(want).max() > 0:
+            assert rel(got.cpu().numpy(), want) <= TOL[dtype]
+        else:
+            assert got.abs().max() <= TOL[dtype]
