@@ -144,6 +144,7 @@ void free_ctx(cisigma_ctx *c) {
     (void)hipFree(c->d_jpq);
     (void)hipFree(c->bt.blk); (void)hipFree(c->bt.tb); (void)hipFree(c->bt.tr); (void)hipFree(c->bt.tc);
     (void)hipFree(c->d_pblk); (void)hipFree(c->d_blkoff);
+    (void)hipFree(c->plan.d_entries[0]); (void)hipFree(c->plan.d_entries[1]);
     (void)hipFree(c->prog.d_words);
     (void)hipFree(c->d_act_start); (void)hipFree(c->d_act_tiles);
     (void)hipFree(c->go.d_slot); (void)hipFree(c->go.d_coff); (void)hipFree(c->go.d_g32); (void)hipFree(c->go.d_g64);
@@ -595,16 +596,26 @@ int plan_tables(cisigma_ctx *c, std::vector<uint32_t> &exc, std::vector<uint32_t
     return CISIGMA_OK;
 }
 
-// Entries per lane of a plan in equal runs, as cisigma_last_shape reports them (16
-// where no such plan holds the space).
+// Entries per lane of a plan in equal runs, as cisigma_last_shape reports them; 0 where
+// no such plan holds the space.
 int plan_width(const PlanSpec &ps, const PlanTiles &pt) {
     for (int cand : {ps.width(pt.need), 16})
         if (cand >= pt.need && ps.width(cand) == cand && plan_fits(pt, cand)) return cand;
-    return 16;
+    return 0;
+}
+
+// Builds the FP64 encoding of a scatter plan of width ew into P.
+int make_scatter_plan(cisigma_ctx *c, const PlanSpec &ps, const PlanTiles &pt, int ew, cis::ScatterPlan &P) {
+    std::vector<uint32_t> plan[2];
+    plan_emit(ps, pt, ew, plan);
+    HIP_OR_FAIL(c, upload(&P.d_entries[0], plan[0]), "init: scatter plan");
+    P.ntile = ps.ntile;
+    P.ew = ew;
+    return CISIGMA_OK;
 }
 
 // The first compiled program that every tile of the space fits.
-int build_scatter_prog(cisigma_ctx *c, const PlanSpec &ps, const PlanTiles &pt) {
+int build_scatter_prog(cisigma_ctx *c, const PlanTiles &pt, int ew) {
     constexpr int WS = 33, WSP = 36;   // W row strides of the items and of the kernels
     const int rb = (c->npair + 15) / 16;
     cis::ProgLayout L{};
@@ -631,7 +642,7 @@ int build_scatter_prog(cisigma_ctx *c, const PlanSpec &ps, const PlanTiles &pt) 
         HIP_OR_FAIL(c, upload(&c->prog.d_words, words), "init: scatter program");
         c->prog.ntile = int(tiles.size());
         c->prog.prog = g;
-        cis::sigma_ab_owner_shape(c->sp[0].nexc, c->npair, plan_width(ps, pt), c->prog.shape);
+        cis::sigma_ab_owner_shape(c->sp[0].nexc, c->npair, ew ? ew : 16, c->prog.shape);
         break;
     }
     return CISIGMA_OK;
@@ -648,6 +659,8 @@ int build_scatter_plan(cisigma_ctx *c) {
     ps.source = [&](int t, int col) { const int Jb = t * 32 + col; return Jb < B.nstr ? Jb : -1; };
     ps.w_row = [](int k, int l) { return cis::pair_ge(k, l); };
     ps.nvirt = ld;
+    ps.unit[0] = 8;
+    ps.unit[1] = 1;
     const int anexc = c->sp[0].nexc, npair = c->npair;
     ps.width = [=](int need) { return cis::sigma_ab_owner_width(anexc, npair, need); };
     std::vector<uint32_t> exc, str;
@@ -656,7 +669,12 @@ int build_scatter_plan(cisigma_ctx *c) {
     PlanTiles pt;
     rc = plan_items(c, ps, exc, str, pt);
     if (rc) return rc;
-    return build_scatter_prog(c, ps, pt);
+    const int ew = plan_width(ps, pt);
+    if (ew && c->n <= 10) {
+        rc = make_scatter_plan(c, ps, pt, ew, c->plan);
+        if (rc) return rc;
+    }
+    return build_scatter_prog(c, pt, ew);
 }
 
 

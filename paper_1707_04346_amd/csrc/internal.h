@@ -134,8 +134,8 @@ struct BlockTilesDev {
     int ntiles;
 };
 
-// The beta-side scatter of the GAS owner-computes sigma_3 kernel through a sorted
-// list (abx.h): the entry words of every unit's tiles.
+// The beta-side scatter of an owner-computes sigma_3 kernel through a sorted list
+// (abx.h): the entry words of every tile (GAS: of every unit's).
 struct ScatterPlan {
     uint32_t *d_entries[2] = {nullptr, nullptr};  // [FP64, FP32] entry encodings, [ntile][4][ew][64]
     int ntile = 0;
@@ -229,7 +229,8 @@ struct cisigma_ctx {
     double *d_jpq = nullptr;       // [n][n] (pp|qq)
     cis::Workspace ws[2];          // per dtype (0 FP64, 1 FP32)
     cis::BlockTilesDev bt{};       // tiles of the caller-layout blocks
-    cis::ProgPlan prog;            // beta-side scatter of the one-block sigma_3 kernels
+    cis::ScatterPlan plan;         // beta-side scatter of the one-block sigma_3 kernel of small spaces
+    cis::ProgPlan prog;            // beta-side scatter of the other one-block sigma_3 kernels
     // general sigma_3 kernel: per alpha type, the 64-column beta tiles that can
     // change sigma (CSR over alpha types; all tiles for one-block spaces)
     int *d_act_start = nullptr;    // [ntype_a + 1]
@@ -308,6 +309,8 @@ bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *C, void *sigma, h
 bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *C, void *sigma, hipStream_t s, hipError_t *err);
 // whether it is compiled for rb 16-row blocks of pairs and a scatter program
 bool sigma_ab_split_prog(int rb, int prog);
+// its list form for at most 10 orbitals: false without a plan (nothing launched)
+bool launch_sigma_ab_list(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipError_t *err);
 // shape[4] of the owner-computes kernel for anexc excitations, npair pairs and a plan of ew entries per lane
 void sigma_ab_owner_shape(int anexc, int npair, int ew, int *shape);
 // plan width (entries per lane and tile) the owner-computes kernel uses for a

@@ -1,5 +1,6 @@
 // sigma_abx.hip -- the alpha-beta part sigma_3 (Eq. 8) of one-block (CAS) spaces
-// of up to 16 orbitals, in FP64: owner-computes rows (FP32: sigma_abs.hip).
+// of up to 16 orbitals, in FP64: owner-computes rows (FP32: sigma_abs.hip; up to 10
+// orbitals mostly sigma_abl.hip).
 //
 // One workgroup per output alpha string Ia keeps the whole sigma row of Ia in
 // LDS and visits the beta strings in 32-column tiles:
@@ -305,6 +306,7 @@ void sigma_ab_owner_shape(int anexc, int npair, int ew, int *shape) {
 }
 
 bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipError_t *err) {
+    if (launch_sigma_ab_list(ctx, cp, sp, s, err)) return true;
     const ProgPlan &P = ctx->prog;
     if (!P.d_words) return false;
     const auto &A = ctx->sp[0];
