@@ -25,6 +25,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstdio>
+#include <cstring>
 #include <functional>
 #include <type_traits>
 #include <vector>
@@ -513,12 +514,16 @@ __global__ void k_scale_copy(const TI *src, TO *dst, double f, int64_t N) {
 
 // x[idx[i]] = v[i] and out[i] = x[idx[i]]: the P-space entries of a vector
 template <typename T>
-__global__ void k_put_entries(T *x, const int64_t *idx, const double *v, int n) {
+__global__ void k_put_entries(T *x, int64_t N, const int64_t *idx, const double *v, int n) {
+    x += int64_t(blockIdx.y) * N;
+    v += int64_t(blockIdx.y) * n;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) x[idx[i]] = T(v[i]);
 }
 
 template <typename T>
-__global__ void k_get_entries(const T *x, const int64_t *idx, double *out, int n) {
+__global__ void k_get_entries(const T *x, int64_t N, const int64_t *idx, double *out, int n) {
+    x += int64_t(blockIdx.y) * N;
+    out += int64_t(blockIdx.y) * n;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) out[i] = double(x[idx[i]]);
 }
 
@@ -631,8 +636,29 @@ struct Dev {
     hipStream_t s;
     bool quad = false;   // vector length a multiple of 4: the streaming kernels' quad form
     int ncu = 0;         // compute units of the device
-    double *partial = nullptr, *dvec = nullptr, *ybuf = nullptr, *qbuf = nullptr, *pval = nullptr;
+    double *partial = nullptr, *dvec = nullptr, *ybuf = nullptr, *qbuf = nullptr;
     int64_t *pidx = nullptr, *pdet = nullptr;
+    // Pinned host memory, mapped: kernels write small results to hres and read the
+    // P-space values at hps there, and coefficients are staged through hup, so that an
+    // iteration has no copy from or to pageable memory (each of those waits for the
+    // stream and stages its bytes; a small space spent most of its time there)
+    double *hres = nullptr, *hps = nullptr, *hup = nullptr;
+    size_t upcap = 0, uppos = 0;   // elements of hup; first one no copy in flight reads
+    hipError_t sync() {
+        uppos = 0;
+        return hipStreamSynchronize(s);
+    }
+    hipError_t upload(double *dst, const double *src, size_t n) {
+        if (uppos + n > upcap) {
+            const hipError_t e = sync();
+            if (e != hipSuccess) return e;
+        }
+        if (n > upcap) return hipErrorInvalidValue;
+        std::memcpy(hup + uppos, src, n * sizeof(double));
+        const hipError_t e = hipMemcpyAsync(dst, hup + uppos, n * sizeof(double), hipMemcpyHostToDevice, s);
+        uppos += n;
+        return e;
+    }
     int grid(int64_t N) const {
         int64_t g = (N + 255) / 256;
         return int(g < kRedBlocks ? (g > 0 ? g : 1) : kRedBlocks);
@@ -658,10 +684,11 @@ template <typename TX, typename TY>
 hipError_t dots(Dev &d, const TX *X, int64_t sx, int nx, const TY *y, int64_t N, double *host_out) {
     int g = d.grid(N);
     hipLaunchKernelGGL((k_dots<TX, TY>), dim3(g), dim3(256), 0, d.s, X, sx, nx, y, N, d.partial);
-    hipLaunchKernelGGL(k_reduce_partials, dim3(nx), dim3(64), 0, d.s, d.partial, g, nx, d.dvec);
-    hipError_t e = hipMemcpyAsync(host_out, d.dvec, size_t(nx) * sizeof(double), hipMemcpyDeviceToHost, d.s);
-    if (e != hipSuccess) return e;
-    return hipStreamSynchronize(d.s);
+    hipLaunchKernelGGL(k_reduce_partials, dim3(nx), dim3(64), 0, d.s, d.partial, g, nx, d.hres);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = d.sync();
+    if (e == hipSuccess) std::memcpy(host_out, d.hres, size_t(nx) * sizeof(double));
+    return e;
 }
 
 // out[j * nx + i] = X_i . Y_j for j < ny (blocks of kMultiY), on the host
@@ -683,12 +710,12 @@ hipError_t dots_multi(Dev &d, const TX *X, int64_t sx, int nx, const TY *Y, int6
             hipLaunchKernelGGL((k_dots_multi<TX, TY, false>), dim3(g), dim3(256), 0, d.s, X, sx, nx,
                                Y + int64_t(j0) * sy, sy, nyc, N, d.partial);
         hipLaunchKernelGGL(k_reduce_partials, dim3(nx * nyc), dim3(64), 0, d.s, d.partial, g, nx * nyc,
-                           d.dvec);
-        hipError_t e = hipMemcpyAsync(host_out + size_t(j0) * nx, d.dvec, size_t(nx) * nyc * sizeof(double),
-                                      hipMemcpyDeviceToHost, d.s);
-        if (e != hipSuccess) return e;
+                           d.hres + size_t(j0) * nx);
     }
-    return hipStreamSynchronize(d.s);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = d.sync();
+    if (e == hipSuccess) std::memcpy(host_out, d.hres, size_t(nx) * ny * sizeof(double));
+    return e;
 }
 
 // T_j -= sum_i c[j * nx + i] X_i for j < ny (host coefficients)
@@ -699,8 +726,7 @@ hipError_t subtract_multi(Dev &d, const T *X, int64_t sx, int nx, const double *
     const int g = d.grid(N);
     for (int j0 = 0; j0 < ny; j0 += kMultiY) {
         const int nyc = std::min(kMultiY, ny - j0);
-        hipError_t e = hipMemcpyAsync(d.dvec, host_c + size_t(j0) * nx, size_t(nx) * nyc * sizeof(double),
-                                      hipMemcpyHostToDevice, d.s);
+        hipError_t e = d.upload(d.dvec, host_c + size_t(j0) * nx, size_t(nx) * nyc);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((k_subtract_multi<T>), dim3(g), dim3(256), 0, d.s, X, sx, nx, d.dvec, nyc,
                            Tv + int64_t(j0) * st, st, N);
@@ -717,7 +743,7 @@ hipError_t subtract_gram(Dev &d, const T *X, int64_t sx, int nx, const double *h
     const int g = d.grid(N);
     const int nv = ny + ny * (ny + 1) / 2;
     hipError_t e = hipSuccess;
-    if (nx > 0) e = hipMemcpyAsync(d.dvec, host_c, size_t(nx) * ny * sizeof(double), hipMemcpyHostToDevice, d.s);
+    if (nx > 0) e = d.upload(d.dvec, host_c, size_t(nx) * ny);
     if (e != hipSuccess) return e;
 #define CIS_SUBG(NY, Q)                                                                                     \
     hipLaunchKernelGGL((k_subtract_gram<T, NY, Q>), dim3(g), dim3(256), 0, d.s, X, sx, nx, d.dvec, Tv, st, N, \
@@ -736,11 +762,11 @@ hipError_t subtract_gram(Dev &d, const T *X, int64_t sx, int nx, const double *h
         default: return hipErrorInvalidValue;
     }
 #undef CIS_SUBG
-    hipLaunchKernelGGL(k_reduce_partials, dim3(nv), dim3(64), 0, d.s, d.partial, g, nv, d.dvec);
-    std::vector<double> out(nv);
-    e = hipMemcpyAsync(out.data(), d.dvec, size_t(nv) * sizeof(double), hipMemcpyDeviceToHost, d.s);
-    if (e == hipSuccess) e = hipStreamSynchronize(d.s);
+    hipLaunchKernelGGL(k_reduce_partials, dim3(nv), dim3(64), 0, d.s, d.partial, g, nv, d.hres);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = d.sync();
     if (e != hipSuccess) return e;
+    const double *out = d.hres;
     int q = ny;
     for (int j = 0; j < ny; ++j) {
         pre[j] = out[j];
@@ -755,7 +781,7 @@ hipError_t combine_new(Dev &d, const T *Tv, int64_t st, int ny, const double *ho
                        int64_t N) {
     if (nd == 0) return hipSuccess;
     const int g = d.grid(N);
-    hipError_t e = hipMemcpyAsync(d.dvec, host_w, size_t(nd) * ny * sizeof(double), hipMemcpyHostToDevice, d.s);
+    hipError_t e = d.upload(d.dvec, host_w, size_t(nd) * ny);
     if (e != hipSuccess) return e;
 #define CIS_COMB(NY, Q) \
     hipLaunchKernelGGL((k_combine_new<T, NY, Q>), dim3(g), dim3(256), 0, d.s, Tv, st, d.dvec, nd, D, sd, N)
@@ -851,7 +877,11 @@ int run(cisigma_ctx *ctx, int nroots, double tol, double *energies, void *vecs, 
         (void)hipFree(B); (void)hipFree(S); (void)hipFree(SX); (void)hipFree(TB); (void)hipFree(X64);
         (void)hipFree(hd); (void)hipFree(sig64);
         (void)hipFree(d.partial); (void)hipFree(d.dvec); (void)hipFree(d.pidx); (void)hipFree(d.ybuf);
-        (void)hipFree(d.qbuf); (void)hipFree(d.pval); (void)hipFree(d.pdet);
+        (void)hipFree(d.qbuf); (void)hipFree(d.pdet);
+        if (d.hres) {
+            (void)hipStreamSynchronize(d.s);   // (an early return: copies and kernels may still use it)
+            (void)hipHostFree(d.hres);
+        }
     };
     struct Guard { std::function<void()> f; ~Guard() { f(); } } guard{cleanup};
     DV_TRY(hipMalloc(&B, size_t(max_space) * N * es));
@@ -877,8 +907,19 @@ int run(cisigma_ctx *ctx, int nroots, double tol, double *energies, void *vecs, 
     // the exact H over them, diagonalised: its lowest eigenvectors are the guess,
     // and on those determinants the correction is (theta - H_PP)^-1 r_P
     const int np = (par == 0 && ctx->pspace >= nroots) ? int(std::min<int64_t>(ctx->pspace, dim)) : 0;
+    {
+        // results: dot products of a full basis with every root, or the residual
+        // partials of a pass over the roots; coefficients of a few uploads
+        const size_t res = std::max(size_t(max_space + 1) * std::max(nroots, kMultiY), size_t(kRitzRoots) * kRedBlocks);
+        const size_t ps = size_t(np) * nroots;
+        d.upcap = 2 * std::max(size_t(512) * kMultiY, std::max(size_t(kRitzRoots) * (512 + 1), size_t(kThick) * 512));
+        DV_TRY(hipHostMalloc(reinterpret_cast<void **>(&d.hres), (res + ps + d.upcap) * sizeof(double),
+                             hipHostMallocMapped | hipHostMallocCoherent));
+        d.hps = d.hres + res;
+        d.hup = d.hps + ps;
+    }
     std::vector<int64_t> pdet;
-    std::vector<double> pdiag, pw, pU;
+    std::vector<double> pdiag, pw, pU, pUt;   // pUt: pU transposed
     // (1) guess: unit vectors on the lowest diagonal elements (ties: lowest index),
     // or the lowest eigenvectors of the P-space block
     {
@@ -995,19 +1036,17 @@ int run(cisigma_ctx *ctx, int nroots, double tol, double *energies, void *vecs, 
                 for (int j = 0; j <= i; ++j)
                     hpp[size_t(i) * np + j] = hpp[size_t(j) * np + i] = hmat_element(ctx, pa[i], pb[i], pa[j], pb[j]);
             sym_eig(hpp, np, pw, pU);
+            pUt.resize(pU.size());
+            for (int i = 0; i < np; ++i)
+                for (int k = 0; k < np; ++k) pUt[size_t(k) * np + i] = pU[size_t(i) * np + k];
             DV_TRY(hipMalloc(&d.pdet, size_t(np) * sizeof(int64_t)));
-            DV_TRY(hipMalloc(&d.pval, size_t(np) * nroots * sizeof(double)));
             DV_TRY(hipMemcpy(d.pdet, pdet.data(), size_t(np) * sizeof(int64_t), hipMemcpyHostToDevice));
-            std::vector<double> u(size_t(np) * nroots);
             for (int r = 0; r < nroots; ++r)
-                for (int i = 0; i < np; ++i) u[size_t(r) * np + i] = pU[size_t(i) * np + r];
-            DV_TRY(hipMemcpy(d.pval, u.data(), u.size() * sizeof(double), hipMemcpyHostToDevice));
-            const int pg = std::min(64, (np + 255) / 256);
-            for (int r = 0; r < nroots; ++r) {
+                for (int i = 0; i < np; ++i) d.hps[size_t(r) * np + i] = pU[size_t(i) * np + r];
+            for (int r = 0; r < nroots; ++r)
                 hipLaunchKernelGGL(k_unit<T>, dim3(g), dim3(256), 0, d.s, B + int64_t(r) * N, N, int64_t(-1));
-                hipLaunchKernelGGL(k_put_entries<T>, dim3(pg), dim3(256), 0, d.s, B + int64_t(r) * N, d.pdet,
-                                   d.pval + size_t(r) * np, np);
-            }
+            hipLaunchKernelGGL(k_put_entries<T>, dim3(unsigned(std::min(64, (np + 255) / 256)), unsigned(nroots)), dim3(256),
+                               0, d.s, B, N, d.pdet, d.hps, np);
             DV_TRY(hipGetLastError());
         }
     }
@@ -1015,37 +1054,33 @@ int run(cisigma_ctx *ctx, int nroots, double tol, double *energies, void *vecs, 
     // t = r / (theta - H_II) there; r_P is recovered and solved exactly
     auto pspace_correct = [&](const std::vector<double> &theta) -> hipError_t {
         if (np == 0) return hipSuccess;
-        const int pg = std::min(64, (np + 255) / 256);
-        for (int r = 0; r < nroots; ++r)
-            hipLaunchKernelGGL(k_get_entries<T>, dim3(pg), dim3(256), 0, d.s, TB + int64_t(r) * N, d.pdet,
-                               d.pval + size_t(r) * np, np);
-        std::vector<double> t(size_t(np) * nroots), y(np);
-        hipError_t e = hipMemcpyAsync(t.data(), d.pval, t.size() * sizeof(double), hipMemcpyDeviceToHost, d.s);
-        if (e == hipSuccess) e = hipStreamSynchronize(d.s);
+        const dim3 pg(unsigned(std::min(64, (np + 255) / 256)), unsigned(nroots));
+        hipLaunchKernelGGL(k_get_entries<T>, pg, dim3(256), 0, d.s, TB, N, d.pdet, d.hps, np);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = d.sync();
         if (e != hipSuccess) return e;
         auto clamp = [](double x) { return std::fabs(x) < 1e-8 ? (x < 0 ? -1e-8 : 1e-8) : x; };
+        // y = U^T r, then U (y / (theta - w)): rows of U and of its transpose added up
+        // (each sum's terms in ascending order)
+        auto add_rows = [&](const double *__restrict__ rows, const double *__restrict__ x, double *__restrict__ sum) {
+            std::fill(sum, sum + np, 0.0);
+            for (int i = 0; i < np; ++i, rows += np) {
+                const double xi = x[i];
+                for (int k = 0; k < np; ++k) sum[k] += rows[k] * xi;
+            }
+        };
+        std::vector<double> t(np), y(np);
         for (int r = 0; r < nroots; ++r) {
-            double *tr = t.data() + size_t(r) * np;
-            for (int i = 0; i < np; ++i) tr[i] *= clamp(theta[r] - pdiag[i]);          // r_P
-            for (int k = 0; k < np; ++k) {
-                double acc = 0;
-                for (int i = 0; i < np; ++i) acc += pU[size_t(i) * np + k] * tr[i];
-                y[k] = acc / clamp(theta[r] - pw[k]);
-            }
-            for (int i = 0; i < np; ++i) {
-                double acc = 0;
-                for (int k = 0; k < np; ++k) acc += pU[size_t(i) * np + k] * y[k];
-                tr[i] = acc;
-            }
+            double *tr = d.hps + size_t(r) * np;
+            for (int i = 0; i < np; ++i) t[i] = tr[i] * clamp(theta[r] - pdiag[i]);    // r_P
+            add_rows(pU.data(), t.data(), y.data());
+            for (int k = 0; k < np; ++k) y[k] /= clamp(theta[r] - pw[k]);
+            add_rows(pUt.data(), y.data(), t.data());
+            std::copy(t.begin(), t.end(), tr);
         }
-        e = hipMemcpyAsync(d.pval, t.data(), t.size() * sizeof(double), hipMemcpyHostToDevice, d.s);
-        if (e != hipSuccess) return e;
-        for (int r = 0; r < nroots; ++r)
-            hipLaunchKernelGGL(k_put_entries<T>, dim3(pg), dim3(256), 0, d.s, TB + int64_t(r) * N, d.pdet,
-                               d.pval + size_t(r) * np, np);
-        e = hipGetLastError();
-        if (e == hipSuccess) e = hipStreamSynchronize(d.s);   // t is host memory
-        return e;
+        // (the next write to these values comes after a later kernel's end)
+        hipLaunchKernelGGL(k_put_entries<T>, pg, dim3(256), 0, d.s, TB, N, d.pdet, d.hps, np);
+        return hipGetLastError();
     };
     std::vector<double> G(size_t(max_space) * max_space, 0.0);
     std::vector<double> theta(nroots, 0.0), theta_old(nroots, INFINITY), rnorm(nroots, 0.0);
@@ -1095,7 +1130,7 @@ int run(cisigma_ctx *ctx, int nroots, double tol, double *energies, void *vecs, 
             for (int r = 0; r < nr; ++r)
                 for (int i = 0; i < mm; ++i) yy[size_t(r) * mm + i] = Yv[size_t(i) * mm + r0 + r];
             for (int r = 0; r < nr; ++r) yy[size_t(nr) * mm + r] = theta[r0 + r];
-            hipError_t e = hipMemcpyAsync(d.ybuf, yy.data(), yy.size() * sizeof(double), hipMemcpyHostToDevice, d.s);
+            hipError_t e = d.upload(d.ybuf, yy.data(), yy.size());
             if (e != hipSuccess) return e;
 #define CIS_RITZ1(RR, WXX, QQ)                                                                                  \
     hipLaunchKernelGGL((k_ritz_multi<T, RR, WXX, QQ>), dim3(g), dim3(256), 0, d.s, B, S, N, mm, nr, d.ybuf,         \
@@ -1122,9 +1157,9 @@ int run(cisigma_ctx *ctx, int nroots, double tol, double *energies, void *vecs, 
 #undef CIS_RITZ
 #undef CIS_RITZ1
             if (norms) {
-                std::vector<double> part(size_t(nr) * g);
-                e = hipMemcpyAsync(part.data(), d.partial, part.size() * sizeof(double), hipMemcpyDeviceToHost, d.s);
-                if (e == hipSuccess) e = hipStreamSynchronize(d.s);
+                const double *part = d.hres;
+                e = hipMemcpyAsync(d.hres, d.partial, size_t(nr) * g * sizeof(double), hipMemcpyDeviceToHost, d.s);
+                if (e == hipSuccess) e = d.sync();
                 if (e != hipSuccess) return e;
                 for (int r = 0; r < nr; ++r) {
                     double ss = 0;
@@ -1283,7 +1318,7 @@ int run(cisigma_ctx *ctx, int nroots, double tol, double *energies, void *vecs, 
                 ++k;
             }
             if (k > nroots) {
-                DV_TRY(hipMemcpyAsync(d.qbuf, Q.data(), size_t(k) * m * sizeof(double), hipMemcpyHostToDevice, d.s));
+                DV_TRY(d.upload(d.qbuf, Q.data(), size_t(k) * m));
                 launch_combine<T>(B, N, m, d.qbuf, k, N, g, d.s, d.quad);
                 launch_combine<T>(S, N, m, d.qbuf, k, N, g, d.s, d.quad);
                 DV_TRY(hipGetLastError());
@@ -1416,7 +1451,7 @@ int run(cisigma_ctx *ctx, int nroots, double tol, double *energies, void *vecs, 
                 T *t = B + int64_t(m + j) * N;
                 for (int pass = 0; pass < 2 && nnew > 0; ++pass) {
                     DV_TRY(dots(d, B + int64_t(m) * N, N, nnew, t, N, col.data()));
-                    DV_TRY(hipMemcpyAsync(d.dvec, col.data(), nnew * sizeof(double), hipMemcpyHostToDevice, d.s));
+                    DV_TRY(d.upload(d.dvec, col.data(), size_t(nnew)));
                     hipLaunchKernelGGL((k_subtract<T>), dim3(g), dim3(256), 0, d.s, B + int64_t(m) * N, N, nnew, d.dvec, t, N);
                 }
                 double tt;
