@@ -26,9 +26,17 @@ __device__ __forceinline__ void lds_st(uint32_t off, T v) {
     *reinterpret_cast<__attribute__((address_space(3))) T *>(off) = v;
 }
 
-// A lane's words of a tile.  The offsets in them count four-byte elements; FP64
-// doubles them.
-template <typename T, int PG>
+// first field of round r
+template <int PG>
+constexpr int prog_field(int r) {
+    int x = kProgs[PG].np * kProgs[PG].ps;
+    for (int i = 0; i < r; ++i) x += 1 + kProgs[PG].r[i];
+    return x;
+}
+
+// A lane's words of a tile for the rounds R0 .. R1 - 1 and the partial round before
+// them.  The offsets in them count four-byte elements; FP64 doubles them.
+template <typename T, int PG, int R0 = 0, int R1 = kProgs[PG].nr>
 struct ProgWords {
     static constexpr int NW = kProgs[PG].words();
     uint32_t q[NW];
@@ -37,7 +45,9 @@ struct ProgWords {
     __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff, int tile) {
         const uint32_t so = uint32_t(tile) * uint32_t(kProgWaves * NW * 64 * 4);
 #pragma unroll
-        for (int i = 0; i < NW; ++i) q[i] = buffer_ld_u32(r, voff + i * 256u, so);
+        for (int i = 0; i < NW; ++i)
+            if (2 * i < prog_field<PG>(0) || (2 * i + 1 >= prog_field<PG>(R0) && 2 * i < prog_field<PG>(R1)))
+                q[i] = buffer_ld_u32(r, voff + i * 256u, so);
     }
     template <int I>
     __device__ __forceinline__ uint32_t ref() const {
@@ -67,52 +77,57 @@ struct ProgWords {
 };
 
 // N references from field I on: the loads, then the sum
-template <int I, int N, typename T, int PG, int V>
-__device__ __forceinline__ void prog_load(const ProgWords<T, PG> &w, T (&v)[V]) {
+template <int I, int N, typename W, typename T, int V>
+__device__ __forceinline__ void prog_load(const W &w, T (&v)[V]) {
     if constexpr (N > 0) {
         v[I] = lds_ld<T>(w.template ref<I>());
         prog_load<I + 1, N - 1>(w, v);
     }
 }
-template <int I, int N, typename T, int PG, int V>
-__device__ __forceinline__ T prog_sum(const ProgWords<T, PG> &w, const T (&v)[V]) {
+template <int I, int N, typename W, typename T, int V>
+__device__ __forceinline__ T prog_sum(const W &w, const T (&v)[V]) {
     if constexpr (N == 1) return w.template sign<I>(v[I]);
     else return prog_sum<I, N / 2>(w, v) + prog_sum<I + N / 2, N - N / 2>(w, v);
 }
-template <int R, int F, typename T, int PG, int V>
-__device__ __forceinline__ void prog_rounds_load(const ProgWords<T, PG> &w, T (&v)[V], uint32_t (&slot)[6]) {
-    if constexpr (R < kProgs[PG].nr) {
+template <int PG, int R, int END, typename W, typename T, int V>
+__device__ __forceinline__ void prog_rounds_load(const W &w, T (&v)[V], uint32_t (&slot)[6]) {
+    if constexpr (R < END) {
+        constexpr int F = prog_field<PG>(R);
         prog_load<F + 1, kProgs[PG].r[R]>(w, v);
         slot[R] = w.template slot<F>();
-        prog_rounds_load<R + 1, F + 1 + kProgs[PG].r[R]>(w, v, slot);
+        prog_rounds_load<PG, R + 1, END>(w, v, slot);
     }
 }
-template <int R, int F, typename T, int PG, int V>
-__device__ __forceinline__ void prog_rounds_sum(const ProgWords<T, PG> &w, const T (&v)[V], T (&sum)[6]) {
-    if constexpr (R < kProgs[PG].nr) {
-        sum[R] = prog_sum<F + 1, kProgs[PG].r[R]>(w, v);
-        prog_rounds_sum<R + 1, F + 1 + kProgs[PG].r[R]>(w, v, sum);
+template <int PG, int R, int END, typename W, typename T, int V>
+__device__ __forceinline__ void prog_rounds_sum(const W &w, const T (&v)[V], T (&sum)[6]) {
+    if constexpr (R < END) {
+        sum[R] = prog_sum<prog_field<PG>(R) + 1, kProgs[PG].r[R]>(w, v);
+        prog_rounds_sum<PG, R + 1, END>(w, v, sum);
     }
 }
 
-// Runs a tile's words: MINE the lane's scratch element (byte offset SC + mine),
-// SIG the byte offset of the sigma row.  The loads go out together, before the sums.
-template <uint32_t SC, uint32_t SIG, typename T, int PG>
-__device__ __forceinline__ void prog_run(const ProgWords<T, PG> &w, uint32_t mine) {
+// Runs the rounds of a tile's words: SC + mine the byte offset of the lane's scratch
+// element, SIG that of the sigma row.  The loads go out together, before the sums.
+// (Two waves that share a quarter, each with its own rounds, both write the same partial
+// sums, each before it reads them.)
+template <uint32_t SC, uint32_t SIG, typename T, int PG, int R0, int R1>
+__device__ __forceinline__ void prog_run(const ProgWords<T, PG, R0, R1> &w, uint32_t mine) {
     static_assert(kProgs[PG].np == 1, "one partial round");
-    constexpr int PS = kProgs[PG].ps, NR = kProgs[PG].nr;
-    T v[kProgs[PG].fields()], sum[6], old[6];
-    uint32_t slot[6];
-    prog_load<0, PS>(w, v);
-    __builtin_amdgcn_sched_barrier(0);
-    lds_st<T>(mine + SC, prog_sum<0, PS>(w, v));
-    prog_rounds_load<0, PS>(w, v, slot);
+    if constexpr (R0 < R1) {
+        constexpr int PS = kProgs[PG].ps;
+        T v[kProgs[PG].fields()], sum[6], old[6];
+        uint32_t slot[6];
+        prog_load<0, PS>(w, v);
+        __builtin_amdgcn_sched_barrier(0);
+        lds_st<T>(mine + SC, prog_sum<0, PS>(w, v));
+        prog_rounds_load<PG, R0, R1>(w, v, slot);
 #pragma unroll
-    for (int i = 0; i < NR; ++i) old[i] = lds_ld<T>(slot[i] + SIG);
-    __builtin_amdgcn_sched_barrier(0);
-    prog_rounds_sum<0, PS>(w, v, sum);
+        for (int i = R0; i < R1; ++i) old[i] = lds_ld<T>(slot[i] + SIG);
+        __builtin_amdgcn_sched_barrier(0);
+        prog_rounds_sum<PG, R0, R1>(w, v, sum);
 #pragma unroll
-    for (int i = 0; i < NR; ++i) lds_st<T>(slot[i] + SIG, old[i] + sum[i]);
+        for (int i = R0; i < R1; ++i) lds_st<T>(slot[i] + SIG, old[i] + sum[i]);
+    }
 }
 
 }  // namespace cis

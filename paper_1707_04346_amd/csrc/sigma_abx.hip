@@ -26,16 +26,22 @@
 // four quads are one 16x16x4 instruction per k step, a single quad one 4x4x4
 // (four blocks, all columns of the half tile: the same operand registers of C, a
 // quarter of the time).  A pair of waves w, w + 4 shares a SIMD (wave w is placed on
-// SIMD w mod 4); every SIMD gets half the quads of one 16-column half, the first wave
-// whole 16-row blocks, the second the rest and a quarter of the tile's scatter.  At
-// CAS(16,16) that is 4.25 blocks per SIMD and k step where whole 16-row blocks on three
-// SIMDs, the fourth scattering alone, took 6: 54.8 instead of 64.1 ms; a whole
-// sigma of CAS(12,12) 285 instead of 472 us (there two workgroups share a compute
-// unit).  The products alone take 42.6 ms (their instructions 39), the stores of W 1.7; the scatter's 100
-// vector instructions a wave and tile cost ~12 cycles each, as every break in a SIMD's
-// run of matrix instructions costs it ~12 cycles.  The scattering waves' own barrier
-// ("consumed") meets the others half way through their products, so that a wave stores
-// its W as soon as it is done (with both barriers at the end 58.0 ms).
+// SIMD w mod 4); every SIMD gets half the quads of one 16-column half.  At CAS(16,16)
+// that is 4.25 blocks per SIMD and k step where whole 16-row blocks on three SIMDs, the
+// fourth scattering alone, took 6.
+//
+// A vector instruction between two matrix ones costs their SIMD ~12 cycles besides its
+// own.  From 13 orbitals on scatter and products are therefore kept apart: per tile the
+// eight waves scatter, meet, multiply the next tile's rows, and store each its W as soon
+// as it is done.  CAS(16,16): 51.5 ms; with four waves scattering beside the products of
+// the other four 54.2, with the stores between two barriers at the end 58.0; 15 orbitals
+// 11.7 against 12.3, 14 2.94 both, 13 0.57 against 0.67.  Up to 12 orbitals two workgroups
+// share a compute unit either way, the one's products fill the other's waits, and the
+// fewer partial sums of four scattering waves count: CAS(12,12) 286 us a sigma, 291 with
+// all eight.
+//
+// CAS(16,16) sigma_3 64.1 -> 51.5 ms (the products alone 42.6, their instructions 39, the
+// stores of W 1.7), a whole sigma of CAS(12,12) 472 -> 286 us.
 #include "internal.h"
 #include "mfma.h"
 #include "bufio.h"
@@ -62,7 +68,7 @@ struct AbxArgs {
 
 // Quads of wave group g (waves 2g and 2g + 1: the two column halves) of q in all.
 // Groups g and g + 2 share SIMDs: half the quads each pair, whole 16-row blocks to
-// the first (a little more than half of them: the second also scatters).
+// the first (a little more than half of them).
 constexpr int group_quads(int q, int g) {
     const int s = (g & 1) ? q / 2 : (q + 1) / 2;
     const int a = 4 * ((s + 9) / 8), b = 4 * (s / 4);
@@ -82,8 +88,9 @@ __device__ __forceinline__ double self_coef(const AbxArgs &p, uint32_t xa, int m
 }
 
 // One wave: KS k steps of four gathered rows, NQ quads of W rows from row m0 on,
-// column half cb; scatter quarter sw (< 0: none).
-template <int KS, int NQ, int RB, int PG, bool SELF, bool SCAT>
+// column half cb; rounds R0 .. R1 - 1 of scatter quarter sw.  A wave without rounds
+// meets the scattering ones ("W of this tile consumed") half way through its products.
+template <int KS, int NQ, int RB, int PG, bool SELF, int R0, int R1>
 __device__ __forceinline__ void abx_body(const AbxArgs &p, int Ia, int cb, int m0, int sw, int lane) {
     constexpr int NB = NQ / 4, NS = NQ % 4, NF = NB + NS > 0 ? NB + NS : 1;   // whole blocks, single quads, fragments
     constexpr uint32_t SC = 16 * RB * kWS * 8u, SIG = SC + kProgWaves * 64 * 8u;
@@ -149,8 +156,7 @@ __device__ __forceinline__ void abx_body(const AbxArgs &p, int Ia, int cb, int m
     doublex4 acc[NB > 0 ? NB : 1];
     double accq[NS > 0 ? NS : 1];
     // W of the rows held in b; as each k step is consumed, b[t] is reloaded with the
-    // rows of tile `next`, so the loads stay in flight for a whole tile.  MEET: the
-    // barrier at which the scattering waves are done with the last W, half way.
+    // rows of tile `next`, so the loads stay in flight for a whole tile
     auto products = [&](int next, bool meet) {
         const uint32_t so = uint32_t(next) * (kNT * 8u);
         if constexpr (SELF) {
@@ -185,33 +191,32 @@ __device__ __forceinline__ void abx_body(const AbxArgs &p, int Ia, int cb, int m
 #pragma unroll
         for (int f = 0; f < NS; ++f) lds_st<double>(o + uint32_t((16 * NB + 4 * f) * kWS) * 8u, accq[f]);
     };
-    // this wave's quarter of a tile's groups: the words, then their sums
-    ProgWords<double, PG> pw;
+    // this wave's part of a tile's groups: the words, then their sums
+    ProgWords<double, PG, R0, R1> pw;
     const uint32_t pl = uint32_t(sw * pw.NW * 64 + lane) * 4u, mine = uint32_t(sw * 64 + lane) * 8u;
-    auto scatter = [&](int next) {
-        if constexpr (SCAT) {
-            __builtin_amdgcn_s_setprio(3);
-            prog_run<SC, SIG>(pw, mine);
-            pw.load(pr, pl, next);
-            __builtin_amdgcn_s_setprio(0);
-        }
-    };
 #pragma unroll
     for (int t = 0; t < KS; ++t) buffer_ld(b[t], cr, boff[t], 0u);
     if constexpr (!SELF) buffer_ld(cI, cr, boffI, 0u);
-    if constexpr (SCAT) pw.load(pr, pl, 0);
+    if constexpr (R0 < R1) pw.load(pr, pl, 0);
     products(ntile > 1 ? 1 : 0, false);
     lds_barrier();                       // the sigma row and the zeros of W's pad columns are in LDS
     store_w();
     lds_barrier();                       // W of tile 0 ready
     for (int tile = 0; tile + 1 < ntile; ++tile) {
-        scatter(tile + 1);
-        if constexpr (SCAT) lds_barrier();   // W of this tile consumed
-        products(tile + 2 < ntile ? tile + 2 : ntile - 1, !SCAT);
+        if constexpr (R0 < R1) {
+            // beside the products of other waves: first (CAS(12,12) 287 us, without 291)
+            constexpr bool BESIDE = R0 == 0 && R1 == kProgs[PG].nr;
+            if constexpr (BESIDE) __builtin_amdgcn_s_setprio(3);
+            prog_run<SC, SIG>(pw, mine);
+            pw.load(pr, pl, tile + 1);
+            if constexpr (BESIDE) __builtin_amdgcn_s_setprio(0);
+            lds_barrier();               // W of this tile consumed
+        }
+        products(tile + 2 < ntile ? tile + 2 : ntile - 1, R0 == R1);
         store_w();
         lds_barrier();                   // W of the next tile ready
     }
-    scatter(ntile - 1);
+    prog_run<SC, SIG>(pw, mine);
 }
 
 // KS: k steps (4*KS >= excitations, plus one with SELF); Q: quads of W rows (4*Q >=
@@ -228,10 +233,15 @@ __global__ __launch_bounds__(512, 2) void k_sigma_ab_x(AbxArgs p) {
         *reinterpret_cast<double2_t *>(sig + c) = *reinterpret_cast<const double2_t *>(row + c);
     for (int r = tid; r < 16 * RB; r += 512) W[r * kWS + kNT] = 0.0;   // pad column: unused references read it
     static_assert(group_quad0(Q, 3) + group_quads(Q, 3) == Q && 4 * Q <= 16 * RB, "every quad has a wave");
-    if (g == 0) abx_body<KS, group_quads(Q, 0), RB, PG, SELF, false>(p, Ia, cb, 0, 0, lane);
-    else if (g == 1) abx_body<KS, group_quads(Q, 1), RB, PG, SELF, false>(p, Ia, cb, 4 * group_quad0(Q, 1), 0, lane);
-    else if (g == 2) abx_body<KS, group_quads(Q, 2), RB, PG, SELF, true>(p, Ia, cb, 4 * group_quad0(Q, 2), wave - 4, lane);
-    else abx_body<KS, group_quads(Q, 3), RB, PG, SELF, true>(p, Ia, cb, 4 * group_quad0(Q, 3), wave - 4, lane);
+    constexpr int NR = kProgs[PG].nr;
+    const int sw = wave & 3;
+    // all waves scatter, w and w + 4 the first round and the others of a quarter, or
+    // waves 4 to 7 do, beside the products of the others (see above)
+    constexpr int LO = RB > 5 ? 1 : 0;
+    if (g == 0) abx_body<KS, group_quads(Q, 0), RB, PG, SELF, 0, LO>(p, Ia, cb, 0, sw, lane);
+    else if (g == 1) abx_body<KS, group_quads(Q, 1), RB, PG, SELF, 0, LO>(p, Ia, cb, 4 * group_quad0(Q, 1), sw, lane);
+    else if (g == 2) abx_body<KS, group_quads(Q, 2), RB, PG, SELF, LO, NR>(p, Ia, cb, 4 * group_quad0(Q, 2), sw, lane);
+    else abx_body<KS, group_quads(Q, 3), RB, PG, SELF, LO, NR>(p, Ia, cb, 4 * group_quad0(Q, 3), sw, lane);
     __syncthreads();
     for (int c = tid * 2; c < p.ld; c += 1024)
         *reinterpret_cast<double2_t *>(row + c) = *reinterpret_cast<const double2_t *>(sig + c);
