@@ -335,7 +335,7 @@ def stored_same_spin_bytes():
     their column chunks, changed after the counters were taken."""
     import hashlib
     csrc = os.path.join(ROOT, "paper_1707_04346_amd", "csrc")
-    prof = os.path.join(ROOT, "profiles", "k_sigma_ab_x_cas16_fp32_traffic.txt")
+    prof = os.path.join(ROOT, "profiles", "k_sigma_ab_s_cas16_fp32_traffic.txt")
     if not os.path.exists(prof):
         return None
     sha = hashlib.sha256(b"".join(open(os.path.join(csrc, f), "rb").read() for f in ("sigma_ss.hip", "bufio.h", "api.hip"))).hexdigest()
