@@ -31,6 +31,7 @@
 namespace cis {
 namespace {
 
+constexpr int kRdmSlots = 20;   // block pairs per wave of the FP64 form: ceil(153 / 8) for 17 row blocks
 constexpr int kRdmMaxBlocks = 17;
 
 template <typename T>
@@ -42,22 +43,235 @@ struct RdmArgs {
     int n, Na, Nb, ld, anexc, bnexc, nb, npb;
 };
 
-// SLOTS: at least the block pairs per wave; TILES: tile buffers (2, or 1 where the LDS
-// holds no more).
+// The FP64 form.
+template <typename T, int NT>
+__global__ __launch_bounds__(512, 1) void k_rdm(RdmArgs<T> p) {
+    using M = Mfma<T>;
+    using acc_t = typename M::acc_t;
+    // D is stored with the columns of a tile permuted so that the k steps a lane
+    // feeds to the matrix cores are contiguous: column c sits at
+    // (c % 4) * KT + c / 4, and one lane's operand for all KT k steps is KT
+    // consecutive elements (16-byte loads).  Rows are padded by 16 bytes.
+    constexpr int KT = NT / 4;                             // k steps per tile
+    constexpr int VE = 16 / int(sizeof(T));                // elements per 16-byte load
+    constexpr int DS = NT + VE;                            // D row stride (elements)
+    using V = typename M::vec_t;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    T *D = reinterpret_cast<T *>(smem_raw);                // [16 nb][DS]
+    T *row = D + 16 * p.nb * DS;                           // [ld]: C(K_a, .)
+    // what fills row r of D for this K_a: rowJ >= 0: alpha excitation J_a with
+    // sign rowS; -1: zero; -2: C(K) itself; -3: diagonal row (k, k), rowS = k + 256 n^a_k
+    int *rowJ = reinterpret_cast<int *>(row + p.ld);       // [16 nb]
+    int *rowS = rowJ + 16 * p.nb;                          // [16 nb]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = p.n, n2 = n * n, MR = 16 * p.nb;
+    constexpr int RG = 512 / NT;                           // threads per tile column
+    constexpr int KA = (64 + RG - 1) / RG;                 // single excitations per string <= 8 * 8 (n <= 16)
+    constexpr int KB = KA;
+    const int c = tid % NT, rg = tid / NT;
+    const int cperm = (c % 4) * KT + c / 4;                // where column c is stored
+    const int lfrag = (lane & 15) * DS + (lane >> 4) * KT; // this lane's operand inside a 16-row block
+
+    // this wave's block pairs (bi <= bj), a contiguous run of the row-major
+    // enumeration of the upper triangle, and their LDS fragment offsets
+    const int per = (p.npb + 7) / 8;
+    const int s0 = wave * per;
+    int sbi[kRdmSlots], sbj[kRdmSlots];                    // block rows / columns of the slots
+    int nslot = 0;
+    {
+        int bi = 0, bj = 0, q = 0;
+        while (q < s0 && bi < p.nb) {                      // walk to pair s0
+            if (++bj == p.nb) { ++bi; bj = bi; }
+            ++q;
+        }
+#pragma unroll
+        for (int s = 0; s < kRdmSlots; ++s) {
+            const bool ok = s < per && s0 + s < p.npb;
+            sbi[s] = ok ? bi : 0;
+            sbj[s] = ok ? bj : 0;
+            nslot += ok ? 1 : 0;
+            if (ok && ++bj == p.nb) { ++bi; bj = bi; }
+        }
+    }
+    acc_t acc[kRdmSlots];
+#pragma unroll
+    for (int s = 0; s < kRdmSlots; ++s) acc[s] = acc_t{0, 0, 0, 0};
+    // partial sums of this workgroup: block pair s0 + s, element (row, col) at row*16 + col
+    double *out = p.part + int64_t(blockIdx.x) * p.npb * 256;
+    bool first = true;
+
+    for (int Ka = blockIdx.x; Ka < p.Na; Ka += gridDim.x) {
+        const T *crow = p.cp + int64_t(Ka) * p.ld;
+        const uint32_t xa = p.astr[Ka];
+        for (int c = tid; c < p.ld; c += 512) row[c] = crow[c];
+        for (int r = tid; r < MR; r += 512) {
+            int kind = r == n2 ? -2 : -1, aux = 0;
+            if (r < n2 && r / n == r % n) {
+                kind = -3;
+                aux = r / n + 256 * int((xa >> (r / n)) & 1u);
+            }
+            rowJ[r] = kind;
+            rowS[r] = aux;
+        }
+        __syncthreads();
+        for (int e = tid; e < p.anexc; e += 512) {
+            const uint32_t w = p.aexc[int64_t(Ka) * p.anexc + e];
+            if (w == kExcNone) continue;
+            const int k = (w >> 6) & 31, l = (w >> 1) & 31;
+            rowJ[k * n + l] = int(w >> 11);
+            rowS[k * n + l] = (w & 1) ? -1 : 1;
+        }
+        // this thread's column c of every tile, its alpha entries a = rg + RG i
+        // (source offset, target row, sign) and beta entries e = rg + RG i
+        uint32_t asrc[KA];
+        int adst[KA];
+        T asgn[KA];
+#pragma unroll
+        for (int i = 0; i < KA; ++i) {
+            const int a = rg + RG * i;
+            const uint32_t w = a < p.anexc ? p.aexc[int64_t(Ka) * p.anexc + a] : kExcNone;
+            adst[i] = w == kExcNone ? -1 : int(((w >> 6) & 31) * n + ((w >> 1) & 31));
+            asrc[i] = w == kExcNone ? 0u : (w >> 11) * uint32_t(p.ld) + uint32_t(c);
+            asgn[i] = (w & 1) ? T(-1) : T(1);
+        }
+        // operands of tile c0 in registers, those of the next tile in flight
+        T aval[KA], anext[KA];
+        uint32_t bw[KB], bnext[KB], bs, bsnext;
+        auto fetch = [&](int t0, T (&av)[KA], uint32_t (&bv)[KB], uint32_t &bsv) {
+            const int Kb = t0 + c;
+#pragma unroll
+            for (int i = 0; i < KA; ++i) av[i] = adst[i] >= 0 ? p.cp[asrc[i] + uint32_t(t0)] : T(0);
+            const bool in = Kb < p.Nb;
+#pragma unroll
+            for (int i = 0; i < KB; ++i) {
+                const int e = rg + RG * i;
+                bv[i] = in && e < p.bnexc ? p.bexc[int64_t(Kb) * p.bnexc + e] : kExcNone;
+            }
+            bsv = in ? p.bstr[Kb] : 0u;
+        };
+        fetch(0, aval, bw, bs);
+        // D starts at zero for this K_a; afterwards each tile rewrites the alpha,
+        // diagonal and C rows and clears the cells of zero rows that the previous
+        // tile's beta part wrote
+        for (int i = tid; i < MR * DS; i += 512) D[i] = T(0);
+        uint32_t bprev[KB];
+#pragma unroll
+        for (int i = 0; i < KB; ++i) bprev[i] = kExcNone;
+        __syncthreads();
+        for (int c0 = 0; c0 < p.ld; c0 += NT) {
+            if (c0 + NT < p.ld) fetch(c0 + NT, anext, bnext, bsnext);
+            const int Kb = c0 + c;
+#pragma unroll
+            for (int i = 0; i < KB; ++i) {
+                const uint32_t w = bprev[i];
+                if (w == kExcNone) continue;
+                const int r = int(((w >> 6) & 31) * n + ((w >> 1) & 31));
+                if (rowJ[r] == -1) D[r * DS + cperm] = T(0);
+            }
+            // diagonal rows (k, k) for orbitals k = rg, rg + RG, ... and the C row (k = n)
+            for (int k = rg; k <= n; k += RG) {
+                const int r = k < n ? k * n + k : n2;
+                T v = row[Kb];
+                if (k < n) v *= T((rowS[r] >> 8) + int((bs >> k) & 1u));
+                D[r * DS + cperm] = v;
+            }
+            // alpha rows (padding columns of C are zero)
+#pragma unroll
+            for (int i = 0; i < KA; ++i)
+                if (adst[i] >= 0) D[adst[i] * DS + cperm] = asgn[i] * aval[i];
+            __syncthreads();
+            // beta part: within a column the excitations have distinct (k, l),
+            // so no two threads add to one cell
+#pragma unroll
+            for (int i = 0; i < KB; ++i) {
+                const uint32_t w = bw[i];
+                if (w == kExcNone) continue;
+                const int k = (w >> 6) & 31, l = (w >> 1) & 31;
+                const T u = row[w >> 11];
+                D[(k * n + l) * DS + cperm] += (w & 1) ? -u : u;
+            }
+            __syncthreads();
+            // M += D D^T over the tile's columns: per slot one operand of each
+            // block (all KT k steps), the row operand reloaded only when the
+            // block row changes, the next slot's column operand in flight
+            {
+                auto frag = [&](int blk, T (&f)[KT]) {
+                    const V *src = reinterpret_cast<const V *>(D + 16 * blk * DS + lfrag);
+#pragma unroll
+                    for (int v = 0; v < KT / VE; ++v) {
+                        const V x = src[v];
+#pragma unroll
+                        for (int e = 0; e < VE; ++e) f[v * VE + e] = x[e];
+                    }
+                };
+                // slots in groups of SG: SG independent accumulation chains per k step
+                constexpr int SG = sizeof(T) == 4 ? 2 : 1;
+#pragma unroll
+                for (int g0 = 0; g0 < kRdmSlots; g0 += SG) {
+                    if (g0 < nslot) {
+                        T fa[SG][KT], fb[SG][KT];
+#pragma unroll
+                        for (int q = 0; q < SG; ++q) {
+                            const int sl = g0 + q < kRdmSlots ? g0 + q : kRdmSlots - 1;
+                            if (g0 + q < nslot) {
+                                frag(sbi[sl], fa[q]);
+                                frag(sbj[sl], fb[q]);
+                            }
+                        }
+#pragma unroll
+                        for (int t = 0; t < KT; ++t)
+#pragma unroll
+                            for (int q = 0; q < SG; ++q)
+                                if (g0 + q < kRdmSlots && g0 + q < nslot)
+                                    acc[g0 + q] = M::op(fa[q][t], fb[q][t], acc[g0 + q]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);         // one group's operands in registers at a time
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < KA; ++i) aval[i] = anext[i];
+#pragma unroll
+            for (int i = 0; i < KB; ++i) {
+                bprev[i] = bw[i];
+                bw[i] = bnext[i];
+            }
+            bs = bsnext;
+        }
+        // one alpha string's products are summed in the accumulators' precision,
+        // the strings of a workgroup in FP64 (each element has one owning lane)
+#pragma unroll
+        for (int s = 0; s < kRdmSlots; ++s) {
+            if (s < nslot) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    double *o = out + int64_t(s0 + s) * 256 + M::out_row(lane, i) * 16 + (lane & 15);
+                    *o = (first ? 0.0 : *o) + double(acc[s][i]);
+                }
+            }
+            acc[s] = acc_t{0, 0, 0, 0};
+        }
+        first = false;
+    }
+}
+
+// The FP32 form.  SLOTS: at least the block pairs per wave.
 //
-// With two buffers the next tile is built between the products of this one (alpha,
+// Two tile buffers: the next tile is built between the products of this one (alpha,
 // diagonal and C rows, barrier, beta part), and on each SIMD (waves w and w + 4 share
 // one) one wave builds first and the other multiplies first.  The build has no
 // branches: missing excitations go to a spare row, all loads of a part are out before
 // the first is used, and the tile's beta words are one contiguous run of the list.
 //
-// What bounds it (CAS(14,14) in FP32: 6.4 ms, with one buffer, branches and the words read
-// string by string 7.1): the FP32 matrix instructions, 4.1 ms with 91 block pairs on 96
-// slots, keep their SIMD from issuing the build's vector instructions.  (Exact three-way
-// splits on the bf16 matrix cores took 5.2 ms and left the sums a hundred times closer
-// to FP64, which is another result than this kernel's by more than a density's 1e-9.)
-template <typename T, int NT, int SLOTS, int TILES>
-__global__ __launch_bounds__(512, 2) void k_rdm(RdmArgs<T> p) {
+// What bounds it (CAS(14,14): 6.4 ms, in the FP64 kernel's form 7.1): the FP32 matrix
+// instructions, 4.1 ms with 91 block pairs on 96 slots, keep their SIMD from issuing the
+// build's vector instructions.  (Exact three-way splits on the bf16 matrix cores took
+// 5.2 ms and left the sums a hundred times closer to FP64, which is another result than
+// this kernel's by more than a density's 1e-9.  In FP64 this form is slower: 11.4 ms
+// against 11.2 at 14 orbitals, 50 against 45 at 15.)
+template <typename T, int NT, int SLOTS>
+__global__ __launch_bounds__(512, 2) void k_rdm2(RdmArgs<T> p) {
     using M = Mfma<T>;
     using acc_t = typename M::acc_t;
     // D is stored with the columns of a tile permuted so that the k steps a lane
@@ -71,8 +285,8 @@ __global__ __launch_bounds__(512, 2) void k_rdm(RdmArgs<T> p) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int n = p.n, n2 = n * n, MR = 16 * p.nb;
     const int DT = (MR + 1) * DS;                          // elements of a tile: MR rows and the spare one
-    T *D0 = reinterpret_cast<T *>(smem_raw);               // [TILES][MR + 1][DS]
-    T *row = D0 + TILES * DT;                              // [ld]: C(K_a, .)
+    T *D0 = reinterpret_cast<T *>(smem_raw);               // [2][MR + 1][DS]
+    T *row = D0 + 2 * DT;                              // [ld]: C(K_a, .)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int RG = 512 / NT;                           // threads per tile column
@@ -128,7 +342,7 @@ __global__ __launch_bounds__(512, 2) void k_rdm(RdmArgs<T> p) {
         // D starts at zero for this K_a; afterwards each tile rewrites the alpha,
         // diagonal and C rows and clears the cells of the other rows that the beta
         // part of the buffer's previous tile wrote
-        for (int i = tid; i < TILES * DT; i += 512) D0[i] = T(0);
+        for (int i = tid; i < 2 * DT; i += 512) D0[i] = T(0);
         // this thread's column c of every tile, its alpha entries a = rg + RG i
         uint32_t asrc[KA];
         int adst[KA];
@@ -144,7 +358,7 @@ __global__ __launch_bounds__(512, 2) void k_rdm(RdmArgs<T> p) {
         }
         // operands of the next tile to build, in flight
         T av[KA];
-        uint32_t bw[KA], bold[TILES][KA], bs;
+        uint32_t bw[KA], bold[2][KA], bs;
         auto fetch = [&](int t) {
             const int Kb = t * NT + c;
 #pragma unroll
@@ -161,7 +375,7 @@ __global__ __launch_bounds__(512, 2) void k_rdm(RdmArgs<T> p) {
         auto build_alpha = [&](T *D, int t) {
 #pragma unroll
             for (int i = 0; i < KA; ++i) {
-                const uint32_t w = bold[TILES - 1][i], k = (w >> 6) & 31, l = (w >> 1) & 31;
+                const uint32_t w = bold[1][i], k = (w >> 6) & 31, l = (w >> 1) & 31;
                 const bool clear = w != kExcNone && !(((xa >> k) & ~(xa >> l)) & 1u);
                 D[clear ? int(k * n + l) * DS + bcol[i] : spare] = T(0);
             }
@@ -191,7 +405,7 @@ __global__ __launch_bounds__(512, 2) void k_rdm(RdmArgs<T> p) {
             for (int i = 0; i < KA; ++i) D[at[i]] = old[i] + ((bw[i] & 1) ? -u[i] : u[i]);
 #pragma unroll
             for (int i = 0; i < KA; ++i) {
-                if (TILES == 2) bold[TILES - 1][i] = bold[0][i];
+                bold[1][i] = bold[0][i];
                 bold[0][i] = bw[i];
             }
         };
@@ -229,7 +443,7 @@ __global__ __launch_bounds__(512, 2) void k_rdm(RdmArgs<T> p) {
             }
         };
 #pragma unroll
-        for (int q = 0; q < TILES; ++q)
+        for (int q = 0; q < 2; ++q)
 #pragma unroll
             for (int i = 0; i < KA; ++i) bold[q][i] = kExcNone;
         fetch(0);
@@ -239,30 +453,22 @@ __global__ __launch_bounds__(512, 2) void k_rdm(RdmArgs<T> p) {
         build_beta(D0);
         if (ntile > 1) fetch(1);
         __syncthreads();
-        constexpr int HALF = TILES == 2 ? (SLOTS / 2 + 1) / 2 * 2 : SLOTS;
+        constexpr int HALF = (SLOTS / 2 + 1) / 2 * 2;
         const std::integral_constant<int, 0> i0;
         const std::integral_constant<int, HALF> i1;
         const std::integral_constant<int, SLOTS> i2;
         const bool early = wave < 4;
         for (int t = 0; t < ntile; ++t) {
             const bool next = t + 1 < ntile;
-            const T *D = D0 + (TILES == 2 && (t & 1) ? DT : 0);
-            T *Dn = D0 + (TILES == 2 && !(t & 1) ? DT : 0);
-            if constexpr (TILES == 2) {
-                if (!early && next) build_alpha(Dn, t + 1);
-                products(D, i0, i1);
-                if (early && next) build_alpha(Dn, t + 1);
-                __syncthreads();
-                if (!early && next) build_beta(Dn);
-                products(D, i1, i2);
-                if (early && next) build_beta(Dn);
-            } else {
-                products(D, i0, i1);
-                __syncthreads();                           // the tile consumed
-                if (next) build_alpha(Dn, t + 1);
-                __syncthreads();
-                if (next) build_beta(Dn);
-            }
+            const T *D = D0 + (t & 1 ? DT : 0);
+            T *Dn = D0 + (t & 1 ? 0 : DT);
+            if (!early && next) build_alpha(Dn, t + 1);
+            products(D, i0, i1);
+            if (early && next) build_alpha(Dn, t + 1);
+            __syncthreads();
+            if (!early && next) build_beta(Dn);
+            products(D, i1, i2);
+            if (early && next) build_beta(Dn);
             if (t + 2 < ntile) fetch(t + 2);
             __syncthreads();                               // this tile consumed, the next one built
         }
@@ -317,32 +523,17 @@ __global__ __launch_bounds__(256) void k_rdm_final(const double *mtri, int nb, i
 template <typename T>
 constexpr int rdm_nt() { return sizeof(T) == 4 ? 32 : 16; }
 
-template <typename T>
-size_t rdm_lds(const cisigma_ctx *ctx, int tiles) {
-    const size_t mr = size_t(16) * ((ctx->n * ctx->n + 1 + 15) / 16), ds = rdm_nt<T>() + 16 / sizeof(T);
-    return (size_t(tiles) * (mr + 1) * ds + size_t(ctx->pl[0].ld[0])) * sizeof(T);
-}
 constexpr size_t kRdmLds = 160 * 1024;
 
-template <typename T, int SLOTS, int TILES>
-hipError_t run_rdm(const RdmArgs<T> &a, int grid, size_t lds, hipStream_t s) {
-    constexpr int NT = rdm_nt<T>();
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rdm<T, NT, SLOTS, TILES>),
+// 8 block pairs per wave serve up to 12 orbitals, 12 up to 14, 20 up to 16
+template <int SLOTS>
+hipError_t run_rdm2(const RdmArgs<float> &a, int grid, size_t lds, hipStream_t s) {
+    constexpr int NT = rdm_nt<float>();
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rdm2<float, NT, SLOTS>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_rdm<T, NT, SLOTS, TILES>), dim3(grid), dim3(512), lds, s, a);
+    hipLaunchKernelGGL((k_rdm2<float, NT, SLOTS>), dim3(grid), dim3(512), lds, s, a);
     return hipGetLastError();
-}
-
-// 8 block pairs per wave serve up to 12 orbitals, 12 up to 14, 20 up to 16.  One tile
-// buffer only for FP64 rows that leave no room for two (16 orbitals, 8 beta electrons).
-template <typename T>
-hipError_t dispatch_rdm(const cisigma_ctx *ctx, const RdmArgs<T> &a, int grid, hipStream_t s) {
-    const int per = (a.npb + 7) / 8;
-    const size_t lds = rdm_lds<T>(ctx, 2);
-    if (lds > kRdmLds) return run_rdm<T, 20, 1>(a, grid, rdm_lds<T>(ctx, 1), s);
-    if (per <= 8) return run_rdm<T, 8, 2>(a, grid, lds, s);
-    return per <= 12 ? run_rdm<T, 12, 2>(a, grid, lds, s) : run_rdm<T, 20, 2>(a, grid, lds, s);
 }
 
 }  // namespace
@@ -350,9 +541,9 @@ hipError_t dispatch_rdm(const cisigma_ctx *ctx, const RdmArgs<T> &a, int grid, h
 int rdm_blocks(int n) { return (n * n + 1 + 15) / 16; }
 
 size_t rdm_lds_bytes(const cisigma_ctx *ctx, int dtype) {
-    const size_t two = dtype == CISIGMA_FP32 ? rdm_lds<float>(ctx, 2) : rdm_lds<double>(ctx, 2);
-    if (two <= kRdmLds) return two;
-    return dtype == CISIGMA_FP32 ? rdm_lds<float>(ctx, 1) : rdm_lds<double>(ctx, 1);
+    const size_t mr = size_t(16) * rdm_blocks(ctx->n), ld = size_t(ctx->pl[0].ld[0]);
+    if (dtype == CISIGMA_FP32) return (2 * (mr + 1) * (rdm_nt<float>() + 4) + ld) * 4;
+    return (mr * (rdm_nt<double>() + 2) + ld) * 8 + 2 * mr * 4;
 }
 
 int rdm_grid(const cisigma_ctx *ctx) { return std::min(ctx->sp[0].nstr, 256); }
@@ -370,7 +561,8 @@ hipError_t launch_rdm(const cisigma_ctx *ctx, const void *cp, int dtype, double 
     if (nb > kRdmMaxBlocks || ctx->sp[0].nexc > 64 || ctx->sp[1].nexc > 64) return hipErrorInvalidValue;
     const int npb = nb * (nb + 1) / 2;
     const int G = rdm_grid(ctx);
-    if (rdm_lds_bytes(ctx, dtype) > kRdmLds || G <= 0) return hipErrorInvalidValue;
+    const size_t lds = rdm_lds_bytes(ctx, dtype);
+    if (lds > kRdmLds || G <= 0) return hipErrorInvalidValue;
     auto fill = [&](auto &a) {
         a.aexc = ctx->sp[0].d_exc;
         a.bexc = ctx->sp[1].d_exc;
@@ -391,12 +583,18 @@ hipError_t launch_rdm(const cisigma_ctx *ctx, const void *cp, int dtype, double 
         RdmArgs<float> a{};
         fill(a);
         a.cp = static_cast<const float *>(cp);
-        e = dispatch_rdm<float>(ctx, a, G, s);
+        const int per = (npb + 7) / 8;
+        e = per <= 8 ? run_rdm2<8>(a, G, lds, s) : per <= 12 ? run_rdm2<12>(a, G, lds, s) : run_rdm2<20>(a, G, lds, s);
     } else {
         RdmArgs<double> a{};
         fill(a);
         a.cp = static_cast<const double *>(cp);
-        e = dispatch_rdm<double>(ctx, a, G, s);
+        constexpr int NT = rdm_nt<double>();
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rdm<double, NT>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_rdm<double, NT>), dim3(G), dim3(512), lds, s, a);
+        e = hipGetLastError();
     }
     if (e != hipSuccess) return e;
     const int64_t len = int64_t(npb) * 256;
