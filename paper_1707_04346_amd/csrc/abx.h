@@ -1,5 +1,6 @@
-// abx.h -- pieces shared by the owner-computes sigma_3 kernels (one-block and
-// GAS forms): the tile geometry and the beta-side scatter through a plan.
+// abx.h -- pieces shared by the owner-computes sigma_3 kernels that scatter through a
+// sorted list (the unit kernels, and the FP64 one-block kernel of small spaces): the
+// tile geometry and the list, or plan.
 //
 // Beta-side scatter plan (identical for every Ia, built once on the host):
 // per tile, the (target Ib, W element, sign) contributions sorted by target.
@@ -14,8 +15,7 @@
 // Plan words per wave and tile, lane-interleaved: EW entry words (bits 16..31:
 // the sigma slot the entry's running sum goes to -- the group's target when the
 // entry ends its group, else the lane's discard slot (row length + lane) -- in
-// bytes for the one-block FP32 kernel, in elements otherwise; bits 0..15: W byte
-// offset with the sign in bit 0)
+// elements; bits 0..15: W byte offset with the sign in bit 0)
 // and a header (bit 0: the lane's first entry starts a group; the rest: where
 // the carry from earlier lanes is added).  A group spans at most four lanes, so
 // the carry needs three lane shifts.
@@ -74,7 +74,7 @@ __device__ __forceinline__ T carry3(T tail, int f) {
 // Every entry writes old + running group sum to its slot (the group's target
 // at the group's last entry, the discard slot otherwise), so no two lanes write
 // one target and the writes need no branches.
-template <typename T, int EW, int TS = (sizeof(T) == 4 ? 0 : 3)>   // TS: log2 of the slot field unit in bytes
+template <typename T, int EW, int TS = (sizeof(T) == 4 ? 2 : 3)>   // TS: log2 of the slot field unit in bytes
 __device__ __forceinline__ void abx_scatter(const T *W, T *sig, const uint32_t (&w)[EW], uint32_t hdr,
                                             uint32_t spare) {
     const char *wb = reinterpret_cast<const char *>(W);
@@ -105,7 +105,7 @@ __device__ __forceinline__ void abx_scatter(const T *W, T *sig, const uint32_t (
 
 // The same for a tile whose plan uses only its first n (1..EW, uniform) entries
 // per lane: the others are neither read nor written.
-template <typename T, int EW, int TS = (sizeof(T) == 4 ? 0 : 3)>
+template <typename T, int EW, int TS = (sizeof(T) == 4 ? 2 : 3)>
 __device__ __forceinline__ void abx_scatter_n(const T *W, T *sig, const uint32_t (&w)[EW], uint32_t hdr,
                                               uint32_t spare, int n) {
     const char *wb = reinterpret_cast<const char *>(W);

@@ -1,10 +1,10 @@
 // sigma_abg.hip -- owner-computes form of the alpha-beta part sigma_3 (Eq. 8)
 // for spaces with several string types (GAS occupation types and point-group
 // irreps, Sec. 3.1), and for one-block spaces whose sigma row is too long for
-// the one-block kernel.  The contraction and the
-// beta-side scatter are those of the one-block form (abx.h); what differs is
-// which source tiles, k steps and W rows each alpha type needs, and that a
-// sigma row holds only the columns of the blocks allowed with the type.
+// the one-block kernel.  The contraction is that of the one-block forms, the
+// beta-side scatter goes through a sorted list (abx.h); what differs is which
+// source tiles, k steps and W rows each alpha type needs, and that a sigma row
+// holds only the columns of the blocks allowed with the type.
 #include "internal.h"
 #include "mfma.h"
 #include "bufio.h"
@@ -32,8 +32,8 @@ __device__ __forceinline__ uint4 uni_ld(const uint4 *p) {
 //
 // Units: an alpha type ta and a range [lo, hi) of its compact columns (the
 // beta strings of the blocks allowed with ta, concatenated).  One launch covers
-// all units, one workgroup per (unit, alpha string of its type), four waves as
-// in the FP64 one-block form.
+// all units, one workgroup per (unit, alpha string of its type), four waves (FP32
+// with C below 4 GB: eight).
 // The LDS sigma row holds the unit's columns; the unit's plan drops every
 // contribution that lands outside them.  For each source tile of the unit (32
 // columns of one beta type u2) the gathered rows are the single excitations of
