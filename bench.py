@@ -5,7 +5,7 @@ One step = one full sigma build (sigma_1 + sigma_2 + sigma_3 of Eq. 8, with the
 layout conversions) through cisigma_apply on a device-resident CI vector.
 Prints one JSON line with
   * value: sigma builds/s of the FP32 path (FP32 accumulation; the alpha-beta
-    products as exact bf16 splits of the FP32 operands);
+    products summed from bf16 parts of the FP32 operands, each as exact as in FP32);
   * roofline: the alpha-beta contraction kernel (the dominant one) against the
     FP32 matrix-core peak, its duration measured with HIP events on its own
     stream over the timed region; its numerator is the method's own work, the
@@ -561,7 +561,7 @@ def main():
     achieved = flops / ab_s / 1e12
     owner = bool(path32 & cis.PATH_AB_OWNER)
     tag = "k_sigma_ab_s" if owner else "k_sigma_ab"
-    kdesc = {"k_sigma_ab_s": "k_sigma_ab_s (owner-computes sigma_3: gathered C rows, split into bf16 parts -> six bf16 "
+    kdesc = {"k_sigma_ab_s": "k_sigma_ab_s (owner-computes sigma_3: gathered C rows, split into bf16 parts -> eight bf16 "
                              "MFMA products per FP32 product, LDS scatter; two workgroups per CU; the fraction is of "
                              "the FP32 matrix peak)",
              "k_sigma_ab": "k_sigma_ab (sigma_3 gather -> FP32 MFMA -> atomic scatter)"}

@@ -14,13 +14,14 @@
 // compute unit (72 KB of LDS, at most 256 registers), so one's matrix
 // instructions run while the other scatters.
 //
-// What bounds it (CAS(16,16), 18.5 ms; the FP32 instructions took 31.9): 54 matrix
+// What bounds it (CAS(16,16), 21.1 ms; the FP32 instructions took 31.9): 72 matrix
 // instructions of 16 cycles and ~170 vector instructions per wave and tile.  Beside
-// a matrix instruction about three vector ones issue free of charge, so the products
-// with the splitting of their operands alone take 14 ms; the scatter, alone 11 ms
-// (a third of it bank conflicts), hides behind the other workgroup's products only
-// in part.  Four waves that multiply and four that scatter in one workgroup, with
-// two W tiles, measured 22 ms: one wave per SIMD does not hide its own latencies.
+// a matrix instruction about three vector ones issue free of charge; the scatter,
+// alone 11 ms (a third of it bank conflicts), hides behind the other workgroup's
+// products only in part.  With six products instead of eight 18.6 ms, and single
+// products less exact than in FP32 (split.h).  Four waves that multiply and four that
+// scatter in one workgroup, with two W tiles, were slower (six products: 22 ms): one
+// wave per SIMD does not hide its own latencies.
 #include "internal.h"
 #include "bufio.h"
 #include "scatter_prog_dev.h"
@@ -137,7 +138,7 @@ __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int
         const uint32_t so = uint32_t(next) * (kNT * 4u);
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            c[s] = split_trunc(b[s]);
+            c[s] = split_round(b[s]);
             load_step(s, so);
         }
         load_self(so);
@@ -146,6 +147,10 @@ __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             h[s] = c[s].h;
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[r] = mfma_bf16(c[s].l, A[r][s].m, acc[r]);
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[r] = mfma_bf16(c[s].m, A[r][s].l, acc[r]);
 #pragma unroll
             for (int r = 0; r < NR; ++r) acc[r] = mfma_bf16(c[s].l, A[r][s].h, acc[r]);
 #pragma unroll
@@ -188,7 +193,7 @@ __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int
     lds_barrier();                       // W of tile 0 ready
     for (int tile = 0; tile + 1 < ntile; ++tile) {
         products(tile + 2 < ntile ? tile + 2 : ntile - 1);
-        __builtin_amdgcn_sched_barrier(0);   // (mixed into the products the scatter is slower: 19.1 against 18.4 ms)
+        __builtin_amdgcn_sched_barrier(0);   // (mixed into the products the scatter is slower; with six products 19.1 against 18.4 ms)
         scatter();
         plan_load(tile + 1);
         lds_barrier();                   // W of this tile consumed

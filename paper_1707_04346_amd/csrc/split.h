@@ -1,14 +1,14 @@
-// split.h -- FP32 products on the bf16 matrix cores, without loss: every FP32
-// operand is the exact sum of three bf16 numbers (h + m + l: 3 x 8 significant
-// bits), and a product a b is summed from the six partial products that reach
-// the last bits of an FP32 result,
-//   a b = ah bh + (ah bm + am bh) + (ah bl + am bm + al bh) + O(2^-24 a b).
-// The bf16 matrix rate is sixteen times the FP32 one, so six products cost 3/8
-// of the FP32 instruction's time.
+// split.h -- FP32 products on the bf16 matrix cores, as exact as FP32 ones: every FP32
+// operand is the exact sum of three bf16 numbers, each rounded to nearest (h + m + l:
+// 3 x 8 significant bits, |m| <= 2^-8 |h|, |l| <= 2^-17 |h|), and a product a b is
+// summed from eight of the nine partial products, smallest first,
+//   a b = ah bh + (ah bm + am bh) + (ah bl + am bm + al bh) + (am bl + al bm) + al bl;
+// al bl, below 2^-34 a b, is left out.  The last addition rounds as an FP32 product
+// does, the earlier ones round sums of at most 2^-7 a b.  (Without the two products of
+// order 2^-25 the largest error of a product is 1.3 times an FP32 product's, with the
+// vector's parts truncated instead of rounded 2.7 times.)  The bf16 matrix rate is
+// sixteen times the FP32 one, so eight products cost half of the FP32 instruction's time.
 //
-// The kernels split one operand once (the integrals: rounded to nearest, so its m
-// and l parts have either sign and the dropped products average out) and the
-// other per use (the vector: truncated, which is one byte permute per pair).
 // Sums run over the small products first and the ah bh last: the accumulator is
 // then rounded at full size only once per 32-row step instead of once per 4 rows
 // (K = 64: error 5.8e-8 of the result against 1.44e-7 for the FP32 instruction,
@@ -38,36 +38,22 @@ __device__ __forceinline__ floatx4 mfma_bf16(bf16x8 a, bf16x8 b, floatx4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// parts rounded to nearest
+// parts rounded to nearest, two values at a time (one conversion a pair)
 __device__ __forceinline__ Split8 split_round(const float (&x)[8]) {
-    Split8 s;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        s.h[j] = __bf16(x[j]);
-        const float r = x[j] - float(s.h[j]);
-        s.m[j] = __bf16(r);
-        s.l[j] = __bf16(r - float(s.m[j]));
-    }
-    return s;
-}
-
-// parts truncated: the high halves of a pair by one byte permute, x - h by a mask
-// and a subtraction (exact).  (A dot product with -1 does the latter in one
-// instruction, but runs on the matrix unit: between bf16 products it costs eight
-// cycles, a mask and a subtraction six.)
-__device__ __forceinline__ Split8 split_trunc(const float (&x)[8]) {
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
     u32x4_t h, m, l;
-    auto rest = [](float v) { return v - __uint_as_float(__float_as_uint(v) & 0xffff0000u); };
     auto pack = [](float a, float b) {
-        return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+        return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{a, b}, bf16x2));
     };
+    auto lo = [](uint32_t p) { return __uint_as_float(p << 16); };
+    auto hi = [](uint32_t p) { return __uint_as_float(p & 0xffff0000u); };
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const float a = x[2 * i], b = x[2 * i + 1];
-        const float a1 = rest(a), b1 = rest(b);
         h[i] = pack(a, b);
+        const float a1 = a - lo(h[i]), b1 = b - hi(h[i]);
         m[i] = pack(a1, b1);
-        l[i] = pack(rest(a1), rest(b1));
+        l[i] = pack(a1 - lo(m[i]), b1 - hi(m[i]));
     }
     Split8 s;
     s.h = __builtin_bit_cast(bf16x8, h);
