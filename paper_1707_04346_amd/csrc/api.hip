@@ -145,7 +145,7 @@ void free_ctx(cisigma_ctx *c) {
     (void)hipFree(c->bt.blk); (void)hipFree(c->bt.tb); (void)hipFree(c->bt.tr); (void)hipFree(c->bt.tc);
     (void)hipFree(c->d_pblk); (void)hipFree(c->d_blkoff);
     (void)hipFree(c->plan.d_entries[0]); (void)hipFree(c->plan.d_entries[1]);
-    (void)hipFree(c->prog.d_words);
+    (void)hipFree(c->prog.d_words); (void)hipFree(c->d_wide);
     (void)hipFree(c->d_act_start); (void)hipFree(c->d_act_tiles);
     (void)hipFree(c->go.d_slot); (void)hipFree(c->go.d_coff); (void)hipFree(c->go.d_g32); (void)hipFree(c->go.d_g64);
     for (int d = 0; d < 2; ++d) {
@@ -216,6 +216,7 @@ int build_integrals(cisigma_ctx *c) {
     std::vector<float> gp32(gp.begin(), gp.end());
     HIP_OR_FAIL(c, upload(&c->d_gp64, gp), "init: integral upload");
     HIP_OR_FAIL(c, upload(&c->d_gp32, gp32), "init: integral upload");
+    c->split_exact = cis::split_integrals_exact(gp32);
     std::vector<float> h32(c->h.begin(), c->h.end());
     HIP_OR_FAIL(c, upload(&c->d_h64, c->h), "init: integral upload");
     HIP_OR_FAIL(c, upload(&c->d_h32, h32), "init: integral upload");
@@ -640,6 +641,7 @@ int build_scatter_prog(cisigma_ctx *c, const PlanTiles &pt, int ew) {
         });
         if (!ok) continue;
         HIP_OR_FAIL(c, upload(&c->prog.d_words, words), "init: scatter program");
+        HIP_OR_FAIL(c, upload(&c->d_wide, std::vector<int>(2, 0)), "init: scatter program");
         c->prog.ntile = int(tiles.size());
         c->prog.prog = g;
         cis::sigma_ab_owner_shape(c->sp[0].nexc, c->npair, ew ? ew : 16, c->prog.shape);
@@ -1307,6 +1309,7 @@ int ensure_workspace(cisigma_ctx *c, int dtype) {
         HIP_OR_FAIL(c, hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming), "apply: side stream");
     }
     HIP_OR_FAIL(c, hipDeviceSynchronize(), "apply: workspace");
+    if (dtype == CISIGMA_FP32) W.wide = c->d_wide;
     W.ready = true;
     return CISIGMA_OK;
 }
@@ -1341,7 +1344,7 @@ int apply_sigma_ws(cisigma_ctx *c, const void *C, void *sigma, int dtype, hipStr
     // to the second accumulator (same shape when nalpha = nbeta), the alpha-beta
     // part alone to the first, and the output gather forms sp + st + p st^T.
     const int par = c->spin_parity;
-    HIP_OR_FAIL(c, launch_scatter_in(c, C, W.cp, par ? nullptr : W.ct, dtype, s), "apply: layout conversion");
+    HIP_OR_FAIL(c, launch_scatter_in(c, C, W.cp, par ? nullptr : W.ct, dtype, s, W.wide), "apply: layout conversion");
     HIP_OR_FAIL(c, mark(CISIGMA_PASS_LAYOUT_IN), "apply: profiling events");
     if (par) {
         HIP_OR_FAIL(c, launch_fill(W.sp, c->pl[0].size, dtype, s), "apply: fill");
@@ -1381,11 +1384,13 @@ int apply_sigma_ws(cisigma_ctx *c, const void *C, void *sigma, int dtype, hipStr
         HIP_OR_FAIL(c, hipEventRecord(c->ev_join, c->side), "apply: join");
     }
     {
-        const hipError_t e = launch_sigma_ab(c, W.cp, W.sp, dtype, s);
-        if (e == hipErrorNotSupported && c->deterministic)
+        const hipError_t e = launch_sigma_ab(c, W.cp, W.sp, dtype, s, W.wide);
+        if (e == hipErrorNotSupported && c->deterministic) {
+            if (W.wide) HIP_OR_FAIL(c, launch_fill(W.wide, 1, CISIGMA_FP32, s), "apply: fill");   // (the output kernel's part)
             return cis_set_error(c, CISIGMA_EUNSUPPORTED,
                                  "apply: deterministic mode: sigma_3 of this space would need the float-atomic "
                                  "general kernel (no owner-computes kernel covers it)");
+        }
         HIP_OR_FAIL(c, e, "apply: sigma_3 (alpha-beta)");
     }
     HIP_OR_FAIL(c, mark(CISIGMA_PASS_SIGMA_AB), "apply: profiling events");
@@ -1396,9 +1401,9 @@ int apply_sigma_ws(cisigma_ctx *c, const void *C, void *sigma, int dtype, hipStr
                     "apply: sigma_1 (beta-beta)");
     HIP_OR_FAIL(c, mark(CISIGMA_PASS_SIGMA_BB), "apply: profiling events");
     if (par)
-        HIP_OR_FAIL(c, launch_gather_parity(c, W.sp, W.st, sigma, par, dtype, s), "apply: layout conversion");
+        HIP_OR_FAIL(c, launch_gather_parity(c, W.sp, W.st, sigma, par, dtype, s, W.wide), "apply: layout conversion");
     else
-        HIP_OR_FAIL(c, launch_gather_out(c, W.sp, W.st, sigma, dtype, s), "apply: layout conversion");
+        HIP_OR_FAIL(c, launch_gather_out(c, W.sp, W.st, sigma, dtype, s, W.wide), "apply: layout conversion");
     HIP_OR_FAIL(c, mark(CISIGMA_PASS_LAYOUT_OUT), "apply: profiling events");
     if (prof) {
         for (auto e : ev) c->prof_events.push_back(e);
@@ -1453,6 +1458,7 @@ int apply_sigma_noalloc(cisigma_ctx *c, const void *C, void *sigma, int dtype, h
     }
     const int64_t ny = ys_rows_elems(c);
     if (ny > 0 && size_t(ny) * es <= kNoallocScratchBytes - copies) W.ys = base + copies;
+    if (dtype == CISIGMA_FP32 && c->d_wide) W.wide = c->d_wide + 1;
     W.ready = true;
     HIP_OR_FAIL(c, launch_fill(W.cp, int64_t(na / es), dtype, s), "apply_noalloc: clear");
     HIP_OR_FAIL(c, launch_fill(W.ct, int64_t(nb / es), dtype, s), "apply_noalloc: clear");

@@ -192,6 +192,7 @@ struct Workspace {
     void *ys = nullptr;    // materialised same-spin rows (one-type spins), ys_chunk columns each
     int ys_chunk = 0;
     void *ys2 = nullptr;   // in ys: the beta rows beside the alpha ones (small spaces, all columns), else null
+    int *wide = nullptr;   // FP32: set while C has elements outside the split products' range
     bool ready = false;
 };
 
@@ -231,6 +232,8 @@ struct cisigma_ctx {
     cis::BlockTilesDev bt{};       // tiles of the caller-layout blocks
     cis::ScatterPlan plan;         // beta-side scatter of the one-block sigma_3 kernel of small spaces
     cis::ProgPlan prog;            // beta-side scatter of the other one-block sigma_3 kernels
+    int *d_wide = nullptr;         // [2]: Workspace::wide of apply and of apply_noalloc (with a program)
+    bool split_exact = false;      // the FP32 integrals are in the split products' range
     // general sigma_3 kernel: per alpha type, the 64-column beta tiles that can
     // change sigma (CSR over alpha types; all tiles for one-block spaces)
     int *d_act_start = nullptr;    // [ntype_a + 1]
@@ -301,12 +304,16 @@ hipError_t build_diag_tables(cisigma_ctx *ctx);
 // padded K extent of the (ij|kl) table used by the alpha-beta kernel
 int sigma_ab_kp(int npair);
 hipError_t launch_fill(void *x, int64_t n, int dtype, hipStream_t s);
-hipError_t launch_sigma_ab(const cisigma_ctx *ctx, const void *C, void *sigma, int dtype, hipStream_t s);
+hipError_t launch_sigma_ab(const cisigma_ctx *ctx, const void *C, void *sigma, int dtype, hipStream_t s, const int *wide);
 // owner-computes sigma_3 in FP64 (one-block spaces with a scatter plan): false when
 // the shape has no compiled kernel (nothing launched), else *err is the launch status
 bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *C, void *sigma, hipStream_t s, hipError_t *err);
-// the FP32 form (split products): false when the space has no program (nothing launched)
-bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *C, void *sigma, hipStream_t s, hipError_t *err);
+// the FP32 form (split products; plain ones where *wide or the integrals ask for them):
+// false when the space has no program (nothing launched)
+bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *C, void *sigma, const int *wide, hipStream_t s,
+                           hipError_t *err);
+// whether all integrals are in the split products' range
+bool split_integrals_exact(const std::vector<float> &g);
 // whether it is compiled for rb 16-row blocks of pairs and a scatter program
 bool sigma_ab_split_prog(int rb, int prog);
 // its list form for at most 10 orbitals: false without a plan (nothing launched)
@@ -339,14 +346,15 @@ bool same_spin_materialisable(int npv);
 // lists of `count` pairs; false when none is compiled
 bool same_spin_shape_for(int count, int *ks, int *mbl);
 // caller vector -> alpha-major and beta-major padded copies
-hipError_t launch_scatter_in(const cisigma_ctx *ctx, const void *C, void *cp, void *ct, int dtype, hipStream_t s);
+hipError_t launch_scatter_in(const cisigma_ctx *ctx, const void *C, void *cp, void *ct, int dtype, hipStream_t s,
+                             int *wide = nullptr);
 // sigma = alpha-major accumulator + transpose of the beta-major accumulator
 hipError_t launch_gather_out(const cisigma_ctx *ctx, const void *sp, const void *st, void *sigma, int dtype,
-                             hipStream_t s);
+                             hipStream_t s, int *wide = nullptr);
 hipError_t launch_hdiag(const cisigma_ctx *ctx, double *out, hipStream_t s);
 // sigma = sp + st + p st^T on the one-block layout (st: the alpha-alpha part, alpha-major)
 hipError_t launch_gather_parity(const cisigma_ctx *ctx, const void *sp, const void *st, void *sigma, int parity,
-                                int dtype, hipStream_t s);
+                                int dtype, hipStream_t s, int *wide = nullptr);
 // x <- (x + p x^T) / 2 for the caller's one-block vector x[n][n]
 hipError_t launch_symmetrize(void *x, int n, int parity, int dtype, hipStream_t s);
 // (x + p x^T) / 2 in place on a caller-layout vector of a space with several

@@ -300,7 +300,7 @@ int ks_for(int kp) {
 }
 
 template <typename T>
-hipError_t sigma_ab_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s) {
+hipError_t sigma_ab_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, const int *wide) {
     const auto &A = ctx->sp[0];
     const auto &B = ctx->sp[1];
     const auto &L = ctx->pl[0];
@@ -341,7 +341,7 @@ hipError_t sigma_ab_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStrea
         // path 2 asks for the units), else the GAS owner kernel (which splits long rows
         // over units), else the general kernel
         const bool one = ctx->cas && ctx->ab_mode != 2 &&
-                         (sizeof(T) == 4 ? launch_sigma_ab_split(ctx, cp, sp, s, &e)
+                         (sizeof(T) == 4 ? launch_sigma_ab_split(ctx, cp, sp, wide, s, &e)
                                          : launch_sigma_ab_owner(ctx, cp, sp, s, &e));
         if (one || launch_sigma_ab_gas(ctx, cp, sp, dt, s, &e)) {
             if (e == hipSuccess) {
@@ -372,9 +372,10 @@ int sigma_ab_kp(int npair) {
     return ks > 0 ? 4 * ks : ((npair + 3) / 4) * 4;
 }
 
-hipError_t launch_sigma_ab(const cisigma_ctx *ctx, const void *cp, void *sp, int dtype, hipStream_t s) {
+hipError_t launch_sigma_ab(const cisigma_ctx *ctx, const void *cp, void *sp, int dtype, hipStream_t s,
+                           const int *wide) {
     if (ctx->na == 0 || ctx->nb == 0) return hipSuccess;
-    return dtype == CISIGMA_FP32 ? sigma_ab_t<float>(ctx, cp, sp, s) : sigma_ab_t<double>(ctx, cp, sp, s);
+    return dtype == CISIGMA_FP32 ? sigma_ab_t<float>(ctx, cp, sp, s, wide) : sigma_ab_t<double>(ctx, cp, sp, s, nullptr);
 }
 
 }  // namespace cis

@@ -14,7 +14,7 @@
 // compute unit (72 KB of LDS, at most 256 registers), so one's matrix
 // instructions run while the other scatters.
 //
-// What bounds it (CAS(16,16), 21.1 ms; the FP32 instructions took 31.9): 72 matrix
+// What bounds it (CAS(16,16), 21.1 to 21.8 ms; the FP32 instructions took 31.9): 72 matrix
 // instructions of 16 cycles and ~170 vector instructions per wave and tile.  Beside
 // a matrix instruction about three vector ones issue free of charge; the scatter,
 // alone 11 ms (a third of it bank conflicts), hides behind the other workgroup's
@@ -22,13 +22,19 @@
 // products less exact than in FP32 (split.h).  Four waves that multiply and four that
 // scatter in one workgroup, with two W tiles, were slower (six products: 22 ms): one
 // wave per SIMD does not hide its own latencies.
+//
+// A C with elements outside the split's range (infinities, NaN, tiny or huge ones:
+// split.h) is multiplied by the FP32 instructions in the same frame, and so is any C
+// where integrals are (CAS(16,16) 29.8 instead of 21.8 ms, CAS(12,12) 130 us instead of
+// 108).  The kernel that copies C in looks at its elements on the way, which its memory
+// traffic hides, and leaves the answer in p.wide.
 #include "internal.h"
 #include "bufio.h"
 #include "scatter_prog_dev.h"
 #include "split.h"
 
 #include <algorithm>
-#include <type_traits>
+#include <cmath>
 
 namespace cis {
 namespace {
@@ -43,6 +49,8 @@ struct AbsArgs {
     const uint32_t *astr;    // [Na]
     const float *gp;         // [n*n][kp]
     const uint32_t *plan;    // [ntile][4 waves][words][64 lanes]
+    const int *wide;         // nonzero: C has elements outside the split's range
+    int exact;               // nonzero: the integrals have
     uint32_t cp_bytes, plan_bytes;   // < 2^31
     int anexc, n, kp, npair, Na, ld;
 };
@@ -58,15 +66,17 @@ __device__ __forceinline__ float self_coef(const AbsArgs &p, uint32_t xa, int m)
 }
 
 // KS: 32-row steps over the gathered rows; NR: row blocks of this wave, from rb0;
-// SELF: Ia's own row takes a slot of the steps, else it is added in FP32 (rank 1)
-template <int KS, int NR, int RB, int PG, bool SELF>
+// SELF: Ia's own row takes a slot of the steps, else it is added in FP32 (rank 1);
+// EX: products by the FP32 instruction
+template <int KS, int NR, int RB, int PG, bool SELF, bool EX>
 __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int cb, int rb0, int wave, int lane) {
     constexpr int NRA = NR > 0 ? NR : 1;
     constexpr int MP = 16 * RB;
     const int lr = lane & 15, lk = lane >> 4;
     const uint32_t xa = p.astr[Ia];
     // gathered rows of this lane: k = 32 s + 8 (lane / 16) + j
-    Split8 A[NRA][KS];
+    Split8 A[EX ? 1 : NRA][EX ? 1 : KS];
+    float A32[EX ? NRA : 1][EX ? KS : 1][8];
     uint32_t boff[KS][8];
     const uint32_t col = uint32_t(cb * 16 + lr);
 #pragma unroll
@@ -102,7 +112,14 @@ __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int
             }
         }
 #pragma unroll
-        for (int r = 0; r < NRA; ++r) A[r][s] = split_round(a[r]);
+        for (int r = 0; r < NRA; ++r) {
+            if constexpr (EX) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) A32[r][s][j] = a[r][j];
+            } else {
+                A[r][s] = split_round(a[r]);
+            }
+        }
     }
     float dI[NRA];
     uint32_t boffI = 0;
@@ -132,10 +149,9 @@ __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int
     };
     // W of the rows held in b, then the rows of tile `next` into b.  D[Jb][kl]:
     // a lane ends with four columns Jb of one kl row.
-    auto products = [&](int next) {
+    auto products_split = [&](uint32_t so) {
         bf16x8 h[KS];
         Split8 c[KS];
-        const uint32_t so = uint32_t(next) * (kNT * 4u);
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             c[s] = split_round(b[s]);
@@ -166,6 +182,25 @@ __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int
         for (int s = 0; s < KS; ++s)
 #pragma unroll
             for (int r = 0; r < NR; ++r) acc[r] = mfma_bf16(h[s], A[r][s].h, acc[r]);
+    };
+    // the same layouts: four rows k = 32 s + 8 (lane / 16) + j per instruction
+    auto products_fp32 = [&](uint32_t so) {
+#pragma unroll
+        for (int r = 0; r < NRA; ++r) acc[r] = floatx4{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+                for (int r = 0; r < NR; ++r) acc[r] = Mfma<float>::op(b[s][j], A32[r][s][j], acc[r]);
+            load_step(s, so);
+        }
+        load_self(so);
+    };
+    auto products = [&](int next) {
+        const uint32_t so = uint32_t(next) * (kNT * 4u);
+        if constexpr (EX) products_fp32(so);
+        else products_split(so);
     };
     auto store_w = [&]() {
 #pragma unroll
@@ -216,8 +251,14 @@ __global__ __launch_bounds__(256, 2) void k_sigma_ab_s(AbsArgs p) {
     for (int c = tid * 4; c < p.ld; c += 1024)
         *reinterpret_cast<floatx4 *>(sig + c) = *reinterpret_cast<const floatx4 *>(row + c);
     for (int r = tid; r < MP; r += 256) W[r * kWS + kNT] = 0.0f;   // pad column: unused references read it
-    if (wave < 2) abs_body<KS, R0, RB, PG, SELF>(p, W, Ia, wave & 1, 0, wave, lane);
-    else abs_body<KS, R1, RB, PG, SELF>(p, W, Ia, wave & 1, R0, wave, lane);
+    const int ex = p.exact | __builtin_amdgcn_readfirstlane(*p.wide);   // one answer for the whole launch
+    if (ex) {
+        if (wave < 2) abs_body<KS, R0, RB, PG, SELF, true>(p, W, Ia, wave & 1, 0, wave, lane);
+        else abs_body<KS, R1, RB, PG, SELF, true>(p, W, Ia, wave & 1, R0, wave, lane);
+    } else {
+        if (wave < 2) abs_body<KS, R0, RB, PG, SELF, false>(p, W, Ia, wave & 1, 0, wave, lane);
+        else abs_body<KS, R1, RB, PG, SELF, false>(p, W, Ia, wave & 1, R0, wave, lane);
+    }
     __syncthreads();
     for (int c = tid * 4; c < p.ld; c += 1024)
         *reinterpret_cast<floatx4 *>(row + c) = *reinterpret_cast<const floatx4 *>(sig + c);
@@ -258,9 +299,16 @@ bool sigma_ab_split_prog(int rb, int prog) {
     return false;
 }
 
-bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipError_t *err) {
+bool split_integrals_exact(const std::vector<float> &g) {
+    for (float v : g)
+        if (v != 0.0f && !(std::fabs(v) >= kSplitMinA && std::fabs(v) < kSplitMax)) return false;
+    return true;
+}
+
+bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *cp, void *sp, const int *wide, hipStream_t s,
+                           hipError_t *err) {
     const ProgPlan &P = ctx->prog;
-    if (!P.d_words) return false;
+    if (!P.d_words || !wide) return false;
     const auto &A = ctx->sp[0];
     AbsArgs x{};
     x.cp = static_cast<const float *>(cp);
@@ -269,6 +317,8 @@ bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *cp, void *sp, hip
     x.astr = A.d_str;
     x.gp = ctx->d_gp32;
     x.plan = P.d_words;
+    x.wide = wide;
+    x.exact = ctx->split_exact ? 0 : 1;
     x.anexc = A.nexc;
     x.n = ctx->n;
     x.kp = ctx->kp;

@@ -14,8 +14,12 @@
 // (K = 64: error 5.8e-8 of the result against 1.44e-7 for the FP32 instruction,
 // both against 64 bits on random operands spread over three decades).
 //
-// Infinities: inf - inf in the split makes them NaN; NaN stays NaN.  Operands
-// below 2^-110 lose their m and l parts to the underflow of bf16.
+// The range: an infinity would split into NaN (inf - inf), an operand near the largest
+// FP32 number round up to one, and a tiny one lose its m and l parts to the underflow of
+// bf16.  Vector elements have to be zero or of magnitude [2^-100, 2^60) (parts down to
+// 2^-125, still normal numbers), integrals zero or [2^-76, 2^60), so that a sum of
+// integrals, a multiple of 2^-99, keeps to the vector's range or is zero.  The products
+// of others are left to the FP32 instruction by the callers.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -29,6 +33,16 @@ namespace cis {
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+constexpr float kSplitMin = 0x1p-100f, kSplitMax = 0x1p60f;   // vector elements
+constexpr float kSplitMinA = 0x1p-76f;                        // integrals
+
+// neither zero nor in the vector's range (NaN: yes)
+__device__ __forceinline__ bool split_wide(float x) {
+    constexpr uint32_t LO = __builtin_bit_cast(uint32_t, kSplitMin), HI = __builtin_bit_cast(uint32_t, kSplitMax);
+    const uint32_t u = __float_as_uint(x) & 0x7fffffffu;
+    return u != 0 && u - LO >= HI - LO;
+}
 
 struct Split8 { bf16x8 h, m, l; };   // eight FP32 values: one lane's operand of a 32-row step
 

@@ -8,6 +8,7 @@
 // 64x64 LDS-tiled transpose); gather_out forms
 // sigma = alpha-major accumulator + (beta-major accumulator)^T.
 #include "internal.h"
+#include "split.h"
 
 namespace cis {
 
@@ -20,16 +21,19 @@ __global__ void k_fill(T *x, int64_t n) {
     for (; i < n; i += stride) x[i] = T(0);
 }
 
-// tiles: (block, r0, c0) with 64x64 extent; 256 threads
+// tiles: (block, r0, c0) with 64x64 extent; 256 threads.  wide (or null): set where C
+// has elements that the split products do not hold exactly; the kernel that forms the
+// output clears it again, after their last reader.
 template <typename T>
 __global__ __launch_bounds__(256) void k_scatter_in(const T *__restrict__ C, T *__restrict__ cp, T *__restrict__ ct,
                                                    const BlockDev *__restrict__ blk, const int *__restrict__ tb,
-                                                   const int *__restrict__ tr, const int *__restrict__ tc) {
+                                                   const int *__restrict__ tr, const int *__restrict__ tc, int *wide) {
     __shared__ T tile[64][65];
     const int t = blockIdx.x;
     const BlockDev B = blk[tb[t]];
     const int r0 = tr[t], c0 = tc[t];
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    bool w = false;
 #pragma unroll 4
     for (int i = 0; i < 16; ++i) {
         int r = r0 + 4 * i + ty, c = c0 + tx;
@@ -38,8 +42,10 @@ __global__ __launch_bounds__(256) void k_scatter_in(const T *__restrict__ C, T *
             v = C[B.off + int64_t(r) * B.nb + c];
             cp[B.sega + int64_t(r) * B.lda + c] = v;
         }
+        if constexpr (sizeof(T) == 4) w |= split_wide(v);
         tile[4 * i + ty][tx] = v;
     }
+    if (sizeof(T) == 4 && wide && w) *wide = 1;
     if (ct == nullptr) return;                 // the beta-major copy is not wanted (uniform)
     __syncthreads();
 #pragma unroll 4
@@ -57,9 +63,10 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_gather_parity(const T *__restrict__ sp, const T *__restrict__ st,
                                                       T *__restrict__ sig, const BlockDev *__restrict__ blk,
                                                       const int *__restrict__ tr, const int *__restrict__ tc,
-                                                      T p) {
+                                                      T p, int *wide) {
     __shared__ T tile[64][65];
     const int t = blockIdx.x;
+    if (wide && t == 0 && threadIdx.x == 0) *wide = 0;
     const BlockDev B = blk[0];
     const int r0 = tr[t], c0 = tc[t];
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
@@ -179,9 +186,10 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_gather_out(const T *__restrict__ sp, const T *__restrict__ st,
                                                    T *__restrict__ sig, const BlockDev *__restrict__ blk,
                                                    const int *__restrict__ tb, const int *__restrict__ tr,
-                                                   const int *__restrict__ tc) {
+                                                   const int *__restrict__ tc, int *wide) {
     __shared__ T tile[64][65];
     const int t = blockIdx.x;
+    if (wide && t == 0 && threadIdx.x == 0) *wide = 0;
     const BlockDev B = blk[tb[t]];
     const int r0 = tr[t], c0 = tc[t];
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
@@ -237,34 +245,35 @@ hipError_t launch_fill(void *x, int64_t n, int dtype, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_scatter_in(const cisigma_ctx *ctx, const void *C, void *cp, void *ct, int dtype, hipStream_t s) {
+hipError_t launch_scatter_in(const cisigma_ctx *ctx, const void *C, void *cp, void *ct, int dtype, hipStream_t s,
+                             int *wide) {
     BlockTilesDev bt = block_tiles(ctx);
     if (bt.ntiles == 0) return hipSuccess;
     if (dtype == CISIGMA_FP32)
         hipLaunchKernelGGL(k_scatter_in<float>, dim3(bt.ntiles), dim3(256), 0, s, static_cast<const float *>(C),
-                           static_cast<float *>(cp), static_cast<float *>(ct), bt.blk, bt.tb, bt.tr, bt.tc);
+                           static_cast<float *>(cp), static_cast<float *>(ct), bt.blk, bt.tb, bt.tr, bt.tc, wide);
     else
         hipLaunchKernelGGL(k_scatter_in<double>, dim3(bt.ntiles), dim3(256), 0, s, static_cast<const double *>(C),
-                           static_cast<double *>(cp), static_cast<double *>(ct), bt.blk, bt.tb, bt.tr, bt.tc);
+                           static_cast<double *>(cp), static_cast<double *>(ct), bt.blk, bt.tb, bt.tr, bt.tc, nullptr);
     return hipGetLastError();
 }
 
 hipError_t launch_gather_out(const cisigma_ctx *ctx, const void *sp, const void *st, void *sigma, int dtype,
-                             hipStream_t s) {
+                             hipStream_t s, int *wide) {
     BlockTilesDev bt = block_tiles(ctx);
     if (bt.ntiles == 0) return hipSuccess;
     if (dtype == CISIGMA_FP32)
         hipLaunchKernelGGL(k_gather_out<float>, dim3(bt.ntiles), dim3(256), 0, s, static_cast<const float *>(sp),
-                           static_cast<const float *>(st), static_cast<float *>(sigma), bt.blk, bt.tb, bt.tr, bt.tc);
+                           static_cast<const float *>(st), static_cast<float *>(sigma), bt.blk, bt.tb, bt.tr, bt.tc, wide);
     else
         hipLaunchKernelGGL(k_gather_out<double>, dim3(bt.ntiles), dim3(256), 0, s, static_cast<const double *>(sp),
                            static_cast<const double *>(st), static_cast<double *>(sigma), bt.blk, bt.tb, bt.tr,
-                           bt.tc);
+                           bt.tc, nullptr);
     return hipGetLastError();
 }
 
 hipError_t launch_gather_parity(const cisigma_ctx *ctx, const void *sp, const void *st, void *sigma, int parity,
-                                int dtype, hipStream_t s) {
+                                int dtype, hipStream_t s, int *wide) {
     BlockTilesDev bt = block_tiles(ctx);
     if (bt.ntiles == 0) return hipSuccess;
     if (!ctx->cas) {
@@ -283,11 +292,11 @@ hipError_t launch_gather_parity(const cisigma_ctx *ctx, const void *sp, const vo
     if (dtype == CISIGMA_FP32)
         hipLaunchKernelGGL(k_gather_parity<float>, dim3(bt.ntiles), dim3(256), 0, s, static_cast<const float *>(sp),
                            static_cast<const float *>(st), static_cast<float *>(sigma), bt.blk, bt.tr, bt.tc,
-                           float(parity));
+                           float(parity), wide);
     else
         hipLaunchKernelGGL(k_gather_parity<double>, dim3(bt.ntiles), dim3(256), 0, s,
                            static_cast<const double *>(sp), static_cast<const double *>(st),
-                           static_cast<double *>(sigma), bt.blk, bt.tr, bt.tc, double(parity));
+                           static_cast<double *>(sigma), bt.blk, bt.tr, bt.tc, double(parity), nullptr);
     return hipGetLastError();
 }
 

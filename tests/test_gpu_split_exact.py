@@ -70,3 +70,86 @@ def test_one_product_is_as_exact_as_in_fp32(space):
     got, want = one_element(space, 1.0)
     assert np.abs(np.abs(got) - np.abs(want)).max() > 0.0
     assert (np.abs(np.abs(got) - np.abs(want)) <= 2.125 * 2.0 ** -24 * np.abs(want)).all()
+
+
+@pytest.mark.parametrize("space", SPACES, ids=lambda s: f"n{s[0]}a{s[1]}b{s[2]}")
+@pytest.mark.parametrize("scale,gscale", [(2.0 ** -115, 1.0), (2.0 ** 70, 1.0), (1.0, 2.0 ** -90), (2.0 ** -10, 2.0 ** 70)],
+                         ids=["tiny_c", "huge_c", "tiny_g", "huge_g"])
+def test_operands_outside_the_split_range(space, scale, gscale):
+    """Operands whose bf16 parts would underflow or overflow: the same bound, wherever the
+    product is a normal number."""
+    got, want = one_element(space, scale, gscale)
+    normal = np.abs(want) >= 2.0 ** -126
+    assert normal.mean() > 0.9
+    assert (np.abs(np.abs(got) - np.abs(want)) <= 2.125 * 2.0 ** -24 * np.abs(want))[normal].all()
+
+
+@pytest.mark.parametrize("space", SPACES, ids=lambda s: f"n{s[0]}a{s[1]}b{s[2]}")
+def test_infinite_element_stays_infinite(space):
+    """(ij|kl) times an infinite element is infinite, not NaN."""
+    got, want = one_element(space[:3] + (2,), float("inf"))
+    assert np.isinf(want).all() and np.isinf(got).all()
+
+
+def dense(n, na, nb, seed=63):
+    import paper_1707_04346_amd as cis
+    import synth_inputs as si
+    h, g = si.integrals(n, 2 * n, seed)
+    ctx = cis.Context(n, na, nb, h, g)
+    return cis, ctx, torch.tensor(si.ci_vector(ctx.ndet, seed + 1), dtype=torch.float32, device="cuda")
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan"), 2.0 ** -130], ids=["inf", "nan", "denormal"])
+def test_bad_element_stays_where_it_couples(bad):
+    """An element (Ja, Jb) that is not finite leaves every sigma element with a string Ia
+    more than one excitation from Ja and Ib != Jb what it is without it."""
+    cis, ctx, C = dense(8, 4, 4)
+    sa = strings(8, 4)
+    ja, jb = 17, 40
+    C[ja * 70 + jb] = 0.0
+    base, S = torch.empty_like(C), torch.empty_like(C)
+    ctx.apply(C, base)
+    C[ja * 70 + jb] = bad
+    ctx.apply(C, S)
+    far = torch.tensor([bin(int(x ^ sa[ja])).count("1") > 2 for x in sa], device="cuda")
+    keep = far[:, None] & (torch.arange(70, device="cuda") != jb)[None, :]
+    assert int(keep.sum()) > 1000
+    d = (S.view(70, 70) - base.view(70, 70))[keep]
+    assert bool(torch.isfinite(d).all()) and float(d.abs().max()) <= 1e-5 * float(base.abs().max())
+
+
+@pytest.mark.parametrize("how", ["apply", "noalloc", "sector", "graph"])
+@pytest.mark.parametrize("space", [(6, 3, 3), (12, 6, 6)], ids=["n6", "n12"])
+def test_one_bad_vector_does_not_change_the_next(space, how):
+    """The choice of the products is made anew on each call: a vector after a bad one gives
+    the bits it gave before, also where a graph replays the calls."""
+    cis, ctx, C = dense(*space)
+    n = int(round(ctx.ndet ** 0.5))
+    if how == "sector":
+        ctx.set_option(cis.OPT_SPIN_PARITY, 1)
+        C = (C.view(n, n) + C.view(n, n).T).reshape(-1).contiguous()
+    bad = C.clone()
+    bad[n + 1] = float("nan")              # on the diagonal: symmetric as the vector is
+    X, S = C.clone(), torch.empty_like(C)
+    call = ctx.apply_noalloc if how == "noalloc" else ctx.apply
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    call(X, S, stream=st)
+    st.synchronize()
+    want = S.clone()
+    if how == "graph":
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            call(X, S, stream=st)
+    for k in range(3):
+        for src in (bad, C):
+            X.copy_(src)
+            S.zero_()
+            torch.cuda.synchronize()
+            if how == "graph":
+                graph.replay()
+            else:
+                call(X, S, stream=st)
+            torch.cuda.synchronize()
+            assert bool(torch.isnan(S).any()) == (src is bad)
+        assert torch.equal(S, want), k
