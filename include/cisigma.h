@@ -412,6 +412,9 @@ int cisigma_rdm(cisigma_ctx *ctx, const void *C, int dtype, double *rdm1, double
  * call synchronises those events and writes the summed milliseconds of each
  * pass since profiling was (re)enabled into ms[CISIGMA_NPASS] and the number
  * of profiled apply calls into *ncalls.  EINVAL when profiling is off.
+ * Spaces so small that both same-spin parts go out in one launch run them one
+ * after the other while they are timed: their passes add up to more than a
+ * call without profiling takes.
  */
 int cisigma_pass_times(cisigma_ctx *ctx, double *ms, int *ncalls);
 
@@ -431,23 +434,38 @@ int cisigma_pass_times(cisigma_ctx *ctx, double *ms, int *ncalls);
 int cisigma_last_path(const cisigma_ctx *ctx, int dtype, int *flags);
 
 /*
- * cisigma_last_shape -- the compiled shape of the owner-computes sigma_3
- * kernel (the alpha-beta part of Eq. 8) that the most recent cisigma_apply of
- * dtype launched, for tests that must know which variant ran:
- *   shape[0]  k steps of gathered alpha rows (4 rows each; the FP32 one-block
- *             kernel multiplies 32 rows at a time and reports the same count)
+ * cisigma_last_shape -- the size class of the sigma_3 kernel (the alpha-beta part of
+ * Eq. 8) that the most recent cisigma_apply of dtype launched:
+ *   shape[0]  k steps of gathered alpha rows (4 rows each)
  *   shape[1]  16-row blocks of orbital pairs
- *   shape[2]  scatter-plan entries per lane and tile (one-block kernels: those a
- *             plan of equal runs per lane would take)
+ *   shape[2]  scatter-plan entries per lane and tile
  *   shape[3]  0: no owner-computes kernel ran (general kernel); 1: one-block
- *             kernel with the own row in a k step; 2: one-block kernel with the
- *             own row as the rank-1 start of the accumulators; 3: units of
+ *             kernel; 2: one-block kernel of a space whose alpha excitations fill
+ *             whole k steps, so that the own row would take one more; 3: units of
  *             the GAS form (four waves); 4: units of a one-block space with
  *             its sigma row split, eight-wave form (FP32); 5: units of the GAS
  *             form, eight waves (FP32 with C below 4 GB)
+ * For units these are the compiled kernel's.  For one-block spaces they are the
+ * space's: the k steps its excitations take, and the entries a plan of equal runs per
+ * lane takes (0: no such plan holds the space); the compiled kernel may be larger, the
+ * FP32 one takes 32 rows a step, and only the kernel of small FP64 spaces has such a
+ * plan.  cisigma_last_kernel says which kernel it was.
  * shape is a host int[4], written.  EINVAL for NULL arguments or a bad dtype.
  */
 int cisigma_last_shape(const cisigma_ctx *ctx, int dtype, int *shape);
+
+/*
+ * cisigma_last_kernel -- the sigma_3 kernel that the most recent cisigma_apply of dtype
+ * launched, with its template arguments, for tests that must know which variant ran:
+ *   "k_sigma_ab_l<k steps, row blocks, entries per lane, F>"          one block, FP64
+ *   "k_sigma_ab_x<k steps, quads of rows, row blocks, program, F>"    one block, FP64
+ *   "k_sigma_ab_s<32-row steps, row blocks, program, F>"              one block, FP32
+ *   "k_sigma_ab_g<..>", "k_sigma_ab_gw<..>" (k steps, row blocks, entries)    units
+ *   "k_sigma_ab", "k_sigma_ab_direct"                                 general
+ * F: "self" with the own row in a k step, "rank1" with it as a rank-1 term.  Never NULL;
+ * empty before any apply, for arguments that are not valid, and where sigma_3 is zero.
+ */
+const char *cisigma_last_kernel(const cisigma_ctx *ctx, int dtype);
 
 /* message of the most recent failure on ctx (never NULL) */
 const char *cisigma_last_error(const cisigma_ctx *ctx);

@@ -95,6 +95,8 @@ _lib.cisigma_apply_noalloc.restype = _i32
 _lib.cisigma_apply_noalloc.argtypes = [_vp, _vp, _vp, _i32, _vp]
 _lib.cisigma_last_shape.restype = _i32
 _lib.cisigma_last_shape.argtypes = [_vp, _i32, _vp]
+_lib.cisigma_last_kernel.restype = ctypes.c_char_p
+_lib.cisigma_last_kernel.argtypes = [_vp, _i32]
 _lib.cisigma_pass_times.restype = _i32
 _lib.cisigma_pass_times.argtypes = [_vp, _vp, ctypes.POINTER(_i32)]
 _lib.cisigma_last_error.restype = ctypes.c_char_p
@@ -105,7 +107,7 @@ _lib.cisigma_strerror.argtypes = [_i32]
 EXPORTS = ["cisigma_init", "cisigma_free", "cisigma_ndet", "cisigma_layout", "cisigma_address", "cisigma_strings",
            "cisigma_excitations", "cisigma_set_option", "cisigma_apply", "cisigma_hdiag", "cisigma_davidson",
            "cisigma_pass_times", "cisigma_last_path", "cisigma_last_error", "cisigma_strerror", "cisigma_rdm",
-           "cisigma_hmat_block", "cisigma_autotune", "cisigma_last_shape",
+           "cisigma_hmat_block", "cisigma_autotune", "cisigma_last_shape", "cisigma_last_kernel",
            "cisigma_apply_noalloc", "cisigma_set_log", "cisigma_init_sym"]
 PATH_AB_OWNER, PATH_SS_MATERIALISED, PATH_AB_SHARED_CU = 1, 2, 4
 
@@ -301,13 +303,16 @@ class Context:
         return f.value
 
     def last_shape(self, dtype=FP32):
-        """(k steps, pair row blocks, plan entries per lane, variant) of the
-        owner-computes sigma_3 kernel of the most recent apply of dtype;
-        variant 0: general kernel, 1: own row in a k step, 2: rank-1 own row,
-        3: GAS units."""
+        """(k steps, pair row blocks, plan entries per lane, variant): the size class of
+        the sigma_3 kernel of the most recent apply of dtype; variant 0: general
+        kernel, 1 and 2: one-block kernels, 3 to 5: units."""
         sh = np.zeros(4, np.int32)
         self._check(_lib.cisigma_last_shape(self._h, int(dtype), sh.ctypes.data))
         return tuple(int(x) for x in sh)
+
+    def last_kernel(self, dtype=FP32):
+        """Name and template arguments of that kernel ("" before any apply)."""
+        return _lib.cisigma_last_kernel(self._h, int(dtype)).decode()
 
     def set_log(self, path):
         """Davidson JSON-lines log file (None: off)."""

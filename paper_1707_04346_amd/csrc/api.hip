@@ -597,8 +597,8 @@ int plan_tables(cisigma_ctx *c, std::vector<uint32_t> &exc, std::vector<uint32_t
     return CISIGMA_OK;
 }
 
-// Entries per lane of a plan in equal runs, as cisigma_last_shape reports them; 0 where
-// no such plan holds the space.
+// Entries per lane of a plan in equal runs: the list kernel's, and part of the size class
+// cisigma_last_shape reports; 0 where no such plan holds the space.
 int plan_width(const PlanSpec &ps, const PlanTiles &pt) {
     for (int cand : {ps.width(pt.need), 16})
         if (cand >= pt.need && ps.width(cand) == cand && plan_fits(pt, cand)) return cand;
@@ -644,7 +644,7 @@ int build_scatter_prog(cisigma_ctx *c, const PlanTiles &pt, int ew) {
         HIP_OR_FAIL(c, upload(&c->d_wide, std::vector<int>(2, 0)), "init: scatter program");
         c->prog.ntile = int(tiles.size());
         c->prog.prog = g;
-        cis::sigma_ab_owner_shape(c->sp[0].nexc, c->npair, ew ? ew : 16, c->prog.shape);
+        cis::sigma_ab_owner_shape(c->sp[0].nexc, c->npair, ew, c->prog.shape);
         break;
     }
     return CISIGMA_OK;
@@ -1339,6 +1339,7 @@ int apply_sigma_ws(cisigma_ctx *c, const void *C, void *sigma, int dtype, hipStr
     auto mark = [&](int pass) -> hipError_t { return prof ? hipEventRecord(ev[pass + 1], s) : hipSuccess; };
     c->last_path[dtype == CISIGMA_FP32] = mat ? CISIGMA_PATH_SS_MATERIALISED : 0;
     for (int &v : c->last_shape[dtype == CISIGMA_FP32]) v = 0;
+    c->last_kernel[dtype == CISIGMA_FP32] = "";
     // M_S = 0 sector (Sec. 3.3): for C(Ib, Ia) = p C(Ia, Ib) the beta-beta part
     // is p times the transposed alpha-alpha part.  The alpha-alpha part then goes
     // to the second accumulator (same shape when nalpha = nbeta), the alpha-beta
@@ -1673,6 +1674,11 @@ CIS_API int cisigma_last_shape(const cisigma_ctx *ctx, int dtype, int *shape) {
     if (!ctx || !shape || (dtype != CISIGMA_FP32 && dtype != CISIGMA_FP64)) return CISIGMA_EINVAL;
     for (int i = 0; i < 4; ++i) shape[i] = ctx->last_shape[dtype == CISIGMA_FP32][i];
     return CISIGMA_OK;
+}
+
+CIS_API const char *cisigma_last_kernel(const cisigma_ctx *ctx, int dtype) {
+    if (!ctx || (dtype != CISIGMA_FP32 && dtype != CISIGMA_FP64)) return "";
+    return ctx->last_kernel[dtype == CISIGMA_FP32];
 }
 
 CIS_API const char *cisigma_strerror(int status) { return status_text(status); }

@@ -148,7 +148,7 @@ struct ProgPlan {
     uint32_t *d_words = nullptr;   // nullptr: none
     int ntile = 0;
     int prog = 0;                  // index into kProgs
-    int shape[4] = {0, 0, 0, 0};   // what cisigma_last_shape reports
+    int shape[4] = {0, 0, 0, 0};   // the space's size class, for cisigma_last_shape
 };
 
 // Owner-computes sigma_3 for GAS spaces: W rows are the orbital pairs grouped
@@ -263,7 +263,8 @@ struct cisigma_ctx {
     std::string log_path;          // Davidson JSON-lines log (cisigma_set_log; empty: none)
     int log_calls = 0;             // Davidson calls logged so far
     int last_path[2] = {0, 0};     // CISIGMA_PATH_* flags of the last apply, [FP64, FP32]
-    int last_shape[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};   // owner-computes sigma_3 shape of the last apply
+    int last_shape[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};   // cisigma_last_shape of the last apply
+    const char *last_kernel[2] = {"", ""};   // cisigma_last_kernel of the last apply: literals
     int ab_shared = 0;             // the one-block FP32 owner kernel last ran two workgroups per CU
     // kernel choice: 0 automatic, 1 the general scatter-atomic kernels only (CISIGMA_OPT_SIGMA_PATH)
     int ab_mode = 0;               // CISIGMA_OPT_SIGMA_PATH
@@ -318,7 +319,7 @@ bool split_integrals_exact(const std::vector<float> &g);
 bool sigma_ab_split_prog(int rb, int prog);
 // its list form for at most 10 orbitals: false without a plan (nothing launched)
 bool launch_sigma_ab_list(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipError_t *err);
-// shape[4] of the owner-computes kernel for anexc excitations, npair pairs and a plan of ew entries per lane
+// size class of a one-block space for anexc excitations, npair pairs and a list of ew entries per lane
 void sigma_ab_owner_shape(int anexc, int npair, int ew, int *shape);
 // plan width (entries per lane and tile) the owner-computes kernel uses for a
 // shape that needs `need`; 0 when no compiled kernel covers it

@@ -354,12 +354,14 @@ hipError_t sigma_ab_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStrea
     }
     // the general kernel accumulates with float atomics: refused in deterministic mode
     if (ctx->deterministic) return hipErrorNotSupported;
+    const_cast<cisigma_ctx *>(ctx)->last_kernel[sizeof(T) == 4] = "k_sigma_ab";
     const int mb = (A.nexc + 15) / 16;   // 16-row blocks of alpha excitations
     if (ks > 0 && ks * 4 == ctx->kp && mb <= 8) {
         if (mb <= 4) return dispatch_ks<T, 1>(a, s, ks);
         return dispatch_ks<T, 2>(a, s, ks);
     }
     int64_t tot = int64_t(a.Na) * a.Nb;
+    const_cast<cisigma_ctx *>(ctx)->last_kernel[sizeof(T) == 4] = "k_sigma_ab_direct";
     hipLaunchKernelGGL((k_sigma_ab_direct<T>), dim3(unsigned((tot + 255) / 256)), dim3(256), 0, s, a, tot);
     return hipGetLastError();
 }

@@ -699,6 +699,7 @@ bool gas_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipE
     a.nvirt = G.maxcols[d];
     a.rtk = ctx->sym ? 1 : 0;
     int *kshape = const_cast<cisigma_ctx *>(ctx)->last_shape[sizeof(T) == 4];
+    const char *&name = const_cast<cisigma_ctx *>(ctx)->last_kernel[sizeof(T) == 4];
     // one launch over every unit, or (CISIGMA_OPT_UNIT_LAUNCH) one launch per unit
     a.block_base = 0;
     auto launch_units = [&](AbgArgs<T> x, auto run) -> hipError_t {
@@ -720,6 +721,7 @@ bool gas_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipE
     if (!ran && G.ks == K && G.rb == R && G.plan[d].ew == E) {          \
         *err = launch_units(a, [&](const AbgArgs<T> &x, int n) { return run_abgw<T, K, R, E>(x, n, s); }); \
         kshape[0] = K; kshape[1] = R; kshape[2] = E; kshape[3] = 4;     \
+        name = "k_sigma_ab_gw<" #K ", " #R ", " #E ">";                 \
         ran = true;                                                     \
     }
         CIS_ABGW_SHAPES(CIS_RUNW)
@@ -732,6 +734,7 @@ bool gas_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipE
         *err = launch_units(a, [&](const AbgArgs<T> &x, int n) { return run_abg<T, K, R, E>(x, n, s); }); \
         kshape[0] = K; kshape[1] = R; kshape[2] = E;                    \
         kshape[3] = sizeof(T) == 4 && a.cp_bytes != 0 ? 5 : 3;          \
+        name = "k_sigma_ab_g<" #K ", " #R ", " #E ">";                  \
     }
     CIS_ABG_SHAPES(CIS_RUN)
 #undef CIS_RUN

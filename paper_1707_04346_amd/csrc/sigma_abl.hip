@@ -296,7 +296,7 @@ int rb_of(int npair) { return (npair + 15) / 16; }
 
 // shape[4] receives {KS, RB, EW, 1: row in a k step, 2: rank-1 start}
 template <typename T>
-bool dispatch_abx(const AbxArgs<T> &a, int ew, hipStream_t s, hipError_t *err, int *shape) {
+bool dispatch_abx(const AbxArgs<T> &a, int ew, hipStream_t s, hipError_t *err, int *shape, const char **name) {
     const int rb = rb_of(a.npair);
     if (a.anexc > 0 && a.anexc % 4 == 0) {
         const int ks1 = a.anexc / 4;
@@ -304,6 +304,7 @@ bool dispatch_abx(const AbxArgs<T> &a, int ew, hipStream_t s, hipError_t *err, i
     if (ks1 == K && rb == R && ew == E) {                           \
         *err = run_abx<T, K, R, E, false>(a, s);                    \
         shape[0] = K; shape[1] = R; shape[2] = E; shape[3] = 2;     \
+        *name = "k_sigma_ab_l<" #K ", " #R ", " #E ", rank1>";      \
         return true;                                                \
     }
         CIS_ABX_SHAPES_R1(CIS_RUN1)
@@ -314,6 +315,7 @@ bool dispatch_abx(const AbxArgs<T> &a, int ew, hipStream_t s, hipError_t *err, i
     if (ks == K && rb == R && ew == E) {                            \
         *err = run_abx<T, K, R, E, true>(a, s);                     \
         shape[0] = K; shape[1] = R; shape[2] = E; shape[3] = 1;     \
+        *name = "k_sigma_ab_l<" #K ", " #R ", " #E ", self>";       \
         return true;                                                \
     }
     CIS_ABX_SHAPES(CIS_RUN)
@@ -348,7 +350,7 @@ bool owner_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hi
     x.cp_bytes = uint32_t(cpb);
     x.plan_bytes = uint32_t(plb);
     auto *c = const_cast<cisigma_ctx *>(ctx);
-    return dispatch_abx<T>(x, P.ew, s, err, c->last_shape[0]);
+    return dispatch_abx<T>(x, P.ew, s, err, c->last_shape[0], &c->last_kernel[0]);
 }
 
 }  // namespace

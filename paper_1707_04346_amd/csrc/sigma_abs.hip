@@ -336,19 +336,23 @@ bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *cp, void *sp, con
     const bool alone = ctx->ab_mode == 3;
     const int ks = (x.anexc + 1 + 31) / 32;
     auto *c = const_cast<cisigma_ctx *>(ctx);
-    bool ran = false;
+    const char *ran = nullptr;
     // 64 excitations (8 of 16 orbitals) fill two steps: the own row as a rank-1 term
     if (x.anexc == 64 && rb == 9) {
-        if (P.prog == 3) { *err = run_abs<2, 9, 3, false>(x, s, alone); ran = true; }
-        if (P.prog == 4) { *err = run_abs<2, 9, 4, false>(x, s, alone); ran = true; }
+        if (P.prog == 3) { *err = run_abs<2, 9, 3, false>(x, s, alone); ran = "k_sigma_ab_s<2, 9, 3, rank1>"; }
+        if (P.prog == 4) { *err = run_abs<2, 9, 4, false>(x, s, alone); ran = "k_sigma_ab_s<2, 9, 4, rank1>"; }
     }
 #define CIS_RUN(K, R, G) \
-    if (!ran && ks == K && rb == R && P.prog == G) { *err = run_abs<K, R, G, true>(x, s, alone); ran = true; }
+    if (!ran && ks == K && rb == R && P.prog == G) {                         \
+        *err = run_abs<K, R, G, true>(x, s, alone);                          \
+        ran = "k_sigma_ab_s<" #K ", " #R ", " #G ", self>";                  \
+    }
     CIS_ABS_SHAPES(CIS_RUN)
 #undef CIS_RUN
     if (!ran) return false;
     c->ab_shared = !alone && abs_lds(x.ld, rb) <= 80 * 1024;
     for (int i = 0; i < 4; ++i) c->last_shape[1][i] = P.shape[i];
+    c->last_kernel[1] = ran;
     return true;
 }
 

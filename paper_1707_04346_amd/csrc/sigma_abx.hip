@@ -278,14 +278,16 @@ hipError_t run_abx(const AbxArgs &a, hipStream_t s) {
 #define CIS_ABX_SHAPES_R1(X) \
     X(4, 12, 3, 0) X(4, 12, 3, 1) X(9, 20, 5, 1) X(9, 20, 5, 4) X(16, 34, 9, 3) X(16, 34, 9, 4)
 
-// The shapes that cisigma_last_shape names: k steps, row blocks and the entries per
-// lane of a scatter plan in equal runs, by the spaces CAS(n, n/2) and their
-// open-shell neighbours.
+// Size classes of one-block spaces: k steps of four gathered rows, row blocks and the
+// entries per lane of a scatter plan in equal runs, by the spaces CAS(n, n/2) and their
+// open-shell neighbours.  Up to 10 orbitals they are the list kernel's compiled shapes
+// (sigma_abl.hip); for the others they only say how large a space is.
 #define CIS_ABX_NAMES(X)                                                                               \
     X(2, 1, 2) X(2, 1, 16) X(3, 2, 2) X(3, 2, 16) X(4, 2, 4) X(4, 2, 16) X(4, 3, 4) X(4, 3, 16)         \
     X(5, 3, 4) X(5, 3, 16) X(6, 3, 4) X(6, 3, 16) X(6, 4, 4) X(6, 4, 16) X(7, 4, 4) X(7, 4, 16)         \
     X(8, 5, 6) X(8, 5, 16) X(10, 5, 6) X(10, 5, 16) X(11, 6, 8) X(11, 6, 16) X(13, 7, 8) X(13, 7, 16)   \
     X(15, 8, 10) X(15, 8, 16) X(17, 9, 10) X(17, 9, 16)
+// Those whose excitations fill the k steps.
 #define CIS_ABX_NAMES_R1(X)                                                                            \
     X(1, 1, 2) X(1, 1, 16) X(2, 2, 2) X(2, 2, 16) X(4, 3, 4) X(4, 3, 16) X(6, 4, 4) X(6, 4, 16)         \
     X(9, 5, 6) X(9, 5, 16) X(12, 7, 8) X(12, 7, 16) X(16, 9, 10) X(16, 9, 16)
@@ -341,22 +343,26 @@ bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *cp, void *sp, hip
     if (cpb >= (uint64_t(1) << 31) || plb >= (uint64_t(1) << 31)) return false;
     x.cp_bytes = uint32_t(cpb);
     x.plan_bytes = uint32_t(plb);
-    bool ran = false;
-#define CIS_RUN1(K, Q, R, G) \
-    if (!ran && x.anexc == 4 * K && rb == R && P.prog == G) { *err = run_abx<K, Q, R, G, false>(x, s); ran = true; }
+    const char *ran = nullptr;
+#define CIS_RUN1(K, Q, R, G)                                                                   \
+    if (!ran && x.anexc == 4 * K && rb == R && P.prog == G) {                                  \
+        *err = run_abx<K, Q, R, G, false>(x, s);                                               \
+        ran = "k_sigma_ab_x<" #K ", " #Q ", " #R ", " #G ", rank1>";                           \
+    }
     CIS_ABX_SHAPES_R1(CIS_RUN1)
 #undef CIS_RUN1
     // the fewest k steps and quads that hold the space
 #define CIS_RUN(K, Q, R, G)                                                                    \
     if (!ran && 4 * K >= x.anexc + 1 && 4 * Q >= x.npair && rb == R && P.prog == G) {          \
         *err = run_abx<K, Q, R, G, true>(x, s);                                                \
-        ran = true;                                                                            \
+        ran = "k_sigma_ab_x<" #K ", " #Q ", " #R ", " #G ", self>";                            \
     }
     CIS_ABX_SHAPES(CIS_RUN)
 #undef CIS_RUN
     if (!ran) return false;
     auto *c = const_cast<cisigma_ctx *>(ctx);
     for (int i = 0; i < 4; ++i) c->last_shape[0][i] = P.shape[i];
+    c->last_kernel[0] = ran;
     return true;
 }
 
