@@ -12,8 +12,6 @@ from tolerance import rel
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.skip(reason="faulted on the GPU before the gather without a table was ruled out; the repaired "
-                         "route is shown by reading only and has not been run on a GPU since")
 @pytest.mark.parametrize("space", [(13, 12, 2), (14, 13, 1), (16, 2, 14)], ids=lambda s: f"n{s[0]}a{s[1]}b{s[2]}")
 @pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-10), (torch.float32, 1e-5)], ids=["fp64", "fp32"])
 def test_sigma_many_electrons(space, dtype, tol):
