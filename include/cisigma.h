@@ -89,7 +89,8 @@ extern "C" {
                                       owner-computes and stored-row kernels, stored rows that do not fit
                                       in memory, CISIGMA_OPT_SIGMA_PATH = 1) fails with
                                       CISIGMA_EUNSUPPORTED instead; the sigma output is then not written.
-                                      0 (default): such applies run the atomic kernels */
+                                      0 (default): such applies run the atomic kernels, and so do
+                                      small spaces where those are the faster ones */
 #define CISIGMA_OPT_UNIT_COLS 18   /* owner-computes units (GAS spaces, one-block spaces whose sigma row is
                                       longer than the LDS, or path 2): at most this many sigma columns per
                                       unit, 64..65536; 0 (default): as many as the LDS holds.  Rows are cut

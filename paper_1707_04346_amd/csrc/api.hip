@@ -702,6 +702,36 @@ int build_scatter_plan(cisigma_ctx *c) {
 //   (t2, l < t1),
 // and a source tile of another class than the unit's multiplies only the
 // blocks that lead into it (one or two instead of all).
+//
+// A space that no shape was made for and a larger one holds (missing k steps and rows are
+// zeros, and the fewer are filled the more of an item is overhead) takes the units where
+// they measured faster than the general kernel (sigma_3, 1,378 GAS and point-group
+// spaces of 8 to 18 orbitals and 50 one-block spaces of 17 to 19):
+//   point group     from 4,096 determinants (FP32 1.33 to 5 times as fast, FP64 1.7 to 5;
+//                   below 0.85 in FP32)
+//   GAS             from 16,384 determinants, with 12 orbitals and more, but not 15, from
+//                   8,192 (median 1.25 to 3.3 times as fast, least 0.85 at the smallest;
+//                   below 0.6 to 1.3, least with the fewest orbitals); in FP64 with 15
+//                   orbitals, whose 8 row blocks run in a kernel of 9, from 131,072 (1.01 to
+//                   1.75; below 0.8 to 1.3)
+//   one block       with many single excitations of both spins (e alpha, b beta): FP32
+//                   b, e >= 40 and e + b >= 104 (19 orbitals, in a kernel of 20: 126): 1.05 to
+//                   2.7, else 0.65 to 1.16; FP64 b >= 40 and e >= 64, or with 17 and 18 orbitals
+//                   b >= 60 and e >= 52: 1.04 to 2, else 0.45 to 1.26
+// Elsewhere the tables, which cost more than the rest of cisigma_init, are not built,
+// except in deterministic mode, which has no other kernel.
+bool units_pay(const cisigma_ctx *c, int d, int rows, int rb) {
+    const auto &A = c->sp[0], &B = c->sp[1];
+    if (c->sym) return c->lay.ndet >= 4096;
+    if (!c->cas) {
+        const bool loose = rb == 9 && (rows + 15) / 16 == 8;
+        return c->lay.ndet >= (loose && d == 0 ? 131072 : loose || c->n < 12 ? 16384 : 8192);
+    }
+    const int e = A.nexc, b = B.nexc;
+    if (d == 1) return b >= 40 && e >= 40 && e + b >= (rb > 11 ? 126 : 104);
+    return (b >= 40 && e >= 64) || (rb <= 11 && b >= 60 && e >= 52);
+}
+
 int build_gas_owner(cisigma_ctx *c, bool one_block) {
     constexpr int WS = 33;
     auto &G = c->go;
@@ -792,6 +822,10 @@ int build_gas_owner(cisigma_ctx *c, bool one_block) {
         return CISIGMA_OK;
     const int mp = 16 * rb, kp = 4 * ks;
     if (size_t(mp) * WS * 8 >= 65536) return CISIGMA_OK;
+    // (10 x 5 and 13 x 7 are compiled as sizes to pad to, the others each for a space)
+    const bool made = ks == (A.nexc + 1 + 3) / 4 && rb == (nrows + 15) / 16 && !(ks == 10 && rb == 5) && !(ks == 13 && rb == 7);
+    for (int d = 0; d < 2; ++d) G.pays[d] = made || one_block || units_pay(c, d, nrows, rb);
+    if (!G.pays[0] && !G.pays[1] && !c->deterministic) return CISIGMA_OK;
     // type moved by one electron from space `from` to space `to` (-1: no such type)
     auto moved = [&](const cis::SpinTables &S, int t, int from, int to) {
         if (from == to) return t;
@@ -930,6 +964,7 @@ int build_gas_owner(cisigma_ctx *c, bool one_block) {
     };
     for (int d = 0; d < 2; ++d) {
         const size_t es = d == 0 ? 8 : 4;
+        if (!G.pays[d] && !c->deterministic) continue;
         // the kernel addresses C with 32-bit element offsets (its zero row included)
         if (uint64_t(c->pl[0].size) + uint64_t(ldmax) >= (uint64_t(1) << 32)) continue;
         // (point-group spaces: one more word per beta type, the kernel's per-type k-step masks,
@@ -1203,9 +1238,9 @@ int64_t ys_rows_elems(const cisigma_ctx *c) {
 // dtype's workspace; one-block spaces (and GAS spaces with owner tables) add
 // one zero row after the copy (rows the owner-computes sigma_3 and the
 // pair-product kernels read in place of missing ones)
-void workspace_copy_sizes(const cisigma_ctx *c, size_t es, size_t *na, size_t *nb) {
+void workspace_copy_sizes(const cisigma_ctx *c, size_t es, size_t *na, size_t *nb, bool units) {
     int64_t zero_row = c->cas ? c->pl[0].ld[0] : 0;
-    if (c->go.ks) for (int ld : c->pl[0].ld) zero_row = std::max<int64_t>(zero_row, ld);
+    if (units) for (int ld : c->pl[0].ld) zero_row = std::max<int64_t>(zero_row, ld);
     *na = size_t(std::max<int64_t>(c->pl[0].size + zero_row, 1)) * es;
     *nb = size_t(std::max<int64_t>(c->pl[1].size + (c->cas ? c->pl[1].ld[0] : 0), 1)) * es;
 }
@@ -1214,7 +1249,7 @@ void workspace_copy_sizes(const cisigma_ctx *c, size_t es, size_t *na, size_t *n
 // materialised same-spin rows, which take what is free)
 size_t workspace_copy_bytes(const cisigma_ctx *c, size_t es) {
     size_t na = 0, nb = 0;
-    workspace_copy_sizes(c, es, &na, &nb);
+    workspace_copy_sizes(c, es, &na, &nb, true);
     return 2 * (na + nb);
 }
 
@@ -1259,7 +1294,7 @@ int ensure_workspace(cisigma_ctx *c, int dtype) {
     if (W.ready) return CISIGMA_OK;
     size_t es = dtype == CISIGMA_FP32 ? 4 : 8;
     size_t na = 0, nb = 0;
-    workspace_copy_sizes(c, es, &na, &nb);
+    workspace_copy_sizes(c, es, &na, &nb, true);   // (an option may build the owner tables later)
     size_t fr = 0, tot = 0;
     if (hipMemGetInfo(&fr, &tot) == hipSuccess && 2 * (na + nb) + (64u << 20) > fr)
         return cis_set_error(c, CISIGMA_ENOMEM, "apply: not enough device memory for the sigma workspace");
@@ -1431,7 +1466,7 @@ int apply_sigma_noalloc(cisigma_ctx *c, const void *C, void *sigma, int dtype, h
     if (!c->scratch) return cis_set_error(c, CISIGMA_EDEVICE, "apply_noalloc: scratch address not available");
     const size_t es = dtype == CISIGMA_FP32 ? 4 : 8;
     size_t na = 0, nb = 0;
-    workspace_copy_sizes(c, es, &na, &nb);
+    workspace_copy_sizes(c, es, &na, &nb, c->go.ks != 0);
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
     const size_t copies = 2 * up(na) + 2 * up(nb);
     if (copies > kNoallocScratchBytes)
@@ -2237,7 +2272,11 @@ CIS_API int cisigma_set_option(cisigma_ctx *ctx, int key, double value) {
         case CISIGMA_OPT_DETERMINISTIC:
             if (value != 0 && value != 1)
                 return cis_set_error(ctx, CISIGMA_EINVAL, "set_option: deterministic must be 0 or 1");
-            ctx->deterministic = int(value);
+            if (value != ctx->deterministic) {
+                ctx->deterministic = int(value);
+                // (units that only this mode takes)
+                if (!ctx->go.pays[0] || !ctx->go.pays[1]) return cis::rebuild_gas_owner(ctx);
+            }
             return CISIGMA_OK;
         case CISIGMA_OPT_UNIT_LAUNCH:
             if (value != 0 && value != 1) return cis_set_error(ctx, CISIGMA_EINVAL, "set_option: unit launch must be 0 or 1");

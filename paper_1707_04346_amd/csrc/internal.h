@@ -168,6 +168,7 @@ struct GasUnit {
 };
 struct GasOwner {
     int ks = 0, rb = 0;                  // k steps (4 gathered rows each), 16-row blocks of W
+    bool pays[2] = {true, true};         // [FP64, FP32]: built without deterministic mode too
     int *d_slot = nullptr;               // [ntype_a][4*ks] excitation index of each gathered row,
                                          //   -2: the string itself, -1: none
     int *d_coff = nullptr;               // [ntype_a][ntype_b] first compact column of each allowed block, -1
