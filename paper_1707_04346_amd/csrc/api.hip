@@ -398,14 +398,13 @@ int build_active_tiles(cisigma_ctx *c) {
 // A group may span at most four lanes (the kernel carries partial sums over
 // three).  One encoding per element size.  Without a plan (a shape no kernel
 // covers) the general kernel runs.
-// Where the contributions of one source tile come from and go to.
+// Where the contributions of the source tiles come from and go to.
 struct PlanSpec {
-    int ntile = 0;                                 // 32-column source tiles
-    std::function<int(int, int)> source;           // (tile, column) -> beta string index, -1: none
-    std::function<int(int, int)> w_row;            // orbital pair (k >= l) -> W row
-    std::function<int(int)> target;                // beta string -> sigma slot, -1: outside (dropped); none: identity
+    int ntile = 0;                                 // source tiles of at most 32 columns
+    std::function<std::pair<int, int>(int)> source;   // tile -> first beta string, strings
+    const std::vector<int> *w_row = nullptr;       // packed pair -> W row; none: identity
+    std::vector<int> target;                       // beta string -> sigma slot, -1: outside (dropped); empty: identity
     int nvirt = 0;                                 // sigma slots (targets < nvirt; discard slots nvirt + lane)
-    uint32_t unit[2] = {8, 4};                     // bytes per unit of the slot field: [FP64, FP32]
     std::function<int(int)> width;                 // entries per lane the kernel compiles for `need`, 0: none
 };
 
@@ -452,57 +451,70 @@ void for_tiles(int n, const F &f) {
     if (err) std::rethrow_exception(err);
 }
 
-int plan_items(cisigma_ctx *c, const PlanSpec &ps, const std::vector<uint32_t> &exc, const std::vector<uint32_t> &str,
-               PlanTiles &out) {
+// One tile of a plan: its items in `tile`, returns the entries per lane that its four
+// wave ranges need.
+int plan_tile(const cisigma_ctx *c, const PlanSpec &ps, int t, const std::vector<uint32_t> &exc,
+              const std::vector<uint32_t> &str, std::vector<PlanItem> &tile) {
     constexpr int WS = 33;
     const auto &B = c->sp[1];
+    const std::pair<int, int> src = ps.source(t);
+    tile.clear();
+    std::vector<PlanItem> list;                    // in the order of the strings
+    list.reserve(size_t(src.second) * size_t(B.nexc + B.nel));
+    std::vector<uint32_t> at(size_t(ps.nvirt) + 1, 0);   // first item of each slot
+    for (int col = 0; col < src.second; ++col) {
+        const int Jb = src.first + col;
+        auto push = [&](int Ib, int k, int l, uint32_t neg) {
+            const int slot = ps.target.empty() ? Ib : ps.target[size_t(Ib)];
+            if (slot < 0) return;
+            const int pair = cis::pair_ge(std::max(k, l), std::min(k, l));
+            list.push_back({uint32_t(slot), uint32_t((ps.w_row ? (*ps.w_row)[size_t(pair)] : pair) * WS + col), neg, 0u, 0u});
+            ++at[size_t(slot) + 1];
+        };
+        for (int e = 0; e < B.nexc; ++e) {
+            const uint32_t w = exc[size_t(Jb) * B.nexc + e];
+            if (w == cis::kExcNone) continue;
+            push(int(w >> 11), (w >> 6) & 31, (w >> 1) & 31, w & 1u);
+        }
+        for (uint32_t b = str[Jb]; b; b &= b - 1) {
+            const int k = __builtin_ctz(b);
+            push(Jb, k, k, 0u);
+        }
+    }
+    std::vector<uint32_t> group;                   // sizes
+    for (size_t q = 0; q < size_t(ps.nvirt); ++q) {
+        if (at[q + 1] > 0) group.push_back(at[q + 1]);
+        at[q + 1] += at[q];
+    }
+    tile.resize(list.size());
+    for (const PlanItem &it : list) tile[at[it.tgt]++] = it;   // (afterwards at: the last item's next)
+    for (size_t i = 0; i < tile.size(); ++i) {
+        tile[i].start = i == 0 || tile[i].tgt != tile[i - 1].tgt;
+        tile[i].end = i + 1 == tile.size() || tile[i].tgt != tile[i + 1].tgt;
+    }
+    // smallest ew whose wave capacity 64*ew packs the groups into four ranges
+    auto fits = [&](size_t cap) {
+        int ranges = 1;
+        size_t cur = 0;
+        for (size_t g : group) {
+            if (g > cap) return false;
+            if (cur + g > cap) { ++ranges; cur = 0; }
+            cur += g;
+        }
+        return ranges <= 4;
+    };
+    int need = std::max<int>(1, int((tile.size() + 255) / 256));
+    while (!fits(size_t(64) * need)) ++need;
+    return need;
+}
+
+void plan_items(const cisigma_ctx *c, const PlanSpec &ps, const std::vector<uint32_t> &exc,
+                const std::vector<uint32_t> &str, PlanTiles &out) {
     out.tiles.assign(ps.ntile, {});
     std::vector<int> needs(size_t(ps.ntile), 1);
-    for_tiles(ps.ntile, [&](int t) {
-        auto &tile = out.tiles[t];
-        for (int col = 0; col < 32; ++col) {
-            const int Jb = ps.source(t, col);
-            if (Jb < 0) continue;
-            auto push = [&](int Ib, int k, int l, uint32_t neg) {
-                const int slot = ps.target ? ps.target(Ib) : Ib;
-                if (slot < 0) return;
-                tile.push_back({uint32_t(slot), uint32_t(ps.w_row(std::max(k, l), std::min(k, l)) * WS + col), neg, 0u, 0u});
-            };
-            for (int e = 0; e < B.nexc; ++e) {
-                const uint32_t w = exc[size_t(Jb) * B.nexc + e];
-                if (w == cis::kExcNone) continue;
-                push(int(w >> 11), (w >> 6) & 31, (w >> 1) & 31, w & 1u);
-            }
-            for (uint32_t b = str[Jb]; b; b &= b - 1) {
-                const int k = __builtin_ctz(b);
-                push(Jb, k, k, 0u);
-            }
-        }
-        std::stable_sort(tile.begin(), tile.end(), [](const PlanItem &a, const PlanItem &b) { return a.tgt < b.tgt; });
-        for (size_t i = 0; i < tile.size(); ++i) {
-            tile[i].start = (i == 0 || tile[i].tgt != tile[i - 1].tgt);
-            tile[i].end = (i + 1 == tile.size() || tile[i].tgt != tile[i + 1].tgt);
-        }
-        // smallest ew whose wave capacity 64*ew packs the groups into four ranges
-        auto fits = [&](size_t cap) {
-            int ranges = 1;
-            size_t cur = 0;
-            for (size_t i = 0; i < tile.size();) {
-                size_t j = i + 1;
-                while (j < tile.size() && !tile[j].start) ++j;
-                const size_t g = j - i;
-                if (g > cap) return false;
-                if (cur + g > cap) { ++ranges; cur = 0; }
-                cur += g;
-                i = j;
-            }
-            return ranges <= 4;
-        };
-        while (!fits(size_t(64) * needs[t])) ++needs[t];
-    });
+    for_tiles(ps.ntile, [&](int t) { needs[t] = plan_tile(c, ps, t, exc, str, out.tiles[t]); });
     out.need = 1;
     for (int v : needs) out.need = std::max(out.need, v);
-    return CISIGMA_OK;
 }
 
 // wave ranges of a tile for entries-per-lane ew; false when a group would
@@ -538,52 +550,39 @@ bool plan_fits(const PlanTiles &pt, int ew) {
     return true;
 }
 
-// plan words of every tile for entry count ew, appended to out[FP64], out[FP32];
-// with widths, tile t spreads its entries over widths[t] <= ew entries per lane
-// (the remaining words of each lane are padding; the header stays at index ew)
-void plan_emit(const PlanSpec &ps, const PlanTiles &pt, int ew, std::vector<uint32_t> (&out)[2],
-               const std::vector<int> *widths = nullptr) {
-    const size_t per_wave = size_t(ew + 1) * 64, per_tile = 4 * per_wave;
+// plan words of one tile for entry count ew in elements of es bytes, to PL (4 * (ew + 1) * 64
+// words): it spreads its entries over w <= ew entries per lane (the remaining words of
+// each lane are padding; the header stays at index ew)
+void plan_emit(const PlanSpec &ps, const std::vector<PlanItem> &tile, int ew, int w, uint32_t es, uint32_t *PL) {
+    const size_t per_wave = size_t(ew + 1) * 64;
     std::vector<std::pair<size_t, size_t>> rg;
-    for (int es_i = 0; es_i < 2; ++es_i) {
-        const uint32_t es = es_i == 0 ? 8 : 4;   // [0]: FP64, [1]: FP32
-        auto &PL = out[es_i];
-        const size_t base0 = PL.size();
-        PL.resize(base0 + per_tile * pt.tiles.size());
-        for (size_t t = 0; t < pt.tiles.size(); ++t) {
-            const auto &tile = pt.tiles[t];
-            const int w = widths ? (*widths)[t] : ew;
-            plan_ranges(tile, w, rg);
-            for (int wv = 0; wv < 4; ++wv) {
-                const size_t base = base0 + (t * 4 + wv) * per_wave;
-                const size_t i = wv < int(rg.size()) ? rg[wv].first : 0, j = wv < int(rg.size()) ? rg[wv].second : 0;
-                for (int lane = 0; lane < 64; ++lane) {
-                    const uint32_t spare = (uint32_t(ps.nvirt) + lane) * es;    // discard slot, bytes
-                    const uint32_t unit = ps.unit[es_i];                         // slot field unit, bytes
-                    uint32_t hdr = spare | 1u;
-                    for (int q = 0; q < ew; ++q) {
-                        const size_t e = i + size_t(lane) * w + q;
-                        // padding: the discard slot, and W element (0, 32) -- the tile's pad
-                        // column, which kernels that run padding entries keep at zero (a
-                        // padding entry may follow the part of a group that continues in
-                        // the next lane, when the tile's width is below ew)
-                        uint32_t word = ((spare / unit) << 16) | (32u * es);   // column 32 of the 33-wide W rows
-                        if (q < w && e < j) {
-                            const PlanItem &it = tile[e];
-                            const uint32_t slot = it.end ? it.tgt * es : spare;
-                            word = ((slot / unit) << 16) | (it.widx * es) | it.neg;
-                            if (q == 0 && !it.start) {
-                                // continued group: its end in this lane takes the carry
-                                hdr = spare;
-                                for (size_t f = e; f < i + size_t(lane + 1) * w && f < j; ++f)
-                                    if (tile[f].end) { hdr = tile[f].tgt * es; break; }
-                            }
-                        }
-                        PL[base + size_t(q) * 64 + lane] = word;
+    plan_ranges(tile, w, rg);
+    for (int wv = 0; wv < 4; ++wv) {
+        const size_t base = wv * per_wave;
+        const size_t i = wv < int(rg.size()) ? rg[wv].first : 0, j = wv < int(rg.size()) ? rg[wv].second : 0;
+        for (int lane = 0; lane < 64; ++lane) {
+            const uint32_t spare = uint32_t(ps.nvirt) + lane;   // discard slot, elements
+            uint32_t hdr = (spare * es) | 1u;
+            for (int q = 0; q < ew; ++q) {
+                const size_t e = i + size_t(lane) * w + q;
+                // padding: the discard slot, and W element (0, 32) -- the tile's pad
+                // column, which kernels that run padding entries keep at zero (a
+                // padding entry may follow the part of a group that continues in
+                // the next lane, when the tile's width is below ew)
+                uint32_t word = (spare << 16) | (32u * es);   // column 32 of the 33-wide W rows
+                if (q < w && e < j) {
+                    const PlanItem &it = tile[e];
+                    word = ((it.end ? it.tgt : spare) << 16) | (it.widx * es) | it.neg;
+                    if (q == 0 && !it.start) {
+                        // continued group: its end in this lane takes the carry
+                        hdr = spare * es;
+                        for (size_t f = e; f < i + size_t(lane + 1) * w && f < j; ++f)
+                            if (tile[f].end) { hdr = tile[f].tgt * es; break; }
                     }
-                    PL[base + size_t(ew) * 64 + lane] = hdr;
                 }
+                PL[base + size_t(q) * 64 + lane] = word;
             }
+            PL[base + size_t(ew) * 64 + lane] = hdr;
         }
     }
 }
@@ -607,9 +606,10 @@ int plan_width(const PlanSpec &ps, const PlanTiles &pt) {
 
 // Builds the FP64 encoding of a scatter plan of width ew into P.
 int make_scatter_plan(cisigma_ctx *c, const PlanSpec &ps, const PlanTiles &pt, int ew, cis::ScatterPlan &P) {
-    std::vector<uint32_t> plan[2];
-    plan_emit(ps, pt, ew, plan);
-    HIP_OR_FAIL(c, upload(&P.d_entries[0], plan[0]), "init: scatter plan");
+    const size_t per = size_t(4) * (ew + 1) * 64;
+    std::vector<uint32_t> plan(per * pt.tiles.size());
+    for (size_t t = 0; t < pt.tiles.size(); ++t) plan_emit(ps, pt.tiles[t], ew, ew, 8, plan.data() + per * t);
+    HIP_OR_FAIL(c, upload(&P.d_entries[0], plan), "init: scatter plan");
     P.ntile = ps.ntile;
     P.ew = ew;
     return CISIGMA_OK;
@@ -658,19 +658,15 @@ int build_scatter_plan(cisigma_ctx *c) {
         return CISIGMA_OK;
     PlanSpec ps;
     ps.ntile = ld / 32;
-    ps.source = [&](int t, int col) { const int Jb = t * 32 + col; return Jb < B.nstr ? Jb : -1; };
-    ps.w_row = [](int k, int l) { return cis::pair_ge(k, l); };
+    ps.source = [&](int t) { return std::make_pair(t * 32, std::max(0, std::min(32, B.nstr - t * 32))); };
     ps.nvirt = ld;
-    ps.unit[0] = 8;
-    ps.unit[1] = 1;
     const int anexc = c->sp[0].nexc, npair = c->npair;
     ps.width = [=](int need) { return cis::sigma_ab_owner_width(anexc, npair, need); };
     std::vector<uint32_t> exc, str;
     int rc = plan_tables(c, exc, str);
     if (rc) return rc;
     PlanTiles pt;
-    rc = plan_items(c, ps, exc, str, pt);
-    if (rc) return rc;
+    plan_items(c, ps, exc, str, pt);
     const int ew = plan_width(ps, pt);
     if (ew && c->n <= 10) {
         rc = make_scatter_plan(c, ps, pt, ew, c->plan);
@@ -962,6 +958,17 @@ int build_gas_owner(cisigma_ctx *c, bool one_block) {
         if (hi > lo) cut.push_back(hi);
         return cut;
     };
+    // the units of both precisions, each with the plan of its column range (the
+    // precisions share those that they cut alike)
+    struct UnitPlan {
+        PlanSpec ps;
+        int ta, lo, hi;
+        PlanTiles pt;                                    // the tiles with a target in the range
+        std::vector<std::array<uint32_t, 4>> act;        // their entries of tact
+        std::vector<int> widths;                         // entries per lane that hold each, at most 16
+    };
+    std::vector<UnitPlan> plans;
+    std::vector<size_t> use[2];
     for (int d = 0; d < 2; ++d) {
         const size_t es = d == 0 ? 8 : 4;
         if (!G.pays[d] && !c->deterministic) continue;
@@ -974,122 +981,127 @@ int build_gas_owner(cisigma_ctx *c, bool one_block) {
         if (fixed >= 160 * 1024) continue;
         int cmax = int(std::min<size_t>((160 * 1024 - fixed) / es, 65536 - 64 - 1));
         if (c->unit_cols > 0) cmax = std::min(cmax, c->unit_cols);
-        std::vector<cis::GasUnit> units;
-        std::vector<PlanSpec> specs;
-        std::vector<PlanTiles> pts;
-        std::vector<std::vector<std::array<uint32_t, 4>>> uact;
-        int need = 1;
         for (int ta = 0; ta < A.ntype; ++ta) {
             if (tact[ta].empty() || A.tcount[ta] == 0) continue;
             const std::vector<int> cut = cuts_of(ta, cmax);
             for (size_t ci = 0; ci + 1 < cut.size(); ++ci) {
                 const int lo = cut[ci], hi = cut[ci + 1];
-                const auto &ta_tiles = tact[ta];
-                PlanSpec ps;
-                ps.ntile = int(ta_tiles.size());
-                ps.source = [&, ta](int t, int col) {
-                    const int u = int(ta_tiles[t][3] & 255u), cc = int(ta_tiles[t][3] >> 8) + col;
-                    return cc < B.tcount[u] ? B.tstart[u] + cc : -1;
+                size_t k = 0;
+                while (k < plans.size() && !(plans[k].ta == ta && plans[k].lo == lo && plans[k].hi == hi)) ++k;
+                use[d].push_back(k);
+                if (k < plans.size()) continue;
+                UnitPlan P;
+                P.ta = ta;
+                P.lo = lo;
+                P.hi = hi;
+                P.ps.ntile = int(tact[ta].size());
+                P.ps.source = [&, ta](int t) {
+                    const int u = int(tact[ta][t][3] & 255u), cc = int(tact[ta][t][3] >> 8);
+                    return std::make_pair(B.tstart[u] + cc, std::min(32, B.tcount[u] - cc));
                 };
-                ps.w_row = [&](int k, int l) { return row_of[cis::pair_ge(k, l)]; };
-                ps.target = [&, ta, lo, hi](int Ib) {
-                    const int u = btype[Ib], o = coff[size_t(ta) * ntb + u];
-                    if (o < 0) return -1;
-                    const int x = o + (Ib - B.tstart[u]);
-                    return x >= lo && x < hi ? x - lo : -1;
-                };
-                ps.nvirt = hi - lo;
-                ps.unit[0] = 8;
-                ps.unit[1] = 4;
-                PlanTiles pt;
-                rc = plan_items(c, ps, exc, str, pt);
-                if (rc) return rc;
-                // keep the tiles with at least one target in the range, each with the
-                // W row blocks its entries read (the only ones it multiplies)
-                std::vector<std::array<uint32_t, 4>> keep;
-                PlanTiles kept;
-                for (size_t t = 0; t < pt.tiles.size(); ++t)
-                    if (!pt.tiles[t].empty()) {
-                        uint32_t used = 0;
-                        for (const auto &it : pt.tiles[t]) used |= 1u << (it.widx / WS / 16);
-                        keep.push_back(ta_tiles[t]);
-                        keep.back()[2] = used;
-                        kept.tiles.push_back(std::move(pt.tiles[t]));
-                    }
-                if (keep.empty()) continue;
-                need = std::max(need, pt.need);
-                cis::GasUnit gu;
-                gu.ta = ta;
-                gu.lo = lo;
-                gu.hi = hi;
-                units.push_back(gu);
-                specs.push_back(ps);
-                pts.push_back(std::move(kept));
-                uact.push_back(std::move(keep));
+                P.ps.w_row = &row_of;
+                P.ps.target.assign(size_t(B.nstr), -1);
+                for (int u = 0; u < ntb; ++u) {
+                    const int o = coff[size_t(ta) * ntb + u];
+                    if (o < 0) continue;
+                    for (int x = std::max(o, lo); x < std::min(o + B.tcount[u], hi); ++x)
+                        P.ps.target[size_t(B.tstart[u] + x - o)] = x - lo;
+                }
+                P.ps.nvirt = hi - lo;
+                P.pt.tiles.resize(size_t(P.ps.ntile));
+                plans.push_back(std::move(P));
             }
         }
-        if (units.empty()) continue;
+    }
+    {
+        // every tile of every plan
+        std::vector<std::pair<size_t, int>> job;
+        for (size_t k = 0; k < plans.size(); ++k)
+            for (int t = 0; t < plans[k].ps.ntile; ++t) job.push_back({k, t});
+        std::vector<int> need(job.size()), width(job.size(), 16);
+        for_tiles(int(job.size()), [&](int x) {
+            UnitPlan &P = plans[job[x].first];
+            auto &tile = P.pt.tiles[size_t(job[x].second)];
+            need[x] = plan_tile(c, P.ps, job[x].second, exc, str, tile);
+            std::vector<std::pair<size_t, size_t>> rg;
+            for (int w = need[x]; w < 16; ++w)
+                if (plan_ranges(tile, w, rg)) { width[x] = w; break; }
+        });
+        // keep the tiles with at least one target in the range, each with the
+        // W row blocks its entries read (the only ones it multiplies)
+        std::vector<size_t> kept(plans.size(), 0);
+        for (size_t x = 0; x < job.size(); ++x) {
+            UnitPlan &P = plans[job[x].first];
+            auto &tile = P.pt.tiles[size_t(job[x].second)];
+            if (tile.empty()) continue;
+            uint32_t used = 0;
+            for (const auto &it : tile) used |= 1u << (it.widx / WS / 16);
+            P.act.push_back(tact[P.ta][size_t(job[x].second)]);
+            P.act.back()[2] = used;
+            P.widths.push_back(width[x]);
+            P.pt.need = std::max(P.pt.need, need[x]);
+            const size_t at = kept[job[x].first]++;
+            if (at != size_t(job[x].second)) P.pt.tiles[at] = std::move(tile);
+        }
+        for (size_t k = 0; k < plans.size(); ++k) plans[k].pt.tiles.resize(kept[k]);
+    }
+    for (int d = 0; d < 2; ++d) {
+        const uint32_t es = d == 0 ? 8 : 4;
+        std::vector<const UnitPlan *> up;
+        int need = 1;
+        for (size_t k : use[d]) {
+            if (plans[k].act.empty()) continue;
+            up.push_back(&plans[k]);
+            need = std::max(need, plans[k].pt.need);
+        }
+        if (up.empty()) continue;
         // splitting rows repeats the gathers of every tile that reaches several
         // units, and its products where they lead into several: give the
         // precision to the general kernel when the row-block products more than
         // double
         {
             double split = 0, whole = 0;
-            for (size_t k = 0; k < units.size(); ++k)
-                for (const auto &e : uact[k]) split += double(__builtin_popcount(e[2])) * A.tcount[units[k].ta];
+            for (const UnitPlan *P : up)
+                for (const auto &e : P->act) split += double(__builtin_popcount(e[2])) * A.tcount[P->ta];
             for (int ta = 0; ta < A.ntype; ++ta)
                 for (const auto &e : tact[ta]) whole += double(__builtin_popcount(e[2])) * A.tcount[ta];
             if (split > 2.0 * whole) continue;
         }
         // longest rows of work first (one launch covers every unit; the longest workgroups start first)
-        {
-            std::vector<size_t> ord(units.size());
-            for (size_t k = 0; k < ord.size(); ++k) ord[k] = k;
-            std::stable_sort(ord.begin(), ord.end(), [&](size_t x, size_t y) { return uact[x].size() > uact[y].size(); });
-            std::vector<cis::GasUnit> u2;
-            std::vector<PlanSpec> s2;
-            std::vector<PlanTiles> p2;
-            std::vector<std::vector<std::array<uint32_t, 4>>> a2;
-            for (size_t k : ord) {
-                u2.push_back(units[k]);
-                s2.push_back(specs[k]);
-                p2.push_back(std::move(pts[k]));
-                a2.push_back(std::move(uact[k]));
-            }
-            units.swap(u2);
-            specs.swap(s2);
-            pts.swap(p2);
-            uact.swap(a2);
-        }
+        std::stable_sort(up.begin(), up.end(), [](const UnitPlan *x, const UnitPlan *y) { return x->act.size() > y->act.size(); });
         int ew = 0;
         for (int cand : {cis::sigma_ab_gas_width(ks, rb, need), 16}) {
             if (cand < need || cis::sigma_ab_gas_width(ks, rb, cand) != cand) continue;
             bool ok = true;
-            for (size_t k = 0; k < pts.size() && ok; ++k) ok = plan_fits(pts[k], cand);
+            for (size_t k = 0; k < up.size() && ok; ++k) ok = plan_fits(up[k]->pt, cand);
             if (ok) { ew = cand; break; }
         }
         if (ew == 0) continue;
-        std::vector<uint32_t> plan[2], act;
-        int tile0 = 0;
-        std::vector<std::pair<size_t, size_t>> rgw;
-        for (size_t k = 0; k < units.size(); ++k) {
-            // each tile at the fewest entries per lane that hold it (the kernel reads no more)
-            std::vector<int> widths(pts[k].tiles.size(), ew);
-            for (size_t t = 0; t < widths.size(); ++t)
-                for (int w = 1; w < ew; ++w)
-                    if (plan_ranges(pts[k].tiles[t], w, rgw)) { widths[t] = w; break; }
-            plan_emit(specs[k], pts[k], ew, plan, &widths);
+        std::vector<cis::GasUnit> units(up.size());
+        std::vector<uint32_t> act;
+        std::vector<std::pair<size_t, size_t>> job;      // plan tile -> unit, its tile
+        for (size_t k = 0; k < up.size(); ++k) {
+            units[k].ta = up[k]->ta;
+            units[k].lo = up[k]->lo;
+            units[k].hi = up[k]->hi;
             units[k].act0 = int(act.size() / 4);
-            units[k].nact = int(uact[k].size());
-            for (size_t t = 0; t < uact[k].size(); ++t) {
-                act.push_back(uint32_t(tile0 + int(t)) | (uint32_t(widths[t]) << 24));
-                act.push_back(uact[k][t][1]);
-                act.push_back(uact[k][t][2]);
-                act.push_back(uact[k][t][3]);
+            units[k].nact = int(up[k]->act.size());
+            for (size_t t = 0; t < up[k]->act.size(); ++t) {
+                // each tile at the fewest entries per lane that hold it (the kernel reads no more)
+                const auto &e = up[k]->act[t];
+                act.insert(act.end(), {uint32_t(job.size()) | (uint32_t(std::min(up[k]->widths[t], ew)) << 24), e[1], e[2], e[3]});
+                job.push_back({k, t});
             }
-            tile0 += int(uact[k].size());
         }
-        if (size_t(tile0) * 4 * (ew + 1) * 64 * 4 >= (size_t(1) << 31)) continue;
+        const int tile0 = int(job.size());
+        const size_t per = size_t(4) * (ew + 1) * 64;
+        if (job.size() * per * 4 >= (size_t(1) << 31)) continue;
+        std::vector<uint32_t> plan(per * job.size());
+        for_tiles(tile0, [&](int x) {
+            const UnitPlan &P = *up[job[x].first];
+            const size_t t = job[x].second;
+            plan_emit(P.ps, P.pt.tiles[t], ew, std::min(P.widths[t], ew), es, plan.data() + per * size_t(x));
+        });
         std::vector<int> utab;
         int nblk = 0, maxc = 0;
         G.launch[d].clear();
@@ -1099,7 +1111,7 @@ int build_gas_owner(cisigma_ctx *c, bool one_block) {
             nblk += A.tcount[un.ta];
             maxc = std::max(maxc, un.hi - un.lo);
         }
-        HIP_OR_FAIL(c, upload(&G.plan[d].d_entries[d], plan[d]), "init: GAS owner tables");
+        HIP_OR_FAIL(c, upload(&G.plan[d].d_entries[d], plan), "init: GAS owner tables");
         HIP_OR_FAIL(c, upload(&G.d_act[d], act), "init: GAS owner tables");
         HIP_OR_FAIL(c, upload(&G.d_units[d], utab), "init: GAS owner tables");
         G.nblocks[d] = nblk;
