@@ -1290,15 +1290,24 @@ bool ys_shape(const cisigma_ctx *c, size_t *rows, size_t *cols) {
 // the other: only for rows that stay in the Infinity Cache (256 MB) until they are
 // gathered.  There a sigma is a few launches of a few microseconds each: with both
 // spins in one launch a sigma of CAS(6,6) takes 18.9 instead of 24.6 us, of CAS(12,12) in
-// FP32 156 instead of 162; larger ones gain nothing.
+// FP32 156 instead of 162; larger ones gain nothing.  The joint launch multiplies both
+// spins in the shape of the spin with more pairs: not where that adds more than 8 million
+// (k step, row block, column) products in FP32 or 6 million in FP64 (36 pairs of unlike
+// spins in 10 to 14 orbitals: below, it saves 2 to 9 us, 3 us more at most; above 12 million
+// it costs up to 74 us; 4 alpha and 11 beta of 14 orbitals, 168 million: a sigma 398
+// instead of 235 us).
 size_t ys_both_bytes(const cisigma_ctx *c, size_t es) {
     size_t rows = 0, cols = 0, total = 0;
     if (!ys_shape(c, &rows, &cols)) return 0;
+    int ks[2], mbl[2];
     for (int s = 0; s < 2; ++s) {
-        if (c->sp[s].nel < 2) return 0;
+        if (c->sp[s].nel < 2 || !cis::same_spin_shape_for(c->sp[s].npv, &ks[s], &mbl[s])) return 0;
         total += ys_spin_bytes(c, s, es);
     }
-    return total <= (size_t(224) << 20) ? total : 0;
+    double extra = 0;
+    for (int s = 0; s < 2; ++s)
+        extra += double(c->sp[s].nK) * double(c->pl[s].ld[0]) * (std::max(ks[0], ks[1]) * std::max(mbl[0], mbl[1]) - ks[s] * mbl[s]);
+    return total <= (size_t(224) << 20) && extra <= (es == 4 ? 8e6 : 6e6) ? total : 0;
 }
 
 int ensure_workspace(cisigma_ctx *c, int dtype) {
