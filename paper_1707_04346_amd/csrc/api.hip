@@ -1293,7 +1293,7 @@ bool ys_shape(const cisigma_ctx *c, size_t *rows, size_t *cols) {
 // FP32 156 instead of 162; larger ones gain nothing.  The joint launch multiplies both
 // spins in the shape of the spin with more pairs: not where that adds more than 8 million
 // (k step, row block, column) products in FP32 or 6 million in FP64 (36 pairs of unlike
-// spins in 10 to 14 orbitals: below, it saves 2 to 9 us, 3 us more at most; above 12 million
+// spins in 10 to 14 orbitals: below it saves up to 16 us and costs 6 at most; above 12 million
 // it costs up to 74 us; 4 alpha and 11 beta of 14 orbitals, 168 million: a sigma 398
 // instead of 235 us).
 size_t ys_both_bytes(const cisigma_ctx *c, size_t es) {

@@ -55,13 +55,14 @@ struct AbsArgs {
     int anexc, n, kp, npair, Na, ld;
 };
 
-// sum_{j in Ia} (jj|kl) for the kl pair of row m
+// sum_{j in Ia} (jj|kl) for the kl pair of row m < npair: all loads at once
 __device__ __forceinline__ float self_coef(const AbsArgs &p, uint32_t xa, int m) {
+    float x[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) x[j] = p.gp[(j < p.n ? j * p.n + j : 0) * p.kp + m];
     float val = 0;
-    for (uint32_t b = xa; b; b &= b - 1) {
-        const int j = __ffs(b) - 1;
-        val += p.gp[int64_t(j * p.n + j) * p.kp + m];
-    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) val += (xa >> j) & 1u ? x[j] : 0.0f;
     return val;
 }
 
@@ -79,36 +80,45 @@ __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int
     float A32[EX ? NRA : 1][EX ? KS : 1][8];
     uint32_t boff[KS][8];
     const uint32_t col = uint32_t(cb * 16 + lr);
+    // (without branches, so that the loads are in flight together: CAS(12,12) 107 -> 103 us,
+    // 8 alpha and 1 beta electrons in 16 orbitals, a tile a workgroup, 476 -> 397)
+    uint32_t ex[KS][8];
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int k = 32 * s + 8 * lk + j;
+            ex[s][j] = kExcNone;
+            if (p.anexc > 0) {                     // (uniform)
+                const uint32_t e = p.aexc[int64_t(Ia) * p.anexc + (k < p.anexc ? k : 0)];
+                if (k < p.anexc) ex[s][j] = e;
+            }
+        }
+    float self[NRA];
+#pragma unroll
+    for (int r = 0; r < NRA; ++r) {
+        const int m = (rb0 + r) * 16 + lr;
+        const float v = self_coef(p, xa, m < p.npair ? m : 0);
+        self[r] = r < NR && m < p.npair ? v : 0.0f;
+    }
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
         float a[NRA][8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int k = 32 * s + 8 * lk + j;
-            int J = p.Na;
-            const float *g = nullptr;
-            float sg = 0;
-            if (k < p.anexc) {
-                const uint32_t e = p.aexc[int64_t(Ia) * p.anexc + k];
-                if (e != kExcNone) {
-                    J = int(e >> 11);
-                    const int i = (e >> 6) & 31, jj = (e >> 1) & 31;   // <Ia|E_ij|Ja>, Ja = Ia - i + j
-                    g = p.gp + int64_t(i * p.n + jj) * p.kp;
-                    sg = (e & 1) ? -1.0f : 1.0f;
-                }
-            } else if (SELF && k == p.anexc) {
-                J = Ia;
-            }
+            const uint32_t e = ex[s][j];
+            const bool ok = e != kExcNone, own = SELF && k == p.anexc;
+            const int i = (e >> 6) & 31, jj = (e >> 1) & 31;   // <Ia|E_ij|Ja>, Ja = Ia - i + j
+            const int g = ok ? (i * p.n + jj) * p.kp : 0;
+            const int J = ok ? int(e >> 11) : own ? Ia : p.Na;
             boff[s][j] = (uint32_t(J) * uint32_t(p.ld) + col) * 4u;   // < cp_bytes
 #pragma unroll
             for (int r = 0; r < NRA; ++r) {
                 const int m = (rb0 + r) * 16 + lr;
-                float val = 0;
-                if (r < NR && m < p.npair) {
-                    if (g) val = sg * g[m];
-                    else if (SELF && k == p.anexc) val = self_coef(p, xa, m);
-                }
-                a[r][j] = val;
+                const bool row = r < NR && m < p.npair;
+                const float v = p.gp[g + (row ? m : 0)];
+                a[r][j] = ok && row ? ((e & 1) ? -v : v) : own ? self[r] : 0.0f;
             }
         }
 #pragma unroll
@@ -121,16 +131,8 @@ __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int
             }
         }
     }
-    float dI[NRA];
     uint32_t boffI = 0;
-    if constexpr (!SELF) {
-#pragma unroll
-        for (int r = 0; r < NRA; ++r) {
-            const int m = (rb0 + r) * 16 + lr;
-            dI[r] = r < NR && m < p.npair ? self_coef(p, xa, m) : 0.0f;
-        }
-        boffI = (uint32_t(Ia) * uint32_t(p.ld) + uint32_t(cb * 16 + 4 * lk)) * 4u;
-    }
+    if constexpr (!SELF) boffI = (uint32_t(Ia) * uint32_t(p.ld) + uint32_t(cb * 16 + 4 * lk)) * 4u;
     const __amdgpu_buffer_rsrc_t cr = buffer_of(p.cp, p.cp_bytes);
     const __amdgpu_buffer_rsrc_t pr = buffer_of(p.plan, p.plan_bytes);
     const int ntile = p.ld / kNT;
@@ -208,7 +210,7 @@ __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int
             floatx4 v = acc[r];
             if constexpr (!SELF)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = __builtin_fmaf(dI[r], cI[i], v[i]);
+                for (int i = 0; i < 4; ++i) v[i] = __builtin_fmaf(self[r], cI[i], v[i]);
             *reinterpret_cast<floatx4 *>(W + ((rb0 + r) * 16 + lr) * kWS + cb * 16 + 4 * lk) = v;
         }
     };
@@ -247,12 +249,12 @@ __global__ __launch_bounds__(256, 2) void k_sigma_ab_s(AbsArgs p) {
     float *sig = W + MP * kWS + kProgWaves * 64;           // [ld + 64]: slots ld.. take discarded writes
     const int Ia = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wide = *p.wide;                              // (in flight while the row is read)
     float *row = p.sp + int64_t(Ia) * p.ld;
     for (int c = tid * 4; c < p.ld; c += 1024)
         *reinterpret_cast<floatx4 *>(sig + c) = *reinterpret_cast<const floatx4 *>(row + c);
     for (int r = tid; r < MP; r += 256) W[r * kWS + kNT] = 0.0f;   // pad column: unused references read it
-    const int ex = p.exact | __builtin_amdgcn_readfirstlane(*p.wide);   // one answer for the whole launch
-    if (ex) {
+    if (p.exact | __builtin_amdgcn_readfirstlane(wide)) {   // one answer for the whole launch
         if (wave < 2) abs_body<KS, R0, RB, PG, SELF, true>(p, W, Ia, wave & 1, 0, wave, lane);
         else abs_body<KS, R1, RB, PG, SELF, true>(p, W, Ia, wave & 1, R0, wave, lane);
     } else {
