@@ -136,7 +136,7 @@ void free_ctx(cisigma_ctx *c) {
         (void)hipFree(c->d_tstart[s]);
         (void)hipFree(c->d_v64[s]); (void)hipFree(c->d_v32[s]);
         auto &W = c->ws[s];
-        (void)hipFree(W.cp); (void)hipFree(W.sp); (void)hipFree(W.ct); (void)hipFree(W.st); (void)hipFree(W.ys);
+        (void)hipFree(W.cp); (void)hipFree(W.sp); (void)hipFree(W.ct); (void)hipFree(W.st); (void)hipFree(W.ys); (void)hipFree(W.part);
     }
     (void)hipFree(c->d_rdm);
     cis::drop_graphs(c);
@@ -1346,6 +1346,7 @@ int ensure_workspace(cisigma_ctx *c, int dtype) {
         if (both > budget) both = 0;
         if (chunk >= size_t(cis::kTileCols) && hipMalloc(&W.ys, std::max(rows * chunk * es, both)) == hipSuccess) {
             W.ys_chunk = int(chunk);
+            W.ys_bytes = std::max(rows * chunk * es, both);
             if (both) W.ys2 = static_cast<unsigned char *>(W.ys) + ys_spin_bytes(c, 0, es);
         } else {
             W.ys = nullptr;
@@ -1359,6 +1360,10 @@ int ensure_workspace(cisigma_ctx *c, int dtype) {
         else
             W.ys = nullptr;
     }
+    // sigma_3 works in the place of the stored rows, or else in its own
+    const size_t part = W.ys ? 0 : cis::sigma_ab_scratch(c, dtype);
+    if (part > 0 && hipMalloc(&W.part, part) == hipSuccess) W.part_bytes = part;
+    else W.part = nullptr;
     if (!c->side) {
         HIP_OR_FAIL(c, hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking), "apply: side stream");
         HIP_OR_FAIL(c, hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming), "apply: side stream");
@@ -1441,7 +1446,9 @@ int apply_sigma_ws(cisigma_ctx *c, const void *C, void *sigma, int dtype, hipStr
         HIP_OR_FAIL(c, hipEventRecord(c->ev_join, c->side), "apply: join");
     }
     {
-        const hipError_t e = launch_sigma_ab(c, W.cp, W.sp, dtype, s, W.wide);
+        // (the stored same-spin rows' place is free now, unless the other stream works in it)
+        const AbScratch scratch = !W.ys ? AbScratch{W.part, W.part_bytes} : fork ? AbScratch{} : AbScratch{W.ys, W.ys_bytes};
+        const hipError_t e = launch_sigma_ab(c, W.cp, W.sp, dtype, s, W.wide, scratch);
         if (e == hipErrorNotSupported && c->deterministic) {
             if (W.wide) HIP_OR_FAIL(c, launch_fill(W.wide, 1, CISIGMA_FP32, s), "apply: fill");   // (the output kernel's part)
             return cis_set_error(c, CISIGMA_EUNSUPPORTED,
@@ -1508,6 +1515,7 @@ int apply_sigma_noalloc(cisigma_ctx *c, const void *C, void *sigma, int dtype, h
         if (chunk >= size_t(cis::kTileCols)) {
             W.ys = base + copies;
             W.ys_chunk = int(chunk);
+            W.ys_bytes = kNoallocScratchBytes - copies;
             const size_t both = ys_both_bytes(c, es);
             if (both && both <= kNoallocScratchBytes - copies)
                 W.ys2 = static_cast<unsigned char *>(W.ys) + ys_spin_bytes(c, 0, es);
@@ -1516,6 +1524,10 @@ int apply_sigma_noalloc(cisigma_ctx *c, const void *C, void *sigma, int dtype, h
     const int64_t ny = ys_rows_elems(c);
     if (ny > 0 && size_t(ny) * es <= kNoallocScratchBytes - copies) W.ys = base + copies;
     if (dtype == CISIGMA_FP32 && c->d_wide) W.wide = c->d_wide + 1;
+    if (!W.ys) {
+        W.part = base + copies;
+        W.part_bytes = kNoallocScratchBytes - copies;
+    }
     W.ready = true;
     HIP_OR_FAIL(c, launch_fill(W.cp, int64_t(na / es), dtype, s), "apply_noalloc: clear");
     HIP_OR_FAIL(c, launch_fill(W.ct, int64_t(nb / es), dtype, s), "apply_noalloc: clear");
@@ -1644,7 +1656,7 @@ int release_workspace(cisigma_ctx *c, int dtype) {
     if (!W.ready) return CISIGMA_OK;
     HIP_OR_FAIL(c, hipDeviceSynchronize(), "release workspace");
     drop_graphs(c);   // captured graphs name these buffers
-    (void)hipFree(W.cp); (void)hipFree(W.sp); (void)hipFree(W.ct); (void)hipFree(W.st); (void)hipFree(W.ys);
+    (void)hipFree(W.cp); (void)hipFree(W.sp); (void)hipFree(W.ct); (void)hipFree(W.st); (void)hipFree(W.ys); (void)hipFree(W.part);
     W = Workspace{};
     return CISIGMA_OK;
 }

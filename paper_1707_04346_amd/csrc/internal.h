@@ -185,6 +185,12 @@ struct GasOwner {
     ScatterPlan plan[2];                 // plan[d].d_entries[d]: tiles of all units (slots: elements)
 };
 
+// device memory that sigma_3 may use until it returns
+struct AbScratch {
+    void *p = nullptr;
+    size_t bytes = 0;
+};
+
 struct Workspace {
     void *cp = nullptr;    // C in the alpha-major padded layout
     void *sp = nullptr;    // sigma accumulator, alpha-major padded layout
@@ -192,6 +198,9 @@ struct Workspace {
     void *st = nullptr;    // beta same-spin sigma, beta-major padded layout
     void *ys = nullptr;    // materialised same-spin rows (one-type spins), ys_chunk columns each
     int ys_chunk = 0;
+    size_t ys_bytes = 0;
+    void *part = nullptr;  // sums of sigma_3's slices where there are no stored rows
+    size_t part_bytes = 0;
     void *ys2 = nullptr;   // in ys: the beta rows beside the alpha ones (small spaces, all columns), else null
     int *wide = nullptr;   // FP32: set while C has elements outside the split products' range
     bool ready = false;
@@ -306,14 +315,18 @@ hipError_t build_diag_tables(cisigma_ctx *ctx);
 // padded K extent of the (ij|kl) table used by the alpha-beta kernel
 int sigma_ab_kp(int npair);
 hipError_t launch_fill(void *x, int64_t n, int dtype, hipStream_t s);
-hipError_t launch_sigma_ab(const cisigma_ctx *ctx, const void *C, void *sigma, int dtype, hipStream_t s, const int *wide);
+hipError_t launch_sigma_ab(const cisigma_ctx *ctx, const void *C, void *sigma, int dtype, hipStream_t s, const int *wide,
+                           const AbScratch &scratch);
 // owner-computes sigma_3 in FP64 (one-block spaces with a scatter plan): false when
 // the shape has no compiled kernel (nothing launched), else *err is the launch status
-bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *C, void *sigma, hipStream_t s, hipError_t *err);
+bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *C, void *sigma, const AbScratch &scratch, hipStream_t s,
+                           hipError_t *err);
 // the FP32 form (split products; plain ones where *wide or the integrals ask for them):
 // false when the space has no program (nothing launched)
-bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *C, void *sigma, const int *wide, hipStream_t s,
-                           hipError_t *err);
+bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *C, void *sigma, const int *wide, const AbScratch &scratch,
+                           hipStream_t s, hipError_t *err);
+// scratch bytes with which sigma_3 of a one-block space keeps the chip busy (0: without any)
+size_t sigma_ab_scratch(const cisigma_ctx *ctx, int dtype);
 // whether all integrals are in the split products' range
 bool split_integrals_exact(const std::vector<float> &g);
 // whether it is compiled for rb 16-row blocks of pairs and a scatter program

@@ -17,6 +17,7 @@
 // vector ALU while D is gathered.
 #include "internal.h"
 #include "mfma.h"
+#include "slices.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -300,7 +301,8 @@ int ks_for(int kp) {
 }
 
 template <typename T>
-hipError_t sigma_ab_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, const int *wide) {
+hipError_t sigma_ab_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, const int *wide,
+                      const AbScratch &scratch) {
     const auto &A = ctx->sp[0];
     const auto &B = ctx->sp[1];
     const auto &L = ctx->pl[0];
@@ -341,8 +343,8 @@ hipError_t sigma_ab_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStrea
         // path 2 asks for the units), else the GAS owner kernel (which splits long rows
         // over units), else the general kernel
         const bool one = ctx->cas && ctx->ab_mode != 2 &&
-                         (sizeof(T) == 4 ? launch_sigma_ab_split(ctx, cp, sp, wide, s, &e)
-                                         : launch_sigma_ab_owner(ctx, cp, sp, s, &e));
+                         (sizeof(T) == 4 ? launch_sigma_ab_split(ctx, cp, sp, wide, scratch, s, &e)
+                                         : launch_sigma_ab_owner(ctx, cp, sp, scratch, s, &e));
         if (one || launch_sigma_ab_gas(ctx, cp, sp, dt, s, &e)) {
             if (e == hipSuccess) {
                 int &f = const_cast<cisigma_ctx *>(ctx)->last_path[sizeof(T) == 4];
@@ -374,10 +376,19 @@ int sigma_ab_kp(int npair) {
     return ks > 0 ? 4 * ks : ((npair + 3) / 4) * 4;
 }
 
+size_t sigma_ab_scratch(const cisigma_ctx *ctx, int dtype) {
+    if (!ctx->prog.d_words) return 0;
+    const bool f32 = dtype == CISIGMA_FP32;
+    const size_t es = f32 ? 4 : 8;
+    const int ld = int(ctx->pl[0].ld[0]), Na = ctx->sp[0].nstr;
+    return size_t(slices(Na, ld, es, ~size_t(0), f32 ? kPlaces32 : kPlaces64) - 1) * size_t(Na) * size_t(ld) * es;
+}
+
 hipError_t launch_sigma_ab(const cisigma_ctx *ctx, const void *cp, void *sp, int dtype, hipStream_t s,
-                           const int *wide) {
+                           const int *wide, const AbScratch &scratch) {
     if (ctx->na == 0 || ctx->nb == 0) return hipSuccess;
-    return dtype == CISIGMA_FP32 ? sigma_ab_t<float>(ctx, cp, sp, s, wide) : sigma_ab_t<double>(ctx, cp, sp, s, nullptr);
+    return dtype == CISIGMA_FP32 ? sigma_ab_t<float>(ctx, cp, sp, s, wide, scratch)
+                                 : sigma_ab_t<double>(ctx, cp, sp, s, nullptr, scratch);
 }
 
 }  // namespace cis

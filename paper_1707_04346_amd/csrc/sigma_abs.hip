@@ -31,6 +31,7 @@
 #include "internal.h"
 #include "bufio.h"
 #include "scatter_prog_dev.h"
+#include "slices.h"
 #include "split.h"
 
 #include <algorithm>
@@ -49,8 +50,10 @@ struct AbsArgs {
     const uint32_t *astr;    // [Na]
     const float *gp;         // [n*n][kp]
     const uint32_t *plan;    // [ntile][4 waves][words][64 lanes]
+    float *part;             // [slices - 1][Na][ld]: the sums of the later slices of the tiles
     const int *wide;         // nonzero: C has elements outside the split's range
     int exact;               // nonzero: the integrals have
+    size_t part_bytes;       // (host)
     uint32_t cp_bytes, plan_bytes;   // < 2^31
     int anexc, n, kp, npair, Na, ld;
 };
@@ -133,9 +136,12 @@ __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int
     }
     uint32_t boffI = 0;
     if constexpr (!SELF) boffI = (uint32_t(Ia) * uint32_t(p.ld) + uint32_t(cb * 16 + 4 * lk)) * 4u;
-    const __amdgpu_buffer_rsrc_t cr = buffer_of(p.cp, p.cp_bytes);
-    const __amdgpu_buffer_rsrc_t pr = buffer_of(p.plan, p.plan_bytes);
-    const int ntile = p.ld / kNT;
+    // from this slice's first tile on
+    const SliceTiles sl(p.ld / kNT);
+    const int ntile = sl.t1 - sl.t0;
+    const uint32_t coff = uint32_t(sl.t0) * kNT, poff = uint32_t(sl.t0) * uint32_t(kProgWaves * ProgWords<float, PG>::NW * 64);
+    const __amdgpu_buffer_rsrc_t cr = buffer_of(p.cp + coff, p.cp_bytes - coff * 4u);
+    const __amdgpu_buffer_rsrc_t pr = buffer_of(p.plan + poff, p.plan_bytes - poff * 4u);
     float b[KS][8];
     bf_floatx4 cI{}, cN{};
     floatx4 acc[NRA];
@@ -250,9 +256,11 @@ __global__ __launch_bounds__(256, 2) void k_sigma_ab_s(AbsArgs p) {
     const int Ia = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wide = *p.wide;                              // (in flight while the row is read)
-    float *row = p.sp + int64_t(Ia) * p.ld;
+    // the first slice adds to the sigma row, the others to zeros
+    float *row = slice_row(p.sp, p.part, Ia, p.Na, p.ld);
     for (int c = tid * 4; c < p.ld; c += 1024)
-        *reinterpret_cast<floatx4 *>(sig + c) = *reinterpret_cast<const floatx4 *>(row + c);
+        *reinterpret_cast<floatx4 *>(sig + c) =
+            blockIdx.y == 0 ? *reinterpret_cast<const floatx4 *>(row + c) : floatx4{0, 0, 0, 0};
     for (int r = tid; r < MP; r += 256) W[r * kWS + kNT] = 0.0f;   // pad column: unused references read it
     if (p.exact | __builtin_amdgcn_readfirstlane(wide)) {   // one answer for the whole launch
         if (wave < 2) abs_body<KS, R0, RB, PG, SELF, true>(p, W, Ia, wave & 1, 0, wave, lane);
@@ -278,8 +286,9 @@ hipError_t run_abs(const AbsArgs &a, hipStream_t s, bool alone) {
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((k_sigma_ab_s<KS, RB, PG, SELF>), dim3(a.Na), dim3(256), lds, s, a);
-    return hipGetLastError();
+    const int ns = slices(a.Na, a.ld, sizeof(float), a.part_bytes, kPlaces32);
+    hipLaunchKernelGGL((k_sigma_ab_s<KS, RB, PG, SELF>), dim3(a.Na, ns), dim3(256), lds, s, a);
+    return add_slices<float>(a.sp, a.part, int64_t(a.Na) * a.ld, ns, s);
 }
 
 // Compiled (KS, RB, program): a space of n orbitals has RB = ceil(n(n+1)/32) and
@@ -307,8 +316,8 @@ bool split_integrals_exact(const std::vector<float> &g) {
     return true;
 }
 
-bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *cp, void *sp, const int *wide, hipStream_t s,
-                           hipError_t *err) {
+bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *cp, void *sp, const int *wide, const AbScratch &scratch,
+                           hipStream_t s, hipError_t *err) {
     const ProgPlan &P = ctx->prog;
     if (!P.d_words || !wide) return false;
     const auto &A = ctx->sp[0];
@@ -320,6 +329,8 @@ bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *cp, void *sp, con
     x.gp = ctx->d_gp32;
     x.plan = P.d_words;
     x.wide = wide;
+    x.part = static_cast<float *>(scratch.p);
+    x.part_bytes = scratch.bytes;
     x.exact = ctx->split_exact ? 0 : 1;
     x.anexc = A.nexc;
     x.n = ctx->n;

@@ -46,6 +46,7 @@
 #include "mfma.h"
 #include "bufio.h"
 #include "scatter_prog_dev.h"
+#include "slices.h"
 
 #include <algorithm>
 
@@ -62,6 +63,8 @@ struct AbxArgs {
     const uint32_t *astr;    // [Na]
     const double *gp;        // [n*n][kp]
     const uint32_t *plan;    // [ntile][4 waves][words][64 lanes]
+    double *part;            // [slices - 1][Na][ld]: the sums of the later slices of the tiles
+    size_t part_bytes;       // (host)
     uint32_t cp_bytes, plan_bytes;   // < 2^31
     int anexc, n, kp, npair, Na, ld;
 };
@@ -90,7 +93,7 @@ __device__ __forceinline__ double self_coef(const AbxArgs &p, uint32_t xa, int m
 // One wave: KS k steps of four gathered rows, NQ quads of W rows from row m0 on,
 // column half cb; rounds R0 .. R1 - 1 of scatter quarter sw.  A wave without rounds
 // meets the scattering ones ("W of this tile consumed") half way through its products.
-template <int KS, int NQ, int RB, int PG, bool SELF, int R0, int R1>
+template <int KS, int NQ, int RB, int PG, bool SELF, bool SL, int R0, int R1>
 __device__ __forceinline__ void abx_body(const AbxArgs &p, int Ia, int cb, int m0, int sw, int lane) {
     constexpr int NB = NQ / 4, NS = NQ % 4, NF = NB + NS > 0 ? NB + NS : 1;   // whole blocks, single quads, fragments
     constexpr uint32_t SC = 16 * RB * kWS * 8u, SIG = SC + kProgWaves * 64 * 8u;
@@ -149,9 +152,14 @@ __device__ __forceinline__ void abx_body(const AbxArgs &p, int Ia, int cb, int m
         }
         boffI = (uint32_t(Ia) * uint32_t(p.ld) + col) * 8u;   // < cp_bytes
     }
-    const __amdgpu_buffer_rsrc_t cr = buffer_of(p.cp, p.cp_bytes);
-    const __amdgpu_buffer_rsrc_t pr = buffer_of(p.plan, p.plan_bytes);
-    const int ntile = p.ld / kNT;
+    // with slices from this one's first tile on
+    const int nt = p.ld / kNT;
+    const SliceTiles sl(nt);
+    const int ntile = SL ? sl.t1 - sl.t0 : nt;
+    const uint32_t coff = SL ? uint32_t(sl.t0) * kNT : 0u;
+    const uint32_t poff = SL ? uint32_t(sl.t0) * uint32_t(kProgWaves * ProgWords<double, PG, R0, R1>::NW * 64) : 0u;
+    const __amdgpu_buffer_rsrc_t cr = buffer_of(p.cp + coff, p.cp_bytes - coff * 8u);
+    const __amdgpu_buffer_rsrc_t pr = buffer_of(p.plan + poff, p.plan_bytes - poff * 4u);
     double b[KS], cI = 0;
     doublex4 acc[NB > 0 ? NB : 1];
     double accq[NS > 0 ? NS : 1];
@@ -221,16 +229,18 @@ __device__ __forceinline__ void abx_body(const AbxArgs &p, int Ia, int cb, int m
 
 // KS: k steps (4*KS >= excitations, plus one with SELF); Q: quads of W rows (4*Q >=
 // npair); RB: 16-row blocks that the program's W has room for; PG: program
-template <int KS, int Q, int RB, int PG, bool SELF>
+template <int KS, int Q, int RB, int PG, bool SELF, bool SL>
 __global__ __launch_bounds__(512, 2) void k_sigma_ab_x(AbxArgs p) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double *W = reinterpret_cast<double *>(smem_raw);      // [16 RB][kWS], then the waves' scratch
     double *sig = W + 16 * RB * kWS + kProgWaves * 64;     // [ld + 64]: slots ld.. take discarded writes
     const int Ia = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = wave >> 1, cb = wave & 1;
-    double *row = p.sp + int64_t(Ia) * p.ld;
+    // the first slice adds to the sigma row, the others to zeros
+    double *row = SL ? slice_row(p.sp, p.part, Ia, p.Na, p.ld) : p.sp + int64_t(Ia) * p.ld;
     for (int c = tid * 2; c < p.ld; c += 1024)
-        *reinterpret_cast<double2_t *>(sig + c) = *reinterpret_cast<const double2_t *>(row + c);
+        *reinterpret_cast<double2_t *>(sig + c) =
+            !SL || blockIdx.y == 0 ? *reinterpret_cast<const double2_t *>(row + c) : double2_t{0, 0};
     for (int r = tid; r < 16 * RB; r += 512) W[r * kWS + kNT] = 0.0;   // pad column: unused references read it
     static_assert(group_quad0(Q, 3) + group_quads(Q, 3) == Q && 4 * Q <= 16 * RB, "every quad has a wave");
     constexpr int NR = kProgs[PG].nr;
@@ -238,10 +248,10 @@ __global__ __launch_bounds__(512, 2) void k_sigma_ab_x(AbxArgs p) {
     // all waves scatter, w and w + 4 the first round and the others of a quarter, or
     // waves 4 to 7 do, beside the products of the others (see above)
     constexpr int LO = RB > 5 ? 1 : 0;
-    if (g == 0) abx_body<KS, group_quads(Q, 0), RB, PG, SELF, 0, LO>(p, Ia, cb, 0, sw, lane);
-    else if (g == 1) abx_body<KS, group_quads(Q, 1), RB, PG, SELF, 0, LO>(p, Ia, cb, 4 * group_quad0(Q, 1), sw, lane);
-    else if (g == 2) abx_body<KS, group_quads(Q, 2), RB, PG, SELF, LO, NR>(p, Ia, cb, 4 * group_quad0(Q, 2), sw, lane);
-    else abx_body<KS, group_quads(Q, 3), RB, PG, SELF, LO, NR>(p, Ia, cb, 4 * group_quad0(Q, 3), sw, lane);
+    if (g == 0) abx_body<KS, group_quads(Q, 0), RB, PG, SELF, SL, 0, LO>(p, Ia, cb, 0, sw, lane);
+    else if (g == 1) abx_body<KS, group_quads(Q, 1), RB, PG, SELF, SL, 0, LO>(p, Ia, cb, 4 * group_quad0(Q, 1), sw, lane);
+    else if (g == 2) abx_body<KS, group_quads(Q, 2), RB, PG, SELF, SL, LO, NR>(p, Ia, cb, 4 * group_quad0(Q, 2), sw, lane);
+    else abx_body<KS, group_quads(Q, 3), RB, PG, SELF, SL, LO, NR>(p, Ia, cb, 4 * group_quad0(Q, 3), sw, lane);
     __syncthreads();
     for (int c = tid * 2; c < p.ld; c += 1024)
         *reinterpret_cast<double2_t *>(row + c) = *reinterpret_cast<const double2_t *>(sig + c);
@@ -249,17 +259,24 @@ __global__ __launch_bounds__(512, 2) void k_sigma_ab_x(AbxArgs p) {
 
 size_t abx_lds(int ld, int rb) { return (size_t(16) * rb * kWS + kProgWaves * 64 + ld + 64) * sizeof(double); }
 
-template <int KS, int Q, int RB, int PG, bool SELF>
-hipError_t run_abx(const AbxArgs &a, hipStream_t s) {
+// (the slices in a kernel of their own: their bounds cost the others 1 to 4%)
+template <int KS, int Q, int RB, int PG, bool SELF, bool SL>
+hipError_t run_abx_sl(const AbxArgs &a, int ns, hipStream_t s) {
     const size_t lds = abx_lds(a.ld, RB);
-    if (4 * Q < a.npair || 4 * KS < a.anexc + (SELF ? 1 : 0)) return hipErrorInvalidValue;
     if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sigma_ab_x<KS, Q, RB, PG, SELF>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sigma_ab_x<KS, Q, RB, PG, SELF, SL>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((k_sigma_ab_x<KS, Q, RB, PG, SELF>), dim3(a.Na), dim3(512), lds, s, a);
-    return hipGetLastError();
+    hipLaunchKernelGGL((k_sigma_ab_x<KS, Q, RB, PG, SELF, SL>), dim3(a.Na, ns), dim3(512), lds, s, a);
+    return add_slices<double>(a.sp, a.part, int64_t(a.Na) * a.ld, ns, s);
+}
+
+template <int KS, int Q, int RB, int PG, bool SELF>
+hipError_t run_abx(const AbxArgs &a, hipStream_t s) {
+    if (4 * Q < a.npair || 4 * KS < a.anexc + (SELF ? 1 : 0)) return hipErrorInvalidValue;
+    const int ns = slices(a.Na, a.ld, sizeof(double), a.part_bytes, kPlaces64);
+    return ns > 1 ? run_abx_sl<KS, Q, RB, PG, SELF, true>(a, ns, s) : run_abx_sl<KS, Q, RB, PG, SELF, false>(a, 1, s);
 }
 
 // Compiled (KS, Q, RB, program), by ascending KS: for each RB = ceil(n(n+1)/32) the
@@ -317,7 +334,8 @@ void sigma_ab_owner_shape(int anexc, int npair, int ew, int *shape) {
 #undef CIS_R1
 }
 
-bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipError_t *err) {
+bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *cp, void *sp, const AbScratch &scratch, hipStream_t s,
+                           hipError_t *err) {
     if (launch_sigma_ab_list(ctx, cp, sp, s, err)) return true;
     const ProgPlan &P = ctx->prog;
     if (!P.d_words) return false;
@@ -329,6 +347,8 @@ bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *cp, void *sp, hip
     x.astr = A.d_str;
     x.gp = ctx->d_gp64;
     x.plan = P.d_words;
+    x.part = static_cast<double *>(scratch.p);
+    x.part_bytes = scratch.bytes;
     x.anexc = A.nexc;
     x.n = ctx->n;
     x.kp = ctx->kp;
