@@ -281,7 +281,7 @@ def stored_traffic(kernel_tag):
     import hashlib
     csrc = os.path.join(ROOT, "paper_1707_04346_amd", "csrc")
     one_block = kernel_tag == "k_sigma_ab_s"
-    srcs = [os.path.join(csrc, f) for f in (("sigma_abs.hip", "scatter_prog.h", "scatter_prog_dev.h", "split.h") if one_block else ("sigma_ab.hip",))]
+    srcs = [os.path.join(csrc, f) for f in (("sigma_abs.hip", "scatter_prog.h", "scatter_prog_dev.h", "slices.h", "split.h") if one_block else ("sigma_ab.hip",))]
     prof = os.path.join(ROOT, "profiles", f"{kernel_tag}_cas16_fp32_traffic.txt")
     if not (all(os.path.exists(f) for f in srcs) and os.path.exists(prof)):
         return None

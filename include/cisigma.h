@@ -423,10 +423,11 @@ int cisigma_pass_times(cisigma_ctx *ctx, double *ms, int *ncalls);
  * cisigma_last_path -- which kernels the most recent cisigma_apply of dtype
  * used, as CISIGMA_PATH_* flags in *flags (0 before any apply).  One-block
  * (CAS) and GAS spaces, with or without point-group symmetry, normally take
- * the materialised same-spin form; sigma_3 takes an owner-computes kernel
- * except with point-group symmetry.  Shapes outside the fast kernels' range,
- * spaces whose stored rows do not fit in memory, and CISIGMA_OPT_SIGMA_PATH = 1
- * use the general scatter kernels (flag clear).
+ * the materialised same-spin form, and sigma_3 an owner-computes kernel.
+ * Shapes outside the fast kernels' range (one-block spaces with more than 11
+ * electrons of a spin for the stored rows), spaces whose stored rows do not fit
+ * in memory, small spaces for which no unit kernel was made, and
+ * CISIGMA_OPT_SIGMA_PATH = 1 use the general scatter kernels (flag clear).
  */
 #define CISIGMA_PATH_AB_OWNER 1          /* sigma_3 by the owner-computes kernel (no global atomics) */
 #define CISIGMA_PATH_SS_MATERIALISED 2   /* same-spin parts by materialised pair products + gather */

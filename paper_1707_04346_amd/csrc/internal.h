@@ -350,12 +350,12 @@ bool launch_sigma_ab_gas(const cisigma_ctx *ctx, const void *C, void *sigma, int
 // columns, a multiple of 64) and gather into Y, overwriting Y.
 hipError_t launch_sigma_same_spin(const cisigma_ctx *ctx, int spin, const void *X, void *Y, int dtype,
                                   hipStream_t s, void *Ys = nullptr, int chunk = 0);
-// whether the same-spin pair count npv has compiled MFMA kernels (else a plain
-// atomic kernel serves it and the materialised form is not used)
 // Both spins of a one-block space (two or more electrons each) by one launch of each
 // kernel; X, Y, Ys by spin, Ys all columns.
 hipError_t launch_same_spin_both(const cisigma_ctx *ctx, const void *const *X, void *const *Y, int dtype, hipStream_t s,
                                  void *const *Ys);
+// whether the same-spin pair count npv has compiled MFMA kernels (else a plain
+// atomic kernel serves it and the materialised form is not used)
 bool same_spin_materialisable(int npv);
 // smallest compiled same-spin pair-kernel shape (k steps, 16-row blocks) for
 // lists of `count` pairs; false when none is compiled

@@ -44,8 +44,9 @@ struct RdmArgs {
 };
 
 // The FP64 form.
-template <typename T, int NT>
-__global__ __launch_bounds__(512, 1) void k_rdm(RdmArgs<T> p) {
+template <int NT>
+__global__ __launch_bounds__(512, 1) void k_rdm(RdmArgs<double> p) {
+    using T = double;
     using M = Mfma<T>;
     using acc_t = typename M::acc_t;
     // D is stored with the columns of a tile permuted so that the k steps a lane
@@ -266,12 +267,13 @@ __global__ __launch_bounds__(512, 1) void k_rdm(RdmArgs<T> p) {
 //
 // What bounds it (CAS(14,14): 6.4 ms, in the FP64 kernel's form 7.1): the FP32 matrix
 // instructions, 4.1 ms with 91 block pairs on 96 slots, keep their SIMD from issuing the
-// build's vector instructions.  (Exact three-way splits on the bf16 matrix cores took
-// 5.2 ms and left the sums a hundred times closer to FP64, which is another result than
-// this kernel's by more than a density's 1e-9.  In FP64 this form is slower: 11.4 ms
-// against 11.2 at 14 orbitals, 50 against 45 at 15.)
-template <typename T, int NT, int SLOTS>
-__global__ __launch_bounds__(512, 2) void k_rdm2(RdmArgs<T> p) {
+// build's vector instructions.  (Three-way splits on the bf16 matrix cores took 5.2 ms and
+// left the sums a hundred times closer to 64 bits; not taken, because every FP64 density a
+// program gets for an FP32 vector would move in its seventh digit.  In FP64 this form is
+// slower: 11.4 ms against 11.2 at 14 orbitals, 50 against 45 at 15.)
+template <int NT, int SLOTS>
+__global__ __launch_bounds__(512, 2) void k_rdm2(RdmArgs<float> p) {
+    using T = float;
     using M = Mfma<T>;
     using acc_t = typename M::acc_t;
     // D is stored with the columns of a tile permuted so that the k steps a lane
@@ -529,10 +531,10 @@ constexpr size_t kRdmLds = 160 * 1024;
 template <int SLOTS>
 hipError_t run_rdm2(const RdmArgs<float> &a, int grid, size_t lds, hipStream_t s) {
     constexpr int NT = rdm_nt<float>();
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rdm2<float, NT, SLOTS>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rdm2<NT, SLOTS>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_rdm2<float, NT, SLOTS>), dim3(grid), dim3(512), lds, s, a);
+    hipLaunchKernelGGL((k_rdm2<NT, SLOTS>), dim3(grid), dim3(512), lds, s, a);
     return hipGetLastError();
 }
 
@@ -590,10 +592,10 @@ hipError_t launch_rdm(const cisigma_ctx *ctx, const void *cp, int dtype, double 
         fill(a);
         a.cp = static_cast<const double *>(cp);
         constexpr int NT = rdm_nt<double>();
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rdm<double, NT>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rdm<NT>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_rdm<double, NT>), dim3(G), dim3(512), lds, s, a);
+        hipLaunchKernelGGL((k_rdm<NT>), dim3(G), dim3(512), lds, s, a);
         e = hipGetLastError();
     }
     if (e != hipSuccess) return e;

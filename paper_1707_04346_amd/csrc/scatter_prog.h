@@ -24,7 +24,7 @@
 // 0..14 the element's offset in `unit` bytes from the start of W, bit 15 the sign.  Slot:
 // the sigma element in `sunit` bytes.  (One 32-bit word a field, which takes fewer
 // vector instructions, doubles the plan's traffic: FP64 sigma_3 of CAS(16,16) 61.7
-// instead of 54.8 ms, FP32 19.6 instead of 18.9.)
+// instead of 54.8 ms, FP32 19.6 instead of 18.9, both when taken.)
 #pragma once
 
 #include <algorithm>

@@ -109,7 +109,8 @@ __device__ __forceinline__ void abg_scatter_ch(const T *W, T *sig, const uint32_
 }
 
 // Point-group items multiply few k steps and row blocks and wait for their loads
-// instead: two workgroups share a compute unit there
+// instead: two workgroups share a compute unit there, where their registers leave room
+// (21 x 11 takes 154 to 162 in FP32; two workgroups leave 128)
 template <int KS, int RB, int NW, bool RTK>
 constexpr int kAbgWaves = RTK && KS * RB <= 17 * 9 ? NW / 2 : 1;   // waves per SIMD at least
 
@@ -119,12 +120,12 @@ __global__ __launch_bounds__(64 * NW, (kAbgWaves<KS, RB, NW, RTK>)) void k_sigma
     using acc_t = typename M::acc_t;
     constexpr int NT = 64 * NW;                             // threads
     // FP64 shapes whose half of the A fragments alone would take more than 320
-    // registers per lane: every wave multiplies both 16-column halves for a quarter
-    // of the row blocks (strided over the waves), so it holds a quarter of the
-    // fragments (GAS(20,20), 26 k steps x 14 row blocks: 234 registers spilled
-    // before; sigma_3 93.7 -> 82.9 ms).  Smaller shapes keep two row groups x two
-    // column halves: the strided split leaves their row blocks uneven (CAS(16,16)
-    // D2h, 9 row blocks: 84.1 -> 92.6 ms with it).
+    // registers per lane (point-group spaces, two workgroups a compute unit: 120):
+    // every wave multiplies both 16-column halves for a quarter of the row blocks
+    // (strided over the waves), so it holds a quarter of the fragments (GAS(20,20), 26 k
+    // steps x 14 row blocks: 234 registers spilled before; sigma_3 93.7 -> 82.9 ms).
+    // Smaller shapes keep two row groups x two column halves: the strided split leaves
+    // their row blocks uneven.
     constexpr bool FC = sizeof(T) == 8 && (RB + 1) / 2 * KS * 2 > (RTK ? 120 : 320);
     constexpr int NH = FC ? 2 : 1;                          // column halves per wave
     constexpr int NG = FC ? NW : NW / 2;                    // row-block groups (x 2 / NH column halves)
@@ -640,7 +641,8 @@ hipError_t run_abgw(const AbgArgs<T> &a, int na, hipStream_t s) {
 // CAS(8,8) and CAS(10,10) split into units, CAS(8,8) with point-group symmetry),
 // GAS(20,20) 6/8/6, CAS(18,18) (whose sigma row is too long for the one-block
 // kernel), and 12, 14 and 16 orbitals.  A space takes the smallest shape that
-// holds it (gas_shape_for): missing k steps and W rows are zeros and never active
+// holds it (sigma_ab_gas_shape; by a rule in build_gas_owner where it was made for
+// others): missing k steps and W rows are zeros and never active
 #define CIS_ABG_SHAPES(X) \
     X(3, 2, 4) X(3, 2, 16) X(4, 2, 4) X(4, 2, 16) X(4, 3, 4) X(4, 3, 16) X(5, 3, 4) X(5, 3, 16) X(5, 4, 4) \
     X(5, 4, 16) X(7, 5, 4) X(7, 5, 16) X(10, 5, 4) X(10, 5, 16) X(13, 7, 4) X(13, 7, 16) X(26, 14, 16) \

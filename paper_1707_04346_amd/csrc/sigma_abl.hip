@@ -8,11 +8,14 @@
 //   sigma(Ia, Ib) += sum_{(kl, Jb): Ib = E_kl Jb} <Ib|E_kl|Jb> W(kl, Jb);
 // Ia's own row takes a k slot (SELF) or starts the accumulators as a rank-1 term.
 //
-// Why it stays: with at most 252 strings a launch is one workgroup per compute unit
-// and a handful of tiles, and a call's other launches take most of its time: CAS(10,10)
-// takes 26 us here and 15 in the quad form, of ~50 for a sigma.  But the sums run in list
-// order, as ever: the signs of the vectors of a Davidson at its 1e-12 hang on the last
-// bits of sigma (with the quad form's sums 8 of 18 vectors came out negated).
+// Why it stays beside the quad form: its sums run in list order, as ever, so FP64 results
+// of these spaces are what they were, bit for bit -- the signs of the vectors of a Davidson
+// at its 1e-12 hang on the last bits of sigma (with the quad form's sums 8 of 18 came out
+// negated) -- and little time is lost: with at most 252 strings a launch is one workgroup
+// per compute unit and a handful of tiles, and a call's other launches take most of its
+// time (CAS(10,10): 26 us here and 15 in the quad form, of ~50 for a sigma).  From 11
+// orbitals on the quad form takes 0.6 of a sigma's time and the sums did change order; the
+// vectors' signs there are as arbitrary as they were.
 #include "internal.h"
 #include "mfma.h"
 #include "bufio.h"
@@ -23,8 +26,10 @@
 namespace cis {
 namespace {
 
+using T = double;
+using acc_t = Mfma<T>::acc_t;
+using vec_t = Mfma<T>::vec_t;
 
-template <typename T>
 struct AbxArgs {
     const T *cp;           // C, alpha-major padded (row stride ld)
     T *sp;                 // sigma accumulator, same layout (read, then overwritten)
@@ -37,17 +42,13 @@ struct AbxArgs {
     int anexc, n, kp, npair, Na, ld;
 };
 
-
-// ---- pieces of the two kernel forms ------------------------------------------
-//
 // KS: k steps over the gathered rows (4*KS >= anexc+1); RB: 16-row blocks of kl
 // (16*RB >= npair); RBW: row blocks per producing wave; EW: plan entries per
 // lane and tile.  A producing wave owns one 16-column half of the 32-column
 // tile (cb) and a run of row blocks [rb0, rb0 + nrb).
 
 // A(m, Ia) = sum_{j in Ia} (jj|kl) for the kl pair of row m
-template <typename T>
-__device__ __forceinline__ T abx_self_coef(const AbxArgs<T> &p, uint32_t xa, int m) {
+__device__ __forceinline__ T abx_self_coef(const AbxArgs &p, uint32_t xa, int m) {
     T val = 0;
     for (uint32_t b = xa; b; b &= b - 1) {
         const int j = __ffs(b) - 1;
@@ -60,8 +61,8 @@ __device__ __forceinline__ T abx_self_coef(const AbxArgs<T> &p, uint32_t xa, int
 // lane%16, column k = 4t + lane/16 -- and the byte offsets of the gathered rows
 // (missing excitations read the zero row Na).  With SELF, column anexc is Ia's
 // own row.
-template <typename T, int KS, int RBW, bool SELF>
-__device__ __forceinline__ void abx_fragments(const AbxArgs<T> &p, int Ia, int lane, int cb, int rb0, int nrb,
+template <int KS, int RBW, bool SELF>
+__device__ __forceinline__ void abx_fragments(const AbxArgs &p, int Ia, int lane, int cb, int rb0, int nrb,
                                               T (&A)[RBW][KS], uint32_t (&boff)[KS]) {
     const uint32_t xa = p.astr[Ia];
     const uint32_t col = uint32_t(cb * 16 + (lane & 15));
@@ -101,8 +102,8 @@ __device__ __forceinline__ void abx_fragments(const AbxArgs<T> &p, int Ia, int l
 
 // Without SELF: A(m, Ia) for the lane's accumulator rows m = 16*(rb0 + r) +
 // out_row(lane, i), and the byte offset of C(Ia, column) of the lane's column
-template <typename T, int RBW>
-__device__ __forceinline__ void abx_self_fragments(const AbxArgs<T> &p, int Ia, int lane, int cb, int rb0, int nrb,
+template <int RBW>
+__device__ __forceinline__ void abx_self_fragments(const AbxArgs &p, int Ia, int lane, int cb, int rb0, int nrb,
                                                    T (&dI)[RBW][4], uint32_t &boffI) {
     using M = Mfma<T>;
     const uint32_t xa = p.astr[Ia];
@@ -116,7 +117,7 @@ __device__ __forceinline__ void abx_self_fragments(const AbxArgs<T> &p, int Ia, 
     boffI = (uint32_t(Ia) * uint32_t(p.ld) + uint32_t(cb * 16 + (lane & 15))) * uint32_t(sizeof(T));   // < cp_bytes
 }
 
-template <typename T, int KS>
+template <int KS>
 __device__ __forceinline__ void abx_load(__amdgpu_buffer_rsrc_t cr, const uint32_t (&boff)[KS], int tile, T (&b)[KS]) {
     const uint32_t soff = uint32_t(tile) * uint32_t(kAbxNT * sizeof(T));
 #pragma unroll
@@ -128,20 +129,20 @@ __device__ __forceinline__ void abx_load(__amdgpu_buffer_rsrc_t cr, const uint32
 // tile), so the loads stay in flight for a whole tile.  Without SELF the
 // accumulators start from A(kl, Ia) C(Ia, Jb), cI holding C(Ia, Jb) of this
 // tile (reloaded likewise).
-template <typename T, int KS, int RBW, bool SELF>
+template <int KS, int RBW, bool SELF>
 __device__ __forceinline__ void abx_products(__amdgpu_buffer_rsrc_t cr, const T (&A)[RBW][KS],
                                              const uint32_t (&boff)[KS], int next, T (&b)[KS],
-                                             typename Mfma<T>::acc_t (&acc)[RBW], const T (&dI)[RBW][4],
+                                             acc_t (&acc)[RBW], const T (&dI)[RBW][4],
                                              uint32_t boffI, T &cI) {
     using M = Mfma<T>;
     const uint32_t soff = uint32_t(next) * uint32_t(kAbxNT * sizeof(T));
     if constexpr (SELF) {
 #pragma unroll
-        for (int r = 0; r < RBW; ++r) acc[r] = typename M::acc_t{0, 0, 0, 0};
+        for (int r = 0; r < RBW; ++r) acc[r] = acc_t{0, 0, 0, 0};
     } else {
 #pragma unroll
         for (int r = 0; r < RBW; ++r)
-            acc[r] = typename M::acc_t{dI[r][0] * cI, dI[r][1] * cI, dI[r][2] * cI, dI[r][3] * cI};
+            acc[r] = acc_t{dI[r][0] * cI, dI[r][1] * cI, dI[r][2] * cI, dI[r][3] * cI};
         buffer_ld(cI, cr, boffI, soff);
     }
 #pragma unroll
@@ -153,8 +154,8 @@ __device__ __forceinline__ void abx_products(__amdgpu_buffer_rsrc_t cr, const T 
     }
 }
 
-template <typename T, int RBW>
-__device__ __forceinline__ void abx_store_w(T *W, const typename Mfma<T>::acc_t (&acc)[RBW], int lane, int cb,
+template <int RBW>
+__device__ __forceinline__ void abx_store_w(T *W, const acc_t (&acc)[RBW], int lane, int cb,
                                             int rb0, int nrb) {
     using M = Mfma<T>;
 #pragma unroll
@@ -165,8 +166,6 @@ __device__ __forceinline__ void abx_store_w(T *W, const typename Mfma<T>::acc_t 
                 W[((rb0 + r) * 16 + M::out_row(lane, i)) * kAbxWS + cb * 16 + (lane & 15)] = acc[r][i];
 }
 
-// ---- eight-wave form -------------------------------------------------------------
-//
 // On gfx950 an FP64 MFMA keeps its SIMD from issuing vector instructions of
 // other waves, so a scatter wave that shares a SIMD with a producing wave waits
 // out every matrix instruction.  The roles are therefore split by SIMD: the
@@ -177,10 +176,8 @@ __device__ __forceinline__ void abx_store_w(T *W, const typename Mfma<T>::acc_t 
 // leaves room for one W tile: the producing waves compute the next tile's W in
 // registers while the scatter waves consume this tile's, and store it between
 // two barriers.
-template <typename T, int KS, int RB, int EW, bool SELF>
-__global__ __launch_bounds__(512, 1) void k_sigma_ab_l(AbxArgs<T> p) {
-    using acc_t = typename Mfma<T>::acc_t;
-    using vec_t = typename Mfma<T>::vec_t;
+template <int KS, int RB, int EW, bool SELF>
+__global__ __launch_bounds__(512, 1) void k_sigma_ab_l(AbxArgs p) {
     constexpr int VEC = 16 / sizeof(T);
     constexpr int RBW = (RB + 2) / 3;
     constexpr int MP = 16 * RB;
@@ -204,27 +201,27 @@ __global__ __launch_bounds__(512, 1) void k_sigma_ab_l(AbxArgs<T> p) {
         const int nrb = RB - rb0 < RBW ? RB - rb0 : RBW;   // may be <= 0 for small RB
         T A[RBW][KS];
         uint32_t boff[KS];
-        abx_fragments<T, KS, RBW, SELF>(p, Ia, lane, cb, rb0, nrb, A, boff);
+        abx_fragments<KS, RBW, SELF>(p, Ia, lane, cb, rb0, nrb, A, boff);
         T dI[RBW][4] = {};
         uint32_t boffI = 0;
-        if constexpr (!SELF) abx_self_fragments<T, RBW>(p, Ia, lane, cb, rb0, nrb, dI, boffI);
+        if constexpr (!SELF) abx_self_fragments<RBW>(p, Ia, lane, cb, rb0, nrb, dI, boffI);
         const __amdgpu_buffer_rsrc_t cr = buffer_of(p.cp, p.cp_bytes);
         T b[KS];
         T cI = 0;
         acc_t acc[RBW];
-        abx_load<T, KS>(cr, boff, 0, b);
+        abx_load<KS>(cr, boff, 0, b);
         if constexpr (!SELF) buffer_ld(cI, cr, boffI, 0u);
-        abx_products<T, KS, RBW, SELF>(cr, A, boff, ntile > 1 ? 1 : 0, b, acc, dI, boffI, cI);
+        abx_products<KS, RBW, SELF>(cr, A, boff, ntile > 1 ? 1 : 0, b, acc, dI, boffI, cI);
         __syncthreads();                       // the sigma row is in LDS
-        abx_store_w<T, RBW>(W, acc, lane, cb, rb0, nrb);
+        abx_store_w<RBW>(W, acc, lane, cb, rb0, nrb);
         __syncthreads();                       // W of tile 0 ready
         for (int tile = 0; tile < ntile; ++tile) {
             if (tile + 1 < ntile) {
                 const int t2 = tile + 2 < ntile ? tile + 2 : ntile - 1;
-                abx_products<T, KS, RBW, SELF>(cr, A, boff, t2, b, acc, dI, boffI, cI);
+                abx_products<KS, RBW, SELF>(cr, A, boff, t2, b, acc, dI, boffI, cI);
             }
             __syncthreads();                   // W of this tile consumed
-            if (tile + 1 < ntile) abx_store_w<T, RBW>(W, acc, lane, cb, rb0, nrb);
+            if (tile + 1 < ntile) abx_store_w<RBW>(W, acc, lane, cb, rb0, nrb);
             __syncthreads();                   // W of the next tile ready
         }
     } else {
@@ -260,19 +257,18 @@ __global__ __launch_bounds__(512, 1) void k_sigma_ab_l(AbxArgs<T> p) {
 }
 
 // LDS bytes: the W tile and the sigma row with its 64 discard slots
-template <typename T>
 size_t abx_lds(int ld, int rb) {
     return (size_t(16) * rb * kAbxWS + ld + 64) * sizeof(T);
 }
 
-template <typename T, int KS, int RB, int EW, bool SELF>
-hipError_t run_abx(const AbxArgs<T> &a, hipStream_t s) {
-    const size_t lds = abx_lds<T>(a.ld, RB);
+template <int KS, int RB, int EW, bool SELF>
+hipError_t run_abx(const AbxArgs &a, hipStream_t s) {
+    const size_t lds = abx_lds(a.ld, RB);
     if (lds > 160 * 1024 || 16 * RB < a.npair || 4 * KS < a.anexc + (SELF ? 1 : 0)) return hipErrorInvalidValue;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sigma_ab_l<T, KS, RB, EW, SELF>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sigma_ab_l<KS, RB, EW, SELF>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_sigma_ab_l<T, KS, RB, EW, SELF>), dim3(a.Na), dim3(512), lds, s, a);
+    hipLaunchKernelGGL((k_sigma_ab_l<KS, RB, EW, SELF>), dim3(a.Na), dim3(512), lds, s, a);
     return hipGetLastError();
 }
 
@@ -290,19 +286,18 @@ int rb_of(int npair) { return (npair + 15) / 16; }
 // CAS(n, n/2) spaces of even n and their neighbours whose excitation count is
 // a multiple of 4 (there it saves a k step; elsewhere the row fills padding).
 // The 16-entry plan width serves spaces whose target groups would span more
-// than four lanes at the narrow width (CAS(8,8), CAS(12,12) and smaller).
+// than four lanes at the narrow width (CAS(8,8) and smaller).
 #define CIS_ABX_SHAPES_R1(X)                                                                            \
     X(1, 1, 2) X(1, 1, 16) X(2, 2, 2) X(2, 2, 16) X(4, 3, 4) X(4, 3, 16) X(6, 4, 4) X(6, 4, 16)
 
 // shape[4] receives {KS, RB, EW, 1: row in a k step, 2: rank-1 start}
-template <typename T>
-bool dispatch_abx(const AbxArgs<T> &a, int ew, hipStream_t s, hipError_t *err, int *shape, const char **name) {
+bool dispatch_abx(const AbxArgs &a, int ew, hipStream_t s, hipError_t *err, int *shape, const char **name) {
     const int rb = rb_of(a.npair);
     if (a.anexc > 0 && a.anexc % 4 == 0) {
         const int ks1 = a.anexc / 4;
 #define CIS_RUN1(K, R, E)                                           \
     if (ks1 == K && rb == R && ew == E) {                           \
-        *err = run_abx<T, K, R, E, false>(a, s);                    \
+        *err = run_abx<K, R, E, false>(a, s);                    \
         shape[0] = K; shape[1] = R; shape[2] = E; shape[3] = 2;     \
         *name = "k_sigma_ab_l<" #K ", " #R ", " #E ", rank1>";      \
         return true;                                                \
@@ -313,7 +308,7 @@ bool dispatch_abx(const AbxArgs<T> &a, int ew, hipStream_t s, hipError_t *err, i
     const int ks = ks_of(a.anexc);
 #define CIS_RUN(K, R, E)                                            \
     if (ks == K && rb == R && ew == E) {                            \
-        *err = run_abx<T, K, R, E, true>(a, s);                     \
+        *err = run_abx<K, R, E, true>(a, s);                     \
         shape[0] = K; shape[1] = R; shape[2] = E; shape[3] = 1;     \
         *name = "k_sigma_ab_l<" #K ", " #R ", " #E ", self>";       \
         return true;                                                \
@@ -324,12 +319,11 @@ bool dispatch_abx(const AbxArgs<T> &a, int ew, hipStream_t s, hipError_t *err, i
 }
 
 bool owner_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hipError_t *err) {
-    using T = double;
     const ScatterPlan &P = ctx->plan;
     const uint32_t *plan = P.d_entries[0];
     if (!plan || P.ew == 0) return false;
     const auto &A = ctx->sp[0];
-    AbxArgs<T> x{};
+    AbxArgs x{};
     x.cp = static_cast<const T *>(cp);
     x.sp = static_cast<T *>(sp);
     x.aexc = A.d_exc;
@@ -342,7 +336,7 @@ bool owner_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hi
     x.npair = ctx->npair;
     x.Na = A.nstr;
     x.ld = ctx->pl[0].ld[0];
-    if (abx_lds<T>(x.ld, rb_of(x.npair)) > 160 * 1024) return false;
+    if (abx_lds(x.ld, rb_of(x.npair)) > 160 * 1024) return false;
     // 32-bit byte offsets of the gathered rows (the zero row Na included) and of the plan
     const uint64_t cpb = (uint64_t(x.Na) + 1) * uint64_t(x.ld) * sizeof(T);
     const uint64_t plb = uint64_t(P.ntile) * 4 * (P.ew + 1) * 64 * sizeof(uint32_t);
@@ -350,7 +344,7 @@ bool owner_t(const cisigma_ctx *ctx, const void *cp, void *sp, hipStream_t s, hi
     x.cp_bytes = uint32_t(cpb);
     x.plan_bytes = uint32_t(plb);
     auto *c = const_cast<cisigma_ctx *>(ctx);
-    return dispatch_abx<T>(x, P.ew, s, err, c->last_shape[0], &c->last_kernel[0]);
+    return dispatch_abx(x, P.ew, s, err, c->last_shape[0], &c->last_kernel[0]);
 }
 
 }  // namespace

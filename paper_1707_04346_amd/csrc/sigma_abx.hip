@@ -63,10 +63,10 @@ struct AbxArgs {
     const uint32_t *astr;    // [Na]
     const double *gp;        // [n*n][kp]
     const uint32_t *plan;    // [ntile][4 waves][words][64 lanes]
-    double *part;            // [slices - 1][Na][ld]: the sums of the later slices of the tiles
-    size_t part_bytes;       // (host)
     uint32_t cp_bytes, plan_bytes;   // < 2^31
     int anexc, n, kp, npair, Na, ld;
+    double *part;            // [slices - 1][Na][ld]: the sums of the later slices of the tiles
+    size_t part_bytes;       // (host)
 };
 
 // Quads of wave group g (waves 2g and 2g + 1: the two column halves) of q in all.
@@ -152,14 +152,21 @@ __device__ __forceinline__ void abx_body(const AbxArgs &p, int Ia, int cb, int m
         }
         boffI = (uint32_t(Ia) * uint32_t(p.ld) + col) * 8u;   // < cp_bytes
     }
-    // with slices from this one's first tile on
-    const int nt = p.ld / kNT;
-    const SliceTiles sl(nt);
-    const int ntile = SL ? sl.t1 - sl.t0 : nt;
-    const uint32_t coff = SL ? uint32_t(sl.t0) * kNT : 0u;
-    const uint32_t poff = SL ? uint32_t(sl.t0) * uint32_t(kProgWaves * ProgWords<double, PG, R0, R1>::NW * 64) : 0u;
-    const __amdgpu_buffer_rsrc_t cr = buffer_of(p.cp + coff, p.cp_bytes - coff * 8u);
-    const __amdgpu_buffer_rsrc_t pr = buffer_of(p.plan + poff, p.plan_bytes - poff * 4u);
+    int ntile = p.ld / kNT;
+    const double *cp = p.cp;
+    const uint32_t *plan = p.plan;
+    uint32_t cp_bytes = p.cp_bytes, plan_bytes = p.plan_bytes;
+    if constexpr (SL) {                  // from this slice's first tile on
+        const SliceTiles sl(ntile);
+        const uint32_t poff = uint32_t(sl.t0) * uint32_t(kProgWaves * ProgWords<double, PG, R0, R1>::NW * 64);
+        ntile = sl.t1 - sl.t0;
+        cp += sl.t0 * kNT;
+        cp_bytes -= uint32_t(sl.t0) * (kNT * 8u);
+        plan += poff;
+        plan_bytes -= poff * 4u;
+    }
+    const __amdgpu_buffer_rsrc_t cr = buffer_of(cp, cp_bytes);
+    const __amdgpu_buffer_rsrc_t pr = buffer_of(plan, plan_bytes);
     double b[KS], cI = 0;
     doublex4 acc[NB > 0 ? NB : 1];
     double accq[NS > 0 ? NS : 1];
