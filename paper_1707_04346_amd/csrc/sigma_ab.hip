@@ -380,8 +380,8 @@ size_t sigma_ab_scratch(const cisigma_ctx *ctx, int dtype) {
     if (!ctx->prog.d_words) return 0;
     const bool f32 = dtype == CISIGMA_FP32;
     const size_t es = f32 ? 4 : 8;
-    const int ld = int(ctx->pl[0].ld[0]), Na = ctx->sp[0].nstr;
-    return size_t(slices(Na, ld, es, ~size_t(0), f32 ? kPlaces32 : kPlaces64) - 1) * size_t(Na) * size_t(ld) * es;
+    const int ld = int(ctx->pl[0].ld[0]), Na = ctx->sp[0].nstr, ntile = (ctx->sp[1].nstr + 31) / 32;
+    return size_t(slices(Na, ntile, ld, es, ~size_t(0), f32 ? kPlaces32 : kPlaces64) - 1) * size_t(Na) * size_t(ld) * es;
 }
 
 hipError_t launch_sigma_ab(const cisigma_ctx *ctx, const void *cp, void *sp, int dtype, hipStream_t s,

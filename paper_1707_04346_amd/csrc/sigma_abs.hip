@@ -56,6 +56,7 @@ struct AbsArgs {
     size_t part_bytes;       // (host)
     uint32_t cp_bytes, plan_bytes;   // < 2^31
     int anexc, n, kp, npair, Na, ld;
+    int ntile;               // tiles with a beta string (rows are padded to 64 columns)
 };
 
 // sum_{j in Ia} (jj|kl) for the kl pair of row m < npair: all loads at once
@@ -137,7 +138,7 @@ __device__ __forceinline__ void abs_body(const AbsArgs &p, float *W, int Ia, int
     uint32_t boffI = 0;
     if constexpr (!SELF) boffI = (uint32_t(Ia) * uint32_t(p.ld) + uint32_t(cb * 16 + 4 * lk)) * 4u;
     // from this slice's first tile on
-    const SliceTiles sl(p.ld / kNT);
+    const SliceTiles sl(p.ntile);
     const int ntile = sl.t1 - sl.t0;
     const uint32_t coff = uint32_t(sl.t0) * kNT, poff = uint32_t(sl.t0) * uint32_t(kProgWaves * ProgWords<float, PG>::NW * 64);
     const __amdgpu_buffer_rsrc_t cr = buffer_of(p.cp + coff, p.cp_bytes - coff * 4u);
@@ -286,7 +287,7 @@ hipError_t run_abs(const AbsArgs &a, hipStream_t s, bool alone) {
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
         if (e != hipSuccess) return e;
     }
-    const int ns = slices(a.Na, a.ld, sizeof(float), a.part_bytes, kPlaces32);
+    const int ns = slices(a.Na, a.ntile, a.ld, sizeof(float), a.part_bytes, kPlaces32);
     hipLaunchKernelGGL((k_sigma_ab_s<KS, RB, PG, SELF>), dim3(a.Na, ns), dim3(256), lds, s, a);
     return add_slices<float>(a.sp, a.part, int64_t(a.Na) * a.ld, ns, s);
 }
@@ -338,6 +339,7 @@ bool launch_sigma_ab_split(const cisigma_ctx *ctx, const void *cp, void *sp, con
     x.npair = ctx->npair;
     x.Na = A.nstr;
     x.ld = ctx->pl[0].ld[0];
+    x.ntile = (ctx->sp[1].nstr + kNT - 1) / kNT;
     const int rb = (x.npair + 15) / 16;
     if (abs_lds(x.ld, rb) > 160 * 1024) return false;
     // 32-bit byte offsets of the gathered rows (the zero row Na included) and of the plan

@@ -65,6 +65,7 @@ struct AbxArgs {
     const uint32_t *plan;    // [ntile][4 waves][words][64 lanes]
     uint32_t cp_bytes, plan_bytes;   // < 2^31
     int anexc, n, kp, npair, Na, ld;
+    int ntile;               // tiles with a beta string (rows are padded to 64 columns)
     double *part;            // [slices - 1][Na][ld]: the sums of the later slices of the tiles
     size_t part_bytes;       // (host)
 };
@@ -152,7 +153,7 @@ __device__ __forceinline__ void abx_body(const AbxArgs &p, int Ia, int cb, int m
         }
         boffI = (uint32_t(Ia) * uint32_t(p.ld) + col) * 8u;   // < cp_bytes
     }
-    int ntile = p.ld / kNT;
+    int ntile = p.ntile;
     const double *cp = p.cp;
     const uint32_t *plan = p.plan;
     uint32_t cp_bytes = p.cp_bytes, plan_bytes = p.plan_bytes;
@@ -282,7 +283,7 @@ hipError_t run_abx_sl(const AbxArgs &a, int ns, hipStream_t s) {
 template <int KS, int Q, int RB, int PG, bool SELF>
 hipError_t run_abx(const AbxArgs &a, hipStream_t s) {
     if (4 * Q < a.npair || 4 * KS < a.anexc + (SELF ? 1 : 0)) return hipErrorInvalidValue;
-    const int ns = slices(a.Na, a.ld, sizeof(double), a.part_bytes, kPlaces64);
+    const int ns = slices(a.Na, a.ntile, a.ld, sizeof(double), a.part_bytes, kPlaces64);
     return ns > 1 ? run_abx_sl<KS, Q, RB, PG, SELF, true>(a, ns, s) : run_abx_sl<KS, Q, RB, PG, SELF, false>(a, 1, s);
 }
 
@@ -362,6 +363,7 @@ bool launch_sigma_ab_owner(const cisigma_ctx *ctx, const void *cp, void *sp, con
     x.npair = ctx->npair;
     x.Na = A.nstr;
     x.ld = ctx->pl[0].ld[0];
+    x.ntile = (ctx->sp[1].nstr + kNT - 1) / kNT;
     const int rb = rb_of(x.npair);
     if (abx_lds(x.ld, rb) > 160 * 1024) return false;
     // 32-bit byte offsets of the gathered rows (the zero row Na included) and of the plan

@@ -38,11 +38,11 @@ __global__ __launch_bounds__(256) void k_add_slices(T *sp, const T *part, int64_
     sp[i] = v;
 }
 
-// Slices of a launch over Na rows of ld columns: workgroups up to `places`, at least four
+// Slices of a launch over Na rows of ld columns in ntile tiles: workgroups up to `places`, at least four
 // tiles each, and sums that fit the scratch.
-inline int slices(int Na, int ld, size_t es, size_t part_bytes, int places) {
+inline int slices(int Na, int ntile, int ld, size_t es, size_t part_bytes, int places) {
     const size_t row = size_t(Na) * size_t(ld) * es;
-    return std::max(1, std::min({places / Na, ld / 32 / 4, int(std::min<size_t>(part_bytes / row, 4096)) + 1}));
+    return std::max(1, std::min({places / Na, ntile / 4, int(std::min<size_t>(part_bytes / row, 4096)) + 1}));
 }
 
 template <typename T>
